@@ -57,6 +57,7 @@ def kernel_bytes(ctx, names, precision=0):
     fam = {
         "k_charges": n * (4 + 12 + 4) + nL * 16,
         "k_zcorr": n * (4 + 12 + 4) + nZ * 16,
+        "k_mprod": n * (4 + 4 + 12 + 4 + 4 + 12) + nL * 24 + nZ * 16,
         "k_anterp": n * (4 + 16) + nbox * 4 + ng * gb,
         "k_anterp_scatter": n * (4 + 16 + 4),
         "k_anterp_sum": ng * gb,

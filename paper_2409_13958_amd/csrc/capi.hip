@@ -26,6 +26,9 @@ constexpr int kFftzT = 256;          // threads per workgroup of the z pass
 constexpr int kFftSplit = 2;         // workgroups per z-plane in the plane transforms
 constexpr int kIcLdsBudget = 24576;  // LDS bytes per interpolation tile
 constexpr int kScTile[3] = {8, 8, 4};  // preferred boxes per scatter tile along x, y, z
+// unknowns from which the element correction and the exchange run on a second
+// stream beside the grid steps
+constexpr int64_t kOverlapMin = 300000;
 constexpr int kScLdsBudget = 65536;    // LDS bytes of a scatter tile's footprint copies
 
 // Scratch of pmfem_grid_convolve_noalloc: the half-spectrum of one grid
@@ -274,6 +277,7 @@ int select_variants(pmfem_ctx* c) {
   d->kname[1] = d->ant_scatter ? "k_anterp_scatter" : d->ant_line ? "k_anterp_line" : "k_anterp";
   if (d->ant_scatter) d->kname[11] = "k_anterp_sum";
   d->kname[7] = "k_interp_tile";
+  if (d->n < kOverlapMin) d->kname[0] = "k_mprod";  // slots 9 and 10 stay empty
   return PMFEM_OK;
 }
 
@@ -1030,6 +1034,28 @@ void launch_interp(const IcPlan& pl, dim3 grid, dim3 blk, size_t lds, hipStream_
 #undef PMFEM_IC_LAUNCH
 }
 
+// Every product of m in one launch on stream s (k_mprod), for cells below
+// kOverlapMin unknowns; mx the magnetisation the exchange reads.
+template <typename MT>
+void launch_mprod(hipStream_t s, int64_t n, int gl, int gz, bool with_ex, const MProd& a,
+                  const float* m, const MT* mx) {
+  const unsigned nbl = (unsigned)((n * gl + 255) / 256), nbz = (unsigned)((n * gz + 255) / 256);
+  const dim3 grid(nbl * (with_ex ? 2 : 1) + nbz), blk(256);
+#define PMFEM_MP(GL, GZ)                                                                    \
+  if (gl == GL && gz == GZ)                                                                 \
+    hipLaunchKernelGGL((k_mprod<GL, GZ, MT>), grid, blk, 0, s, n, nbl, nbz, a, m, mx)
+  PMFEM_MP(4, 4);
+  PMFEM_MP(4, 8);
+  PMFEM_MP(4, 16);
+  PMFEM_MP(8, 4);
+  PMFEM_MP(8, 8);
+  PMFEM_MP(8, 16);
+  PMFEM_MP(16, 4);
+  PMFEM_MP(16, 8);
+  PMFEM_MP(16, 16);
+#undef PMFEM_MP
+}
+
 int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const double* happ,
              const double* m64 = nullptr) {
   pmfem_dev* d = c->dev;
@@ -1075,7 +1101,14 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
     else
       hipLaunchKernelGGL(k_rowdot3<16>, grid, dim3(T), 0, st, n, m, rp, rec, out);
   };
-  if (with_ms) {
+  const bool overlap = n >= kOverlapMin;
+  if (with_ms && !overlap) {
+    mark(0, 0);
+    const MProd mp = {d->lrp, d->zrp, d->drec, d->zrec, d->lrec, d->q, d->uz, d->hex};
+    if (m64) launch_mprod(s, n, d->lanes_l, d->lanes_z, with_ex, mp, m, m64);
+    else launch_mprod(s, n, d->lanes_l, d->lanes_z, with_ex, mp, m, m);
+    mark(0, 1);
+  } else if (with_ms) {
     mark(0, 0);
     rowdot3(s, d->lrp, d->drec, d->q, d->lanes_l);
     mark(0, 1);
@@ -1157,7 +1190,7 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
       convolve(d, s, d->grid, d->grid, d->spec, d->g.gmode, mark);
     }
     if (d->tap_u) (void)hipMemcpyAsync(d->tap_u, d->grid, gbytes, hipMemcpyDeviceToDevice, s);
-    (void)hipStreamWaitEvent(s, d->join, 0);
+    if (overlap) (void)hipStreamWaitEvent(s, d->join, 0);
     mark(7, 0);
     {
       const IcPlan& pl = d->ic_seg ? d->icp : d->icp_small;
@@ -2120,13 +2153,19 @@ int batch_heff(pmfem_batch* b, const float* m, float* h, uint32_t terms) {
     else hipLaunchKernelGGL((k_exch<16, float>), grid, dim3(T), 0, st, n, b->lrp, b->lrec, m, b->hex);
   };
   const CellTab* tab = b->tab;
+  const bool overlap = n >= kOverlapMin;
   if (with_ms) {
-    rowdot3(s, b->lrp, b->drec, b->q, b->lanes_l);
-    (void)hipEventRecord(b->fork, s);
-    (void)hipStreamWaitEvent(b->side, b->fork, 0);
-    rowdot3(b->side, b->zrp, b->zrec, b->uz, b->lanes_z);
-    if (with_ex) exch(b->side);
-    (void)hipEventRecord(b->join, b->side);
+    if (!overlap) {
+      const MProd mp = {b->lrp, b->zrp, b->drec, b->zrec, b->lrec, b->q, b->uz, b->hex};
+      launch_mprod(s, n, b->lanes_l, b->lanes_z, with_ex, mp, m, m);
+    } else {
+      rowdot3(s, b->lrp, b->drec, b->q, b->lanes_l);
+      (void)hipEventRecord(b->fork, s);
+      (void)hipStreamWaitEvent(b->side, b->fork, 0);
+      rowdot3(b->side, b->zrp, b->zrec, b->uz, b->lanes_z);
+      if (with_ex) exch(b->side);
+      (void)hipEventRecord(b->join, b->side);
+    }
 #define PMFEM_SCC(P)                                                                           \
   hipLaunchKernelGGL(k_anterp_scatter_cells<P>, dim3(b->sc.blocks), dim3(64), b->lds_sc, s, tab, \
                      (const int32_t*)b->sc.bcell, (const int32_t*)b->sc.boff)
@@ -2201,7 +2240,7 @@ int batch_heff(pmfem_batch* b, const float* m, float* h, uint32_t terms) {
       hipLaunchKernelGGL(k_c2r_x_cells, dim3(b->c2r.blocks), dim3(T), b->lds_r2c, s, tab,
                          (const int32_t*)b->c2r.bcell, (const int32_t*)b->c2r.boff);
     }
-    (void)hipStreamWaitEvent(s, b->join, 0);
+    if (overlap) (void)hipStreamWaitEvent(s, b->join, 0);
     switch (b->W) {
       case 1:
         launch_interp_cells_kc<1>(b, s);

@@ -91,6 +91,18 @@ struct CellTab {
   float* u;         // potential
 };
 
+// operators and results of k_mprod: the local pattern with the charge and
+// exchange records, the element correction
+struct MProd {
+  const int32_t *lrp, *zrp;
+  const int4 *drec, *zrec;
+  const int2* lrec;
+  float *q, *uz, *hex;
+};
+template <int GL, int GZ, typename MT>
+__global__ void k_mprod(int64_t n, unsigned nbl, unsigned nbz, MProd a, const float* m,
+                        const MT* mx);
+
 template <int G>
 __global__ void k_rowdot3(int64_t n, const float* m, const int32_t* rp, const int4* rec,
                           float* out);

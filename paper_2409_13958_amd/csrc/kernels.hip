@@ -10,6 +10,7 @@
 //                  (k_r2c_x, k_fft_y, k_c2r_x: the same passes one axis at a time)
 //   k_interp_tile  u = W U + P q + u_Z            (steps 3 and 4)
 //   k_exch         H_ex = L m, as differences     (Eqs. hex, lapl_2; second stream)
+//   k_mprod        q, u_Z and H_ex in one launch  (small cells; no second stream)
 //   k_gsum         H = H_ex - G u (+ H_applied)   (Eq. hms_d3, heff)
 // All arithmetic is FP32; every reduction is done in a fixed order inside a
 // wavefront or a thread, so results are bitwise reproducible (no atomics).
@@ -192,13 +193,10 @@ __device__ __forceinline__ void row_entries(int e0, int e1, int lane, const Rec*
 // beside anterpolation and the FFT.
 
 template <int G>
-__global__ void __launch_bounds__(256) k_rowdot3(int64_t n, const float* __restrict__ m,
-                                                 const int32_t* __restrict__ rp,
-                                                 const int4* __restrict__ rec,
-                                                 float* __restrict__ out) {
-  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const int lane = threadIdx.x & (G - 1);
-  if (row >= n) return;  // whole groups leave together
+__device__ __forceinline__ void rowdot3_body(int64_t row, int lane, const float* __restrict__ m,
+                                             const int32_t* __restrict__ rp,
+                                             const int4* __restrict__ rec,
+                                             float* __restrict__ out) {
   float acc = 0.f;
   row_entries<G, 4>(rp[row], rp[row + 1], lane, rec, [&](const int4& r, bool ok) {
     const float* mk = m + 3 * (int64_t)r.x;
@@ -209,6 +207,16 @@ __global__ void __launch_bounds__(256) k_rowdot3(int64_t n, const float* __restr
   });
   acc = group_sum<G>(acc);
   if (lane == 0) out[row] = acc;
+}
+
+template <int G>
+__global__ void __launch_bounds__(256) k_rowdot3(int64_t n, const float* __restrict__ m,
+                                                 const int32_t* __restrict__ rp,
+                                                 const int4* __restrict__ rec,
+                                                 float* __restrict__ out) {
+  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+  if (row >= n) return;  // whole groups leave together
+  rowdot3_body<G>(row, threadIdx.x & (G - 1), m, rp, rec, out);
 }
 
 template __global__ void k_rowdot3<4>(int64_t, const float*, const int32_t*, const int4*, float*);
@@ -1964,13 +1972,9 @@ PMFEM_INTERP_TILES(7)
 // beside the grid steps; k_gsum then adds the magnetostatic gradient.
 
 template <int G, typename MT>
-__global__ void __launch_bounds__(256) k_exch(int64_t n, const int32_t* __restrict__ rp,
-                                              const int2* __restrict__ lrec,
-                                              const MT* __restrict__ m,
-                                              float* __restrict__ hex) {
-  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const int lane = threadIdx.x & (G - 1);
-  if (row >= n) return;  // whole groups leave together
+__device__ __forceinline__ void exch_body(int64_t row, int lane, const int32_t* __restrict__ rp,
+                                          const int2* __restrict__ lrec,
+                                          const MT* __restrict__ m, float* __restrict__ hex) {
   // difference form: the rows of L sum to zero (constants are in its null
   // space), so H_ex,n = sum_k L_nk (m_k - m_n); a uniform m gives exactly
   // zero and the FP32 rounding scales with the variation of m, not with m.
@@ -1996,6 +2000,40 @@ __global__ void __launch_bounds__(256) k_exch(int64_t n, const int32_t* __restri
     hex[3 * row + 1] = hy;
     hex[3 * row + 2] = hz;
   }
+}
+
+template <int G, typename MT>
+__global__ void __launch_bounds__(256) k_exch(int64_t n, const int32_t* __restrict__ rp,
+                                              const int2* __restrict__ lrec,
+                                              const MT* __restrict__ m,
+                                              float* __restrict__ hex) {
+  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+  if (row >= n) return;  // whole groups leave together
+  exch_body<G, MT>(row, threadIdx.x & (G - 1), rp, lrec, m, hex);
+}
+
+// Every product that needs only m in one launch: workgroups [0, nbl) the
+// charges, [nbl, nbl + nbz) the element correction, the rest (none without
+// exchange) the exchange, each row summed as in its own kernel, so the
+// results are the same bits. For cells whose stages are shorter than the
+// events that fork a second stream and join it again (a fork and join around
+// three empty kernels takes 31 us against 4.6 us in line): on the 20 x 20 x
+// 2 nm film three launches of 2.7 us and the events become one of 3 us.
+template <int GL, int GZ, typename MT>
+__global__ void __launch_bounds__(256) k_mprod(int64_t n, unsigned nbl, unsigned nbz, MProd a,
+                                               const float* __restrict__ m,
+                                               const MT* __restrict__ mx) {
+  const unsigned b = blockIdx.x;
+  if (b >= nbl && b < nbl + nbz) {
+    const int64_t row = ((int64_t)(b - nbl) * blockDim.x + threadIdx.x) / GZ;
+    if (row < n) rowdot3_body<GZ>(row, threadIdx.x & (GZ - 1), m, a.zrp, a.zrec, a.uz);
+    return;
+  }
+  const unsigned bl = b < nbl ? b : b - nbl - nbz;
+  const int64_t row = ((int64_t)bl * blockDim.x + threadIdx.x) / GL;
+  if (row >= n) return;
+  if (b < nbl) rowdot3_body<GL>(row, threadIdx.x & (GL - 1), m, a.lrp, a.drec, a.q);
+  else exch_body<GL, MT>(row, threadIdx.x & (GL - 1), a.lrp, a.lrec, mx, a.hex);
 }
 
 template <int G>
@@ -2044,6 +2082,22 @@ PMFEM_LOCAL_KERNELS(4)
 PMFEM_LOCAL_KERNELS(8)
 PMFEM_LOCAL_KERNELS(16)
 #undef PMFEM_LOCAL_KERNELS
+
+#define PMFEM_MPROD(GL, GZ)                                                                  \
+  template __global__ void k_mprod<GL, GZ, float>(int64_t, unsigned, unsigned, MProd,         \
+                                                  const float*, const float*);               \
+  template __global__ void k_mprod<GL, GZ, double>(int64_t, unsigned, unsigned, MProd,        \
+                                                   const float*, const double*);
+PMFEM_MPROD(4, 4)
+PMFEM_MPROD(4, 8)
+PMFEM_MPROD(4, 16)
+PMFEM_MPROD(8, 4)
+PMFEM_MPROD(8, 8)
+PMFEM_MPROD(8, 16)
+PMFEM_MPROD(16, 4)
+PMFEM_MPROD(16, 8)
+PMFEM_MPROD(16, 16)
+#undef PMFEM_MPROD
 
 // ---------------------------------------------------------------------------
 // LLG (unit-vector Landau-Lifshitz form), classic RK4 in FP64

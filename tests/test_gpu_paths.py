@@ -1,0 +1,40 @@
+"""Kernel paths that a size rule chooses, against the path they replace or the
+FP64 oracle, at the sizes where the split into workgroups can go wrong."""
+import numpy as np
+import pytest
+
+from paper_2409_13958_amd import meshgen as mg
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+B = pytest.importorskip("paper_2409_13958_amd.binding")
+
+
+def film(nx, ny, nz=1):
+    return mg.kuhn_box((nx, ny, nz), 1e-9, periodic=0b011, jitter=0.1, grid=(16, 16, 4))
+
+
+@pytest.mark.parametrize("lanes", [0, 4, 8, 16])
+@pytest.mark.parametrize("nx, ny", [(4, 4), (4, 8), (5, 7), (16, 16)])
+def test_products_of_m_in_one_launch_equal_the_single_kernels(nx, ny, lanes):
+    """k_mprod (both terms, small cells) against k_exch alone, bit for bit, and
+    its charges' sum; rows below, at and past a workgroup's share."""
+    prob = film(nx, ny)
+    ctx = B.Context.from_problem(prob, device=0)
+    ctx.set_variant("spmv", lanes)
+    n, _, nou, _ = ctx.query()
+    m = torch.tensor(prob.m[nou], dtype=torch.float32, device="cuda")
+    h, alone, hex_ = (torch.empty_like(m) for _ in range(3))
+    q = torch.empty(n, dtype=torch.float32, device="cuda")
+    ctx.heff_parts(m, h, q=q, hex=hex_)
+    ctx.heff(m, alone, terms=B.TERM_EX)
+    torch.cuda.synchronize()
+    assert torch.equal(hex_, alone)
+    loc = ctx.export("loc_val").reshape(-1, 8)[:, 1:4].astype(np.float64)
+    rp, col = ctx.export("loc_rowptr"), ctx.export("loc_col")
+    terms = (loc * m.cpu().numpy().astype(np.float64)[col]).sum(1)
+    ref = np.add.reduceat(terms, rp[:-1])
+    # FP32 sums of at most a few dozen terms: 64 roundings of the largest sum
+    bound = 64 * 2.0 ** -24 * np.add.reduceat(np.abs(terms), rp[:-1]).max()
+    assert np.abs(q.cpu().numpy() - ref).max() <= bound
