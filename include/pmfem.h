@@ -121,7 +121,8 @@ int pmfem_set_aim(pmfem_ctx* ctx, const int32_t grid[3], int32_t order_p, int32_
  * scatter (per-workgroup LDS sums in a fixed order, then a fixed-order sum of
  * the overlapping tile footprints);
  * "interp" (interpolation + precorrection): 1 narrow observer tiles (at
- * most 4 boxes along x), 2 the largest tiles whose staging fits in LDS;
+ * most 4 boxes along x), 2 the largest tiles whose staging fits in LDS and
+ * that are enough to fill the chip;
  * "fft": 1 separate x, y, z passes, 2 whole z-planes in LDS for x and y;
  * "spmv" (charges, element correction, exchange and gradient rows): 4, 8
  * or 16 lanes per row on both patterns. variant 0 (the default) picks the

@@ -25,6 +25,8 @@ constexpr int kFftPlaneMrT = 512;
 constexpr int kFftzT = 256;          // threads per workgroup of the z pass
 constexpr int kFftSplit = 2;         // workgroups per z-plane in the plane transforms
 constexpr int kIcLdsBudget = 24576;  // LDS bytes per interpolation tile
+constexpr int kIcThreads = 256;      // threads per interpolation workgroup
+constexpr double kIcTiles = 600.0;   // full interpolation tiles wanted of one launch (plan_interp)
 constexpr int kScTile[3] = {8, 8, 4};  // preferred boxes per scatter tile along x, y, z
 // unknowns from which the element correction and the exchange run on a second
 // stream beside the grid steps
@@ -352,12 +354,37 @@ bool plan_anterp(const HostOps& o, const std::vector<int2>& bx, const std::vecto
 // nodes of its box columns (column-major, box row, node order), each entry
 // node | row << 26, the list start of every workgroup and the column starts
 // within it (stride sbx + 1).
+// Launch order of the interpolation tiles: those that hold observer rows, the
+// fullest first (in sixteenths of the fullest tile, grid order within one), so
+// that the launch ends with its short workgroups.
+std::vector<int32_t> interp_order(const HostOps& o, const IcPlan& pl) {
+  const int nbx = o.nbox[0], nby = o.nbox[1], nbz = o.nbox[2];
+  const int64_t nt = (int64_t)pl.nsx * nby * pl.nsz;
+  std::vector<int32_t> rows(nt, 0), order;
+  int32_t most = 1;
+  for (int64_t w = 0; w < nt; ++w) {
+    const int x0 = (int)(w % pl.nsx) * pl.xs, by = (int)(w / pl.nsx % nby);
+    const int z0 = (int)(w / pl.nsx / nby) * pl.tz;
+    for (int z = z0; z < std::min(z0 + pl.tz, nbz); ++z) {
+      const int64_t row = ((int64_t)z * nby + by) * nbx;
+      rows[w] += o.box_start[row + std::min(x0 + pl.xs, nbx)] - o.box_start[row + x0];
+    }
+    most = std::max(most, rows[w]);
+    if (rows[w] > 0) order.push_back((int32_t)w);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+    return (int64_t)rows[a] * 16 / most > (int64_t)rows[b] * 16 / most;
+  });
+  return order;
+}
+
 // Node lists of k_interp_tile for plan pl, in launch order: per workgroup the
 // nodes of its source block column-major (x column, z, y, node order), the
 // list start of every workgroup, its observer segments (row prefix over the
-// z box rows, then the first row of each; stride 2 tz + 1), and per row the
-// (start | length << 16) of its 2 r_b + 1 runs in the workgroup's list.
-bool build_interp_lists(const HostOps& o, const IcPlan& pl, std::vector<int32_t>& list,
+// z box rows, then the first row of each, then the tile's number; stride
+// 2 tz + 2), and per row the (start | length << 16) of its 2 r_b + 1 runs in
+// the workgroup's list.
+bool build_interp_lists(const HostOps& o, IcPlan& pl, std::vector<int32_t>& list,
                         std::vector<int32_t>& lstart, std::vector<int32_t>& wseg,
                         std::vector<uint32_t>& rdesc) {
   const int nbx = o.nbox[0], nby = o.nbox[1], nbz = o.nbox[2];
@@ -372,16 +399,18 @@ bool build_interp_lists(const HostOps& o, const IcPlan& pl, std::vector<int32_t>
     else if (z < 0 || z >= nbz) return -1;
     return ((int64_t)z * nby + y) * nbx + x;
   };
-  const int64_t nwg = (int64_t)pl.nsx * nby * pl.nsz;
-  const int segw = 2 * pl.tz + 1, rpc = pl.szr * W;
+  const std::vector<int32_t> order = interp_order(o, pl);
+  const int64_t nwg = (int64_t)order.size();
+  pl.nwg = (int)nwg;
+  const int segw = 2 * pl.tz + 2, rpc = pl.szr * W;
   lstart.assign(nwg + 1, 0);
   wseg.assign(nwg * segw, 0);
   rdesc.assign((size_t)o.n_unk * W, 0u);
   list.clear();
   std::vector<int32_t> pos((size_t)pl.sbx * (rpc + 1));
   for (int64_t w = 0; w < nwg; ++w) {
-    const int sx = (int)(w % pl.nsx);
-    const int64_t rest = w / pl.nsx;
+    const int sx = (int)(order[w] % pl.nsx);
+    const int64_t rest = order[w] / pl.nsx;
     const int by = (int)(rest % nby), sz = (int)(rest / nby);
     const int x0 = sx * pl.xs, z0 = sz * pl.tz;
     const int xs = std::min(pl.xs, nbx - x0), tz = std::min(pl.tz, nbz - z0);
@@ -400,6 +429,7 @@ bool build_interp_lists(const HostOps& o, const IcPlan& pl, std::vector<int32_t>
     }
     if ((int64_t)list.size() - l0 >= 65536) return false;
     int32_t* sg = &wseg[w * segw];
+    sg[segw - 1] = order[w];
     int32_t run = 0;
     for (int kz = 0; kz <= pl.tz; ++kz) {
       sg[kz] = run;
@@ -570,8 +600,16 @@ bool build_anterp_lists(const HostOps& o, const std::vector<int2>& bx,
 
 // Tile plan for k_interp_tile: the largest tile (xs boxes along x times tz
 // box rows along z, both powers of two, xs <= max_xs) whose staged arrays fit
-// the LDS budget; larger tiles stage each source charge fewer times.
-bool plan_interp(const HostOps& o, int max_xs, IcPlan& pl) {
+// the LDS budget and that leaves `want` full tiles' worth of rows, or holds no
+// more rows than a workgroup forms at once. Larger tiles stage each source
+// charge fewer times, but a chip of 256 compute units that hold five
+// workgroups each needs many of them: the kernel takes, by full tiles,
+//   138 k composite     335: 35.8 us    669: 27.1    1340: 30.0    2600: 35
+//   52.7 k wire         388: 15.4       776: 12.7    1550: 16.0
+//   44 k jittered box   170: 19.9       343: 14.0     687: 12.3    1370: 15.6
+// and at 12 k unknowns 8.7 us with 32 rows per tile, 11.0 with 64. No tile
+// that meets both: the one that leaves the most.
+bool plan_interp(const HostOps& o, int max_xs, double want, IcPlan& pl) {
   const int nbx = o.nbox[0], nby = o.nbox[1], nbz = o.nbox[2];
   const int rb = o.rb, W = 2 * rb + 1, p = o.p;
   const std::vector<int32_t>& bs = o.box_start;
@@ -599,42 +637,46 @@ bool plan_interp(const HostOps& o, int max_xs, IcPlan& pl) {
     const double rb2 = (double)(b.xs + 2 * rb) * (b.tz + 2 * rb) / (b.xs * b.tz);
     return ra < rb2;
   });
+  int64_t most = 0;  // rows of the fullest tile of the plan held so far (0: none)
   for (const Shape& sh : shapes) {
     const int xs = sh.xs, tz = sh.tz;
     const int nsx = (nbx + xs - 1) / xs, nsz = (nbz + tz - 1) / tz;
     const int sbx = xs + 2 * rb, szr = tz + 2 * rb;
-    int64_t qcap = 0, rcap = 0, colmax = 0;
+    int64_t qcap = 0, rcap = 0;
+    auto rows_of = [&](int x0, int by, int z0) {
+      int64_t rows = 0;
+      for (int z = z0; z < std::min(z0 + tz, nbz); ++z) {
+        const int64_t row = ((int64_t)z * nby + by) * nbx;
+        rows += bs[row + std::min(x0 + xs, nbx)] - bs[row + x0];
+      }
+      return rows;
+    };
+    for (int sz = 0; sz < nsz; ++sz)
+      for (int by = 0; by < nby; ++by)
+        for (int sx = 0; sx < nsx; ++sx) rcap = std::max(rcap, rows_of(sx * xs, by, sz * tz));
+    const bool enough = rcap <= kIcThreads / kIcLanes || (double)o.n_unk >= want * (double)rcap;
+    if (!enough && most && rcap >= most) continue;
     for (int sz = 0; sz < nsz; ++sz)
       for (int by = 0; by < nby; ++by)
         for (int sx = 0; sx < nsx; ++sx) {
           const int x0 = sx * xs, z0 = sz * tz;
-          int64_t rows = 0;
-          for (int kz = 0; kz < tz && z0 + kz < nbz; ++kz)
-            for (int kx = 0; kx < xs && x0 + kx < nbx; ++kx) rows += cnt(x0 + kx, by, z0 + kz);
-          if (rows == 0) continue;
-          rcap = std::max(rcap, rows);
+          if (rows_of(x0, by, z0) == 0) continue;
           int64_t staged = 0;
-          for (int k = 0; k < sbx; ++k) {
-            int64_t col = 0;
+          for (int k = 0; k < sbx; ++k)
             for (int zz = 0; zz < szr; ++zz)
               for (int yy = 0; yy < W; ++yy)
-                col += cnt(x0 - rb + k, by - rb + yy, z0 - rb + zz);
-            colmax = std::max(colmax, col);
-            staged += col;
-          }
+                staged += cnt(x0 - rb + k, by - rb + yy, z0 - rb + zz);
           qcap = std::max(qcap, staged);
         }
     auto al = [](int64_t b) { return (b + 15) & ~(int64_t)15; };
     const int ux = xs + p, uzl = tz + p;
-    int64_t off = 0;
-    pl.o_q = (int)off;
-    off += al((qcap + 4) * 4);  // staged charges and 4 zeros
-    pl.o_u = (int)off;
-    off += al((int64_t)uzl * (p + 1) * ux * 4);
-    pl.o_seg = (int)off;
-    off += al((int64_t)(2 * tz + 1) * 4);
-    (void)colmax;
+    const int64_t o_u = al((qcap + 4) * 4);  // after the staged charges and 4 zeros
+    const int64_t o_seg = o_u + al((int64_t)uzl * (p + 1) * ux * 4);
+    const int64_t off = o_seg + al((int64_t)(2 * tz + 1) * 4);
     if (off <= kIcLdsBudget && qcap < 65536) {
+      pl.o_q = 0;
+      pl.o_u = (int)o_u;
+      pl.o_seg = (int)o_seg;
       pl.xs = xs;
       pl.tz = tz;
       pl.nsx = nsx;
@@ -646,10 +688,11 @@ bool plan_interp(const HostOps& o, int max_xs, IcPlan& pl) {
       pl.ux = ux;
       pl.uzl = uzl;
       pl.lds_bytes = (int)off;
-      return true;
+      if (enough) return true;
+      most = rcap;
     }
   }
-  return false;
+  return most > 0;
 }
 
 int upload_all(pmfem_ctx* c) {
@@ -676,8 +719,8 @@ int upload_all(pmfem_ctx* c) {
   int rc;
   if ((rc = upload(c, &d->pos4, o.pos4.data(), n))) return rc;
   if ((rc = upload(c, &d->box_start, o.box_start.data(), o.box_start.size()))) return rc;
-  d->ic_ok = plan_interp(o, 128, d->icp);
-  d->ic_small_ok = plan_interp(o, 4, d->icp_small);
+  d->ic_ok = plan_interp(o, 128, kIcTiles, d->icp);
+  d->ic_small_ok = plan_interp(o, 4, 0.0, d->icp_small);
   for (int which = 0; which < 2; ++which) {
     bool& ok = which == 0 ? d->ic_ok : d->ic_small_ok;
     if (!ok) continue;
@@ -1195,8 +1238,7 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
     {
       const IcPlan& pl = d->ic_seg ? d->icp : d->icp_small;
       const pmfem_dev::IcLists& L = d->ic_seg ? d->icl : d->icl_small;
-      const int64_t nwg = (int64_t)pl.nsx * g.nbox[1] * pl.nsz;
-      const dim3 grid((unsigned)nwg), blk(T);
+      const dim3 grid((unsigned)pl.nwg), blk(T);
       const size_t lds = (size_t)pl.lds_bytes;
       switch (g.rb) {
         case 0:
@@ -1987,6 +2029,21 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
   b->PT = 4;
   for (size_t c = 0; c < K; ++c)
     if (b->cells[c]->dev->g.N[0] % 4 != 0) b->PT = 1;
+  struct BatchTiles {
+    bool ok = false;
+    IcPlan pl{};
+    std::vector<int32_t> list, lstart, wseg;
+    std::vector<uint32_t> rdesc;
+  };
+  std::vector<BatchTiles> bplan(K);
+  parallel_for((int64_t)K, [&](int64_t c) {
+    const pmfem_dev* d = b->cells[c]->dev;
+    const HostOps& o = b->cells[c]->ops;
+    BatchTiles& t = bplan[c];
+    if (!d->ic_ok || !plan_interp(o, 128, kIcTiles * (double)o.n_unk / (double)n, t.pl)) return;
+    if (t.pl.xs == d->icp.xs && t.pl.tz == d->icp.tz) return;  // the cell's own lists
+    t.ok = build_interp_lists(o, t.pl, t.list, t.lstart, t.wseg, t.rdesc);
+  }, 1);
   for (size_t c = 0; c < K; ++c) {
     const pmfem_dev* d = b->cells[c]->dev;
     if (d->g.p != b->p || 2 * d->g.rb + 1 != b->W)
@@ -1996,7 +2053,6 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     CellTab& t = tab[c];
     t.g = d->g;
     t.sp = d->sp;
-    t.icp = d->icp;
     t.pos4 = d->pos4;
     t.sc_list = d->sc_list;
     t.sc_lstart = d->sc_lstart;
@@ -2011,9 +2067,19 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     t.twfx = d->twfx;
     t.twfy = d->twfy;
     t.twfz = d->twfz;
-    // interpolation: the largest tiles whose staging fits, else the narrow ones
-    const IcPlan& ipl = d->ic_ok ? d->icp : d->icp_small;
-    const pmfem_dev::IcLists& il = d->ic_ok ? d->icl : d->icl_small;
+    // interpolation: the cell's tiles, or larger ones where the other cells
+    // of the batch fill the launch (its share of the tiles wanted)
+    IcPlan ipl = d->ic_ok ? d->icp : d->icp_small;
+    pmfem_dev::IcLists il = d->ic_ok ? d->icl : d->icl_small;
+    if (d->ic_ok && bplan[c].ok) {
+      ipl = bplan[c].pl;
+      ipl.kc = d->icp.kc;
+      if ((rc = bupload(b, &il.list, bplan[c].list.data(), bplan[c].list.size())) ||
+          (rc = bupload(b, &il.lstart, bplan[c].lstart.data(), bplan[c].lstart.size())) ||
+          (rc = bupload(b, &il.wseg, bplan[c].wseg.data(), bplan[c].wseg.size())) ||
+          (rc = bupload(b, &il.rdesc, bplan[c].rdesc.data(), bplan[c].rdesc.size())))
+        return rc;
+    }
     t.icp = ipl;
     t.ic_list = il.list;
     t.ic_lstart = il.lstart;
@@ -2062,7 +2128,7 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
       b->lds_fy = std::max(b->lds_fy, (size_t)(g.M[1] / 2 + t.by * g.M[1]) * sizeof(float2));
     }
     if (!d->fft_mr) b->Bz = std::min(b->Bz, std::max(1, std::min(kFftzB, 4096 / g.M[2])));
-    nic[c] = (int64_t)ipl.nsx * g.nbox[1] * ipl.nsz;
+    nic[c] = ipl.nwg;
     b->lds_sc = std::max(b->lds_sc, (size_t)d->sp.lds_bytes);
     b->lds_ic = std::max(b->lds_ic, (size_t)ipl.lds_bytes);
     b->KC = std::max(b->KC, ipl.kc);

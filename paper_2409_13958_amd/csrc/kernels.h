@@ -31,6 +31,7 @@ constexpr int kAntHalo = (kAntTX + 6) * (kAntTY + 6) * (kAntTZ + 6) + 1;
 struct IcPlan {
   int xs, tz;    // observer boxes per tile along x and z
   int nsx, nsz;  // tiles along x and z
+  int nwg;       // tiles that hold observer rows (one workgroup each)
   int sbx, szr;  // staged box columns (xs + 2 r_b) and z rows (tz + 2 r_b)
   int qcap;      // staged source charges
   int rcap;      // observer rows per tile

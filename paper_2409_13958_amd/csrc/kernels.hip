@@ -1741,16 +1741,18 @@ __device__ __forceinline__ void interp_tile_body(
   const int tid = threadIdx.x, T = blockDim.x;
   const int nby = g.nbox[1];
   const int p = g.p, p1 = p + 1;
-  const int w = blk;
+  // [0, pl.tz]: row prefix over the z segments; [pl.tz + 1, 2 pl.tz]: first
+  // row of each; then the tile (only tiles with rows are launched, the
+  // fullest first)
+  const int segw = 2 * pl.tz + 2;
+  const int w = wseg[(int64_t)blk * segw + segw - 1];
   const int sx = w % pl.nsx, rest = w / pl.nsx;
   const int by = rest % nby, sz = rest / nby;
   const int x0 = sx * pl.xs, z0 = sz * pl.tz;
   const int tz = min(pl.tz, g.nbox[2] - z0);
-  // [0, pl.tz]: row prefix over the z segments; [pl.tz + 1, 2 pl.tz]: first row of each
-  const int segw = 2 * pl.tz + 1;
-  for (int i = tid; i < segw; i += T) s_seg[i] = wseg[(int64_t)w * segw + i];
-  const int l0 = lstart[w];
-  const int n = min(lstart[w + 1] - l0, pl.qcap);
+  for (int i = tid; i < segw - 1; i += T) s_seg[i] = wseg[(int64_t)blk * segw + i];
+  const int l0 = lstart[blk];
+  const int n = min(lstart[blk + 1] - l0, pl.qcap);
   // the first list entries are requested before the potential lines are
   // staged, so that both wait on memory together
   constexpr int KQ = 8;

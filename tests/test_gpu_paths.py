@@ -38,3 +38,36 @@ def test_products_of_m_in_one_launch_equal_the_single_kernels(nx, ny, lanes):
     # FP32 sums of at most a few dozen terms: 64 roundings of the largest sum
     bound = 64 * 2.0 ** -24 * np.add.reduceat(np.abs(terms), rp[:-1]).max()
     assert np.abs(q.cpu().numpy() - ref).max() <= bound
+
+
+@pytest.mark.parametrize("make", [
+    lambda: film(4, 4),                       # one tile holds every row
+    lambda: film(40, 33),                     # more than 32 rows per tile
+    # spheres in an empty host: tiles without rows beside full ones
+    lambda: mg.composite_c3(n_cells=24, grid=(21, 21, 21)),
+    lambda: mg.kuhn_box((13, 17, 22), 1e-9, periodic=0b111, jitter=0.2, grid=(14, 18, 24)),
+])
+def test_interpolation_tiles_do_not_change_the_sums(make):
+    """The tile shape only regroups the rows: the narrow tiles and those
+    chosen by size give the same bits, alone and in a batch (larger tiles)."""
+    prob = make()
+    ctx = B.Context.from_problem(prob, device=0)
+    _, _, nou, _ = ctx.query()
+    m = torch.tensor(prob.m[nou], dtype=torch.float32, device="cuda")
+    out = []
+    for v in (0, 2, 1):
+        ctx.set_variant("interp", v)
+        out.append(torch.empty_like(m))
+        ctx.heff(m, out[-1])
+    other = B.Context.from_problem(film(60, 61), device=0)
+    batch = B.Batch([ctx, other], spmv_lanes=4)
+    ctx.set_variant("spmv", 4)
+    ref = torch.empty_like(m)
+    ctx.heff(m, ref)
+    mb = torch.cat([m, torch.zeros((other.n, 3), device="cuda")])
+    hb = torch.empty_like(mb)
+    batch.heff(mb, hb)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+    assert torch.equal(hb[:ctx.n], ref)
+    batch.close()
