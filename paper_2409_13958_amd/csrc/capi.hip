@@ -32,6 +32,7 @@ constexpr int kScTile[3] = {8, 8, 4};  // preferred boxes per scatter tile along
 // stream beside the grid steps
 constexpr int64_t kOverlapMin = 300000;
 constexpr int kScLdsBudget = 65536;    // LDS bytes of a scatter tile's footprint copies
+constexpr int kScWeights = 12288;      // LDS bytes of the scatter kernel's weights
 
 // Scratch of pmfem_grid_convolve_noalloc: the half-spectrum of one grid
 // convolution, at most kNoallocSpecMax complex values (16 MiB). Every device
@@ -56,7 +57,10 @@ struct pmfem_dev {
   int ant_threads = 0;
   ScPlan sp{};              // scatter form of anterpolation
   bool sc_ok = false, ant_scatter = false;
-  int2* sc_list = nullptr;     // {node, stencil offset in the footprint} of every tile, box order
+  // the nodes of every launched tile in launch order: {xi, LDS offset of the
+  // stencil} and the node index; the tiles' numbers
+  float4* sc_rec = nullptr;
+  int32_t *sc_node = nullptr, *sc_tile = nullptr;
   int32_t* sc_lstart = nullptr;
   int2* sc_tab[3] = {};     // per axis and grid index: (tile, offset) of the covering tiles
   float* sc_part = nullptr; // footprint sums of every tile
@@ -536,10 +540,17 @@ bool plan_scatter_with(const HostOps& o, ScPlan& pl, std::vector<int2>& list,
       }
   }
   lstart[nt] = (int32_t)list.size();
-  // the footprint copies, one per lane group (four groups of 16 lanes for p <= 3)
-  const int64_t lds = (int64_t)pl.fsize * (o.p <= 3 ? 4 : 1) * 4;
-  if (lds > kScLdsBudget) return false;
-  pl.lds_bytes = (int)lds;
+  if ((int64_t)pl.fsize * (o.p <= 3 ? 4 : 1) * 4 > kScLdsBudget) return false;
+  // the footprint copies, one per wavefront, at padded strides; fewer of them
+  // where a tile is large
+  pl.sy = pl.fd[0];
+  while (pl.sy % 8 != 4) ++pl.sy;
+  pl.sz = pl.sy * pl.fd[1];
+  while (pl.sz % 32 != 16) ++pl.sz;
+  pl.lsize = pl.sz * pl.fd[2];
+  pl.nw = kScWaves;
+  while (pl.nw > 1 && pl.lsize * 4 * pl.nw > kScLdsBudget - kScWeights) pl.nw /= 2;
+  pl.lds_bytes = pl.lsize * 4 * pl.nw;
   return (int64_t)list.size() == o.n_unk;
 }
 
@@ -695,6 +706,23 @@ bool plan_interp(const HostOps& o, int max_xs, double want, IcPlan& pl) {
   return most > 0;
 }
 
+// The scatter kernel of order p (cells: its multi-cell form), allowed `lds`
+// bytes of dynamic LDS where that and its weights exceed the default 64 KB.
+bool scatter_lds(int p, bool cells, int lds) {
+  if (lds + kScWeights <= 65536) return true;
+  const void* f = nullptr;
+  switch (p) {
+    case 1: f = cells ? (const void*)k_anterp_scatter_cells<1> : (const void*)k_anterp_scatter<1>; break;
+    case 2: f = cells ? (const void*)k_anterp_scatter_cells<2> : (const void*)k_anterp_scatter<2>; break;
+    case 3: f = cells ? (const void*)k_anterp_scatter_cells<3> : (const void*)k_anterp_scatter<3>; break;
+    case 4: f = cells ? (const void*)k_anterp_scatter_cells<4> : (const void*)k_anterp_scatter<4>; break;
+    default: f = cells ? (const void*)k_anterp_scatter_cells<5> : (const void*)k_anterp_scatter<5>; break;
+  }
+  const bool ok = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
+  (void)hipGetLastError();
+  return ok;
+}
+
 int upload_all(pmfem_ctx* c) {
   HostOps& o = c->ops;
   pmfem_dev* d = c->dev;
@@ -778,14 +806,48 @@ int upload_all(pmfem_ctx* c) {
     std::vector<int2> list;
     std::vector<int32_t> lstart;
     std::vector<int2> tab[3];
-    d->sc_ok = plan_scatter(o, d->sp, list, lstart, tab);
+    d->sc_ok = plan_scatter(o, d->sp, list, lstart, tab) &&
+               scatter_lds(o.p, false, d->sp.lds_bytes);
     if (d->sc_ok) {
-      if ((rc = upload(c, &d->sc_list, list.data(), list.size()))) return rc;
-      if ((rc = upload(c, &d->sc_lstart, lstart.data(), lstart.size()))) return rc;
+      // launch order: the tiles that hold nodes, the fullest first (in
+      // sixteenths of the fullest, grid order within one)
+      const int64_t ntile = (int64_t)lstart.size() - 1;
+      std::vector<int32_t> tile, start(1, 0), node;
+      std::vector<float4> rec;
+      int32_t most = 1;
+      for (int64_t t = 0; t < ntile; ++t) {
+        most = std::max(most, lstart[t + 1] - lstart[t]);
+        if (lstart[t + 1] > lstart[t]) tile.push_back((int32_t)t);
+      }
+      auto level = [&](int32_t t) { return (int64_t)(lstart[t + 1] - lstart[t]) * 16 / most; };
+      std::stable_sort(tile.begin(), tile.end(),
+                       [&](int32_t a, int32_t b) { return level(a) > level(b); });
+      node.reserve(list.size());
+      rec.reserve(list.size());
+      const ScPlan& pl = d->sp;
+      for (int32_t t : tile) {
+        for (int32_t i = lstart[t]; i < lstart[t + 1]; ++i) {
+          float4 r;
+          std::memcpy(&r, &o.pos4[4 * (size_t)list[i].x], sizeof r);
+          const int off = list[i].y, z = off / (pl.fd[0] * pl.fd[1]);
+          const int y = off / pl.fd[0] % pl.fd[1], x = off % pl.fd[0];
+          const int32_t at = z * pl.sz + y * pl.sy + x;
+          std::memcpy(&r.w, &at, sizeof at);
+          rec.push_back(r);
+          node.push_back(list[i].x);
+        }
+        start.push_back((int32_t)node.size());
+      }
+      d->sp.nwg = (int)tile.size();
+      if ((rc = upload(c, &d->sc_rec, rec.data(), rec.size()))) return rc;
+      if ((rc = upload(c, &d->sc_node, node.data(), node.size()))) return rc;
+      if ((rc = upload(c, &d->sc_tile, tile.data(), tile.size()))) return rc;
+      if ((rc = upload(c, &d->sc_lstart, start.data(), start.size()))) return rc;
       for (int a = 0; a < 3; ++a)
         if ((rc = upload(c, &d->sc_tab[a], tab[a].data(), tab[a].size()))) return rc;
-      const int64_t nt = (int64_t)d->sp.nt[0] * d->sp.nt[1] * d->sp.nt[2];
-      if ((rc = dalloc(c, &d->sc_part, nt * d->sp.fsize))) return rc;
+      // footprints of tiles without nodes stay zero
+      const std::vector<float> zero((size_t)ntile * d->sp.fsize, 0.f);
+      if ((rc = upload(c, &d->sc_part, zero.data(), zero.size()))) return rc;
     }
   }
   if ((rc = upload(c, &d->brx, bx.data(), bx.size()))) return rc;
@@ -1180,11 +1242,10 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
     mark(1, 0);
     if (d->ant_scatter) {
       const ScPlan& pl = d->sp;
-      const int64_t nt = (int64_t)pl.nt[0] * pl.nt[1] * pl.nt[2];
       const size_t lds = (size_t)pl.lds_bytes;
 #define PMFEM_SC_LAUNCH(P)                                                                    \
-  hipLaunchKernelGGL(k_anterp_scatter<P>, dim3((unsigned)nt), dim3(64), lds, s, g, pl, d->q,   \
-                     d->pos4, d->sc_list, d->sc_lstart, d->sc_part)
+  hipLaunchKernelGGL(k_anterp_scatter<P>, dim3((unsigned)pl.nwg), dim3(64 * kScWaves), lds, s, \
+                     g, pl, d->q, d->sc_rec, d->sc_node, d->sc_lstart, d->sc_tile, d->sc_part)
       switch (g.p) {
         case 1:
           PMFEM_SC_LAUNCH(1);
@@ -2054,7 +2115,9 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     t.g = d->g;
     t.sp = d->sp;
     t.pos4 = d->pos4;
-    t.sc_list = d->sc_list;
+    t.sc_rec = d->sc_rec;
+    t.sc_node = d->sc_node;
+    t.sc_tile = d->sc_tile;
     t.sc_lstart = d->sc_lstart;
     for (int a = 0; a < 3; ++a) t.sc_tab[a] = d->sc_tab[a];
     t.sc_part = d->sc_part;
@@ -2093,7 +2156,7 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     const GridParams& g = d->g;
     const int64_t ng = (int64_t)g.N[0] * g.N[1] * g.N[2];
     const int Hx = g.M[0] / 2 + 1;
-    nsc[c] = (int64_t)d->sp.nt[0] * d->sp.nt[1] * d->sp.nt[2];
+    nsc[c] = d->sp.nwg;
     nsum[c] = (ng / b->PT + 255) / 256;
     // FFT: whole z-planes in LDS where they fit, else one axis per pass
     // (radix 2, or mixed radix where an extent is not a power of two)
@@ -2156,6 +2219,8 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
       (rc = batch_launch_table(b, nzm_mr, b->zm_mr)) ||
       (rc = batch_launch_table(b, nxy_mr, b->xy_mr)))
     return rc;
+  if (!scatter_lds(b->p, true, (int)b->lds_sc))
+    return batch_err(b, PMFEM_EINVAL, "scatter tiles of the batch do not fit in LDS");
   if (b->lds_plane_mr > 65536) {
     const int lb = (int)b->lds_plane_mr;
     if (hipFuncSetAttribute((const void*)k_fft_xy_fwd_mr_cells,
@@ -2233,7 +2298,7 @@ int batch_heff(pmfem_batch* b, const float* m, float* h, uint32_t terms) {
       (void)hipEventRecord(b->join, b->side);
     }
 #define PMFEM_SCC(P)                                                                           \
-  hipLaunchKernelGGL(k_anterp_scatter_cells<P>, dim3(b->sc.blocks), dim3(64), b->lds_sc, s, tab, \
+  hipLaunchKernelGGL(k_anterp_scatter_cells<P>, dim3(b->sc.blocks), dim3(64 * kScWaves), b->lds_sc, s, tab, \
                      (const int32_t*)b->sc.bcell, (const int32_t*)b->sc.boff)
     switch (b->p) {
       case 1:

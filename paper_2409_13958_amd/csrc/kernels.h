@@ -53,14 +53,20 @@ struct AntPlan {
   int lds_bytes;
 };
 
-// anterpolation by scatter: one 64-lane workgroup per tile of
+// anterpolation by scatter: one workgroup of kScWaves wavefronts per tile of
 // tb[0] x tb[1] x tb[2] boxes, its footprint (the grid points the stencils
-// of its boxes cover) fd[0] x fd[1] x fd[2] points at most
+// of its boxes cover) fd[0] x fd[1] x fd[2] points at most; in LDS the y and z
+// strides are padded to sy = 4 (mod 8) and sz = 16 (mod 32) values, which
+// spreads the 4 x 4 x 2 points of half a cubic stencil over all 32 banks
+constexpr int kScWaves = 4;
 struct ScPlan {
   int tb[3];  // boxes per tile along each axis
   int nt[3];  // tiles along each axis
   int fd[3];  // footprint extent along each axis (tb + p at most)
   int fsize;  // fd[0] fd[1] fd[2]
+  int nw;             // wavefronts that take nodes, each with a footprint copy
+  int sy, sz, lsize;  // LDS strides and size of a footprint copy
+  int nwg;            // tiles that hold nodes
   int lds_bytes;
 };
 
@@ -73,7 +79,8 @@ struct CellTab {
   ScPlan sp;
   IcPlan icp;
   const float4* pos4;
-  const int2* sc_list;
+  const float4* sc_rec;
+  const int32_t *sc_node, *sc_tile;
   const int32_t* sc_lstart;
   const int2* sc_tab[3];
   float* sc_part;
@@ -114,8 +121,9 @@ __global__ void k_anterp_line(GridParams g, AntPlan pl, const float* q, const fl
                               const int32_t* list, const int32_t* lstart, const int32_t* colst,
                               const int2* brx, const int2* bry, const int2* brz, float* Q);
 template <int P>
-__global__ void k_anterp_scatter(GridParams g, ScPlan pl, const float* q, const float4* pos4,
-                                 const int2* list, const int32_t* lstart, float* part);
+__global__ void k_anterp_scatter(GridParams g, ScPlan pl, const float* q, const float4* rec,
+                                 const int32_t* node, const int32_t* lstart, const int32_t* tile,
+                                 float* part);
 template <int PT>
 __global__ void k_anterp_sum(GridParams g, ScPlan pl, const int2* tabx, const int2* taby,
                              const int2* tabz, const float* part, float* Q);

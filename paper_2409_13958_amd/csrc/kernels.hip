@@ -160,6 +160,15 @@ __device__ __forceinline__ int staged_node(int e, int nrow, const int* base, con
   return b0[lo] + rel;
 }
 
+// n / d for 0 <= n < 2^22 and 1 <= d < 2^10 without an integer divide: the
+// float quotient is off by at most one, which the correction removes.
+__device__ __forceinline__ int fdiv(int n, int d, float inv_d) {
+  int q = (int)((float)n * inv_d);
+  if (q * d > n) --q;
+  else if ((q + 1) * d <= n) ++q;
+  return q;
+}
+
 template <int W>
 __device__ __forceinline__ float group_sum(float v) {
   // butterfly sum over groups of W consecutive lanes (W divides 64)
@@ -473,20 +482,32 @@ __global__ void __launch_bounds__(128) k_anterp_line(
 }
 
 // ---------------------------------------------------------------------------
-// anterpolation by scatter. One 64-lane workgroup per tile of boxes: its
-// nodes (listed on the host in box order, each with the offset of its box's
-// stencil in the tile footprint) come in batches of 64, one per lane, and the
-// 16 nodes of a 16-lane row go to that row's lane group (DPP broadcasts
-// within the row; one 64-lane group for p > 3). A lane of a group owns one
-// (a, b) pair of x and y stencil offsets and adds, for every node of its
-// group, q L_a(xi_x) L_b(xi_y) L_c(xi_z), c = 0..p, to the grid points of the
-// node's stencil in the group's own LDS copy of the tile footprint (the
-// grid points the stencils of the tile's boxes cover). Within an instruction
-// the lanes of a group address distinct points and the groups distinct
-// copies, and each group takes its nodes in a fixed order, so the sums do
-// not depend on timing. The copies are then added in group order and the
-// footprint written out; k_anterp_sum adds, for every grid point, the
-// footprints of the (at most two per axis) tiles that cover it.
+// anterpolation by scatter. One workgroup of four wavefronts per tile of boxes
+// (only tiles with nodes are launched, the fullest first). The tile's nodes,
+// listed on the host in box order, are dealt to the four wavefronts in turn
+// and taken in batches of 64 per wavefront: each lane forms the p + 1 weights
+// per axis of one node of the batch (q times those of x) and leaves them in
+// LDS; then the wavefront takes the nodes one by one, a lane owning one
+// (a, b, c) point of the stencil (p = 3: 64 points, 64 lanes; larger p: several
+// points per lane) and adding q L_a(xi_x) L_b(xi_y) L_c(xi_z) to it in the
+// wavefront's own LDS copy of the tile footprint (the grid points the stencils
+// of the tile's boxes cover), the next node's weights being read meanwhile.
+// Within an instruction the lanes address distinct points, and a wavefront
+// takes its nodes in a fixed order, so the sums do not depend on timing. The
+// copies are then added in wavefront order and the footprint written out (where
+// four copies do not fit in LDS, ScPlan::nw wavefronts take nodes);
+// k_anterp_sum adds, for every grid point, the footprints of the (at most two
+// per axis) tiles that cover it.
+//
+// What bounds it is LDS: a read-add-write per node and its latency, so a node
+// costs one conflict-free read and write (ScPlan's strides put the 32 points
+// of half a wavefront into 32 banks) besides three broadcast reads, and twenty
+// wavefronts per compute unit hide the latency. With one wavefront per tile,
+// 16 lanes per node and four points per lane, two- to threefold bank conflicts
+// and nine wavefronts per compute unit, the composite of 1.03 M unknowns took
+// 63 us alone, against 39 us now (25 MB of nodes, 28 MB of footprints); the
+// 138 k composite 18 us against 12; a 44 k unknown box, where a wavefront's 61
+// nodes in a row are what counts, 17 us against 11.
 
 // L_a(xi) for compile-time p and a
 template <int P>
@@ -495,145 +516,130 @@ __device__ __forceinline__ float basis_ct(int a, float xi) {
   else return lagrange(a, xi, P);
 }
 
-// value of lane I of this lane's 16-lane row (DPP row broadcast)
-template <int I>
-__device__ __forceinline__ float row_lane(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + I, 0xf, 0xf, false));
-}
-
 template <int P>
 __device__ __forceinline__ void anterp_scatter_body(
-    GridParams g, ScPlan pl, const float* __restrict__ q, const float4* __restrict__ pos4,
-    const int2* __restrict__ list, const int32_t* __restrict__ lstart,
-    float* __restrict__ part, const int blk) {
-  constexpr int P1 = P + 1, GS = P1 * P1 <= 16 ? 16 : 64, NG = 64 / GS;
-  extern __shared__ float s_acc[];  // [NG][fsize] footprint copies
-  const int lane = threadIdx.x, grp = lane / GS, gl = lane - grp * GS;
-  const bool act = gl < P1 * P1;
-  // the lane's x and y stencil offsets; lane c of a group (b = 0) also
-  // evaluates the z weight of index c for the group
-  const int a = gl % P1, b = gl / P1;
-  const int w = blk;
-  const int l0 = lstart[w], cnt = lstart[w + 1] - l0;
-  // nodes come in batches of 64, lane L holding entry f0 + L of the tile's
-  // list {node, footprint offset of its stencil}; the next batch is requested
-  // while the current one is added
-  auto fetch = [&](int f0, float4& ps, float& qq, int& off) {
-    const int f = f0 + lane;
-    const int2 e = list[l0 + (f < cnt ? f : 0)];
-    ps = pos4[e.x];
-    qq = f < cnt ? q[e.x] : 0.f;
-    off = e.y;
-  };
-  float4 ps = make_float4(0.f, 0.f, 0.f, 0.f);
-  float qq = 0.f;
-  int ofs = 0;
-  if (cnt > 0) fetch(0, ps, qq, ofs);
-  const int FXY = pl.fd[0] * pl.fd[1], fsize = pl.fsize;
-  for (int i = lane; i < NG * fsize; i += 64) s_acc[i] = 0.f;
+    GridParams g, ScPlan pl, const float* __restrict__ q, const float4* __restrict__ rec,
+    const int32_t* __restrict__ node, const int32_t* __restrict__ lstart,
+    const int32_t* __restrict__ tile, float* __restrict__ part, const int blk) {
+  constexpr int P1 = P + 1, NP = P1 * P1 * P1, K = (NP + 63) / 64;
+  constexpr int WS = P1 <= 4 ? 4 : 8;           // weights of one axis, padded
+  constexpr int NB = P1 <= 4 ? 64 : 32;         // nodes whose weights are held at a time
+  extern __shared__ float4 smem4[];
+  __shared__ float s_w[kScWaves][3][NB * WS];
+  const int lane = threadIdx.x & 63, T = 64 * kScWaves, nw = pl.nw;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l0 = lstart[blk], cnt = lstart[blk + 1] - l0;
+  float* out = part + (int64_t)tile[blk] * pl.fsize;
+  // thread (wv, lane) holds entry f0 + nw lane + wv of the list: its record
+  // {xi_x, xi_y, xi_z, LDS offset of its stencil} lies in list order, only its
+  // charge is gathered. The next batch's records and charges and the node
+  // indices of the one after are requested while a batch is added.
+  const int step = NB * nw;
+  const int slot = nw * (lane & (NB - 1)) + wv;
+  auto entry = [&](int f0) { return l0 + (f0 + slot < cnt ? f0 + slot : 0); };
+  float4 ps = rec[entry(0)];
+  int nd = node[entry(0)];
+  float qq = slot < cnt ? q[nd] : 0.f;
+  nd = node[entry(step)];
+  for (int i = threadIdx.x; i < nw * pl.lsize / 4; i += T)
+    smem4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
-  float* acc = s_acc + grp * fsize + b * pl.fd[0] + a;
-  Cubic cxa{}, cyb{};
-  if constexpr (P == 3) {
-    cxa = cubic_basis(a);
-    cyb = cubic_basis(b);
+  // the lane's stencil points (a, b, c)
+  float* acc = reinterpret_cast<float*>(smem4) + (wv < nw ? wv : 0) * pl.lsize;
+  int pt[K], pa[K], pb[K], pc[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = min(lane + 64 * k, NP - 1);
+    pa[k] = i % P1;
+    pb[k] = i / P1 % P1;
+    pc[k] = i / (P1 * P1);
+    pt[k] = pc[k] * pl.sz + pb[k] * pl.sy + pa[k];
   }
-  auto lane_basis = [&](int k, const Cubic& ck, float xi) {
-    if constexpr (P == 3) return cubic_eval(ck, xi);
-    else return lagrange(k, xi, P);
-  };
-  // one node: its stencil's contributions on the lane's (a, b) column, a
-  // plain read-add-write (the lanes of a group address distinct points of
-  // the group's own copy, and one wavefront's LDS accesses complete in order)
-  auto add = [&](float px, float py, float qv, int off, const float* lz) {
-    const float wab = qv * lane_basis(a, cxa, px) * lane_basis(b, cyb, py);
-    float* base = acc + off;
-    float v[P1];
+  float *wx = s_w[wv][0], *wy = s_w[wv][1], *wz = s_w[wv][2];
+  for (int f0 = 0; f0 < cnt && wv < nw; f0 += step) {
+    const float4 psn = rec[entry(f0 + step)];
+    const float qn = q[nd];
+    const float qqn = f0 + step + slot < cnt ? qn : 0.f;
+    nd = node[entry(f0 + 2 * step)];
+    // this wavefront's nodes of the batch
+    const int nb = min(NB, (cnt - f0 - wv + nw - 1) / nw);
+    wave_lds_sync();  // the previous batch's weights have been read
+    if (lane < NB) {
 #pragma unroll
-    for (int c = 0; c < P1; ++c) v[c] = base[c * FXY];
-#pragma unroll
-    for (int c = 0; c < P1; ++c) base[c * FXY] = fmaf(wab, lz[c], v[c]);
-    // keep the next node's reads behind these writes (other lanes' points)
-    __builtin_amdgcn_wave_barrier();
-  };
-  for (int f0 = 0; f0 < cnt; f0 += 64) {
-    float4 psn = make_float4(0.f, 0.f, 0.f, 0.f);
-    float qqn = 0.f;
-    int ofsn = 0;
-    if (f0 + 64 < cnt) fetch(f0 + 64, psn, qqn, ofsn);
-    const int nb = min(64, cnt - f0);
-    if constexpr (GS == 16) {
-      // group g adds the nodes of its row's lanes 0..15 in order
-      const int mine = nb - 16 * grp;  // nodes of this batch in the group's row
-#define PMFEM_SC_NODE(I)                                                                     \
-  {                                                                                          \
-    const float px = row_lane<I>(ps.x), py = row_lane<I>(ps.y), pz = row_lane<I>(ps.z);     \
-    const float qv = row_lane<I>(qq);                                                        \
-    const int off = __float_as_int(row_lane<I>(__int_as_float(ofs)));                        \
-    const float lzm = lane_basis(a, cxa, pz);                                                \
-    float lz[P1];                                                                            \
-    lz[0] = row_lane<0>(lzm);                                                                \
-    if constexpr (P1 > 1) lz[1 % P1] = row_lane<1>(lzm);                                     \
-    if constexpr (P1 > 2) lz[2 % P1] = row_lane<2>(lzm);                                     \
-    if constexpr (P1 > 3) lz[3 % P1] = row_lane<3>(lzm);                                     \
-    if (act && I < mine) add(px, py, qv, off, lz);                                           \
-  }
-      PMFEM_SC_NODE(0) PMFEM_SC_NODE(1) PMFEM_SC_NODE(2) PMFEM_SC_NODE(3)
-      PMFEM_SC_NODE(4) PMFEM_SC_NODE(5) PMFEM_SC_NODE(6) PMFEM_SC_NODE(7)
-      PMFEM_SC_NODE(8) PMFEM_SC_NODE(9) PMFEM_SC_NODE(10) PMFEM_SC_NODE(11)
-      PMFEM_SC_NODE(12) PMFEM_SC_NODE(13) PMFEM_SC_NODE(14) PMFEM_SC_NODE(15)
-#undef PMFEM_SC_NODE
-    } else {
-      // one group: every lane adds node i of the batch
-      for (int i = 0; i < nb; ++i) {
-        auto bc = [&](float v) {
-          return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-        };
-        const float px = bc(ps.x), py = bc(ps.y), pz = bc(ps.z), qv = bc(qq);
-        const int off = __builtin_amdgcn_readlane(ofs, i);
-        const float lzm = lane_basis(a, cxa, pz);
-        float lz[P1];
-#pragma unroll
-        for (int c = 0; c < P1; ++c)
-          lz[c] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lzm), c));
-        if (act) add(px, py, qv, off, lz);
+      for (int c = 0; c < P1; ++c) {
+        wx[lane * WS + c] = qq * basis_ct<P>(c, ps.x);
+        wy[lane * WS + c] = basis_ct<P>(c, ps.y);
+        wz[lane * WS + c] = basis_ct<P>(c, ps.z);
       }
+    }
+    wave_lds_sync();
+    float x[K], y[K], z[K];
+    auto weights = [&](int i) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        x[k] = wx[i * WS + pa[k]];
+        y[k] = wy[i * WS + pb[k]];
+        z[k] = wz[i * WS + pc[k]];
+      }
+    };
+    weights(0);
+#pragma unroll 4
+    for (int i = 0; i < nb; ++i) {
+      float* base = acc + __builtin_amdgcn_readlane(__float_as_int(ps.w), i);
+      float v[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = base[pt[k]];
+      float wxy[K], cz[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        wxy[k] = x[k] * y[k];
+        cz[k] = z[k];
+      }
+      weights(min(i + 1, NB - 1));
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (lane + 64 * k < NP) base[pt[k]] = fmaf(wxy[k], cz[k], v[k]);
+      // keep the next node's reads behind these writes (other lanes' points)
+      __builtin_amdgcn_wave_barrier();
     }
     ps = psn;
     qq = qqn;
-    ofs = ofsn;
   }
   __syncthreads();
-  float* out = part + (int64_t)w * fsize;
-  for (int i = lane; i < fsize; i += 64) {
-    float v = s_acc[i];
-#pragma unroll
-    for (int k = 1; k < NG; ++k) v += s_acc[k * fsize + i];
+  const float* s = reinterpret_cast<const float*>(smem4);
+  const int FX = pl.fd[0], FXY = FX * pl.fd[1];
+  const float ifx = 1.0f / (float)FX, ifxy = 1.0f / (float)FXY;
+  for (int i = threadIdx.x; i < pl.fsize; i += T) {
+    const int cz = fdiv(i, FXY, ifxy), r = i - cz * FXY, cy = fdiv(r, FX, ifx);
+    const int o = cz * pl.sz + cy * pl.sy + (r - cy * FX);
+    float v = s[o];
+    for (int k = 1; k < nw; ++k) v += s[k * pl.lsize + o];
     out[i] = v;
   }
 }
 
 template <int P>
-__global__ void __launch_bounds__(64) k_anterp_scatter(
-    GridParams g, ScPlan pl, const float* __restrict__ q, const float4* __restrict__ pos4,
-    const int2* __restrict__ list, const int32_t* __restrict__ lstart,
-    float* __restrict__ part) {
-  anterp_scatter_body<P>(g, pl, q, pos4, list, lstart, part, blockIdx.x);
+__global__ void __launch_bounds__(64 * kScWaves) k_anterp_scatter(
+    GridParams g, ScPlan pl, const float* __restrict__ q, const float4* __restrict__ rec,
+    const int32_t* __restrict__ node, const int32_t* __restrict__ lstart,
+    const int32_t* __restrict__ tile, float* __restrict__ part) {
+  anterp_scatter_body<P>(g, pl, q, rec, node, lstart, tile, part, blockIdx.x);
 }
 
 template <int P>
-__global__ void __launch_bounds__(64) k_anterp_scatter_cells(const CellTab* __restrict__ tab,
-                                                            const int32_t* __restrict__ bcell,
-                                                            const int32_t* __restrict__ boff) {
+__global__ void __launch_bounds__(64 * kScWaves) k_anterp_scatter_cells(
+    const CellTab* __restrict__ tab, const int32_t* __restrict__ bcell,
+    const int32_t* __restrict__ boff) {
   const int c = bcell[blockIdx.x];
   const CellTab& t = tab[c];
-  anterp_scatter_body<P>(t.g, t.sp, t.q, t.pos4, t.sc_list, t.sc_lstart, t.sc_part,
-                         blockIdx.x - boff[c]);
+  anterp_scatter_body<P>(t.g, t.sp, t.q, t.sc_rec, t.sc_node, t.sc_lstart, t.sc_tile,
+                         t.sc_part, blockIdx.x - boff[c]);
 }
 
 #define PMFEM_ANTERP_SCATTER(P)                                                               \
   template __global__ void k_anterp_scatter<P>(GridParams, ScPlan, const float*, const float4*, \
-                                               const int2*, const int32_t*, float*);         \
+                                               const int32_t*, const int32_t*,               \
+                                               const int32_t*, float*);                      \
   template __global__ void k_anterp_scatter_cells<P>(const CellTab*, const int32_t*,          \
                                                      const int32_t*);
 PMFEM_ANTERP_SCATTER(1)
@@ -899,15 +905,6 @@ __global__ void __launch_bounds__(256) k_r2c_x_cells(const CellTab* __restrict__
   const int c = bcell[blockIdx.x];
   const CellTab& t = tab[c];
   r2c_x_body(t.g, t.grid, t.spec, t.twx, t.lpb, blockIdx.x - boff[c]);
-}
-
-// n / d for 0 <= n < 2^22 and 1 <= d < 2^10 without an integer divide: the
-// float quotient is off by at most one, which the correction removes.
-__device__ __forceinline__ int fdiv(int n, int d, float inv_d) {
-  int q = (int)((float)n * inv_d);
-  if (q * d > n) --q;
-  else if ((q + 1) * d <= n) ++q;
-  return q;
 }
 
 // Forward transform of one z-plane held whole in LDS: real rows y < Ny are

@@ -71,3 +71,28 @@ def test_interpolation_tiles_do_not_change_the_sums(make):
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
     assert torch.equal(hb[:ctx.n], ref)
     batch.close()
+
+
+@pytest.mark.parametrize("p, rb, nx, grid", [
+    (1, 0, 5, (8, 8, 4)), (2, 1, 9, (12, 12, 4)), (3, 2, 16, (16, 16, 4)),
+    (3, 2, 40, (16, 16, 4)),      # several batches of 64 nodes per wavefront
+    (4, 1, 7, (16, 16, 8)), (5, 1, 12, (16, 16, 8)),
+    # tiles of 25 boxes along x and y: the wavefronts that take nodes are two
+    (5, 1, 6, (125, 125, 8)),
+])
+def test_scatter_anterpolation_against_the_tile_gather(p, rb, nx, grid):
+    """Every order of the scatter kernel against the gather by tiles, at node
+    counts below, at and past a wavefront's batch."""
+    prob = mg.kuhn_box((nx, nx + 1, 2), 1e-9, periodic=0b011, jitter=0.1, grid=grid)
+    ctx = B.Context.from_problem(prob, device=0, order_p=p, near_boxes=rb)
+    _, _, nou, _ = ctx.query()
+    m = torch.tensor(prob.m[nou], dtype=torch.float32, device="cuda")
+    h = []
+    for v in (3, 1):
+        ctx.set_variant("anterp", v)
+        h.append(torch.empty_like(m))
+        ctx.heff(m, h[-1], terms=B.TERM_MS)
+    torch.cuda.synchronize()
+    # two FP32 sums of the same charges in other orders; the far field is a
+    # part of H_ms of at most its size
+    assert float((h[0] - h[1]).norm() / h[1].norm()) < 1e-5
