@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -17,13 +18,8 @@
 using namespace pmfem;
 
 // launch shapes (each the best of the measured alternatives on MI355X)
-constexpr int kFftzB = 8;            // z columns per workgroup of the z pass
-// z columns per workgroup of the mixed-radix z pass (short columns: many)
-constexpr int kFftzMr = 64;
-// threads of a mixed-radix plane workgroup
-constexpr int kFftPlaneMrT = 512;
-constexpr int kFftzT = 256;          // threads per workgroup of the z pass
-constexpr int kFftSplit = 2;         // workgroups per z-plane in the plane transforms
+constexpr int kFftBlocks = 256;      // workgroups wanted of a one-axis FFT pass
+constexpr int kFftValues = 2048;     // values per workgroup of a one-axis FFT pass at most
 constexpr int kIcLdsBudget = 24576;  // LDS bytes per interpolation tile
 constexpr int kIcThreads = 256;      // threads per interpolation workgroup
 constexpr double kIcTiles = 600.0;   // full interpolation tiles wanted of one launch (plan_interp)
@@ -44,6 +40,12 @@ constexpr int kScWeights = 12288;      // LDS bytes of the scatter kernel's weig
 // it local, where the lookup cannot find it.
 constexpr int64_t kNoallocSpecMax = (int64_t)1 << 21;
 static __device__ __align__(256) float2 scratch[kNoallocSpecMax];
+
+// lines per workgroup, threads and dynamic LDS of an FFT pass
+struct FftLaunch {
+  int B = 1, T = 64;
+  size_t lds = 0;
+};
 
 struct pmfem_dev {
   int64_t n = 0;
@@ -72,9 +74,8 @@ struct pmfem_dev {
   bool ic_small_ok = false;
   bool ic_seg = false;        // false: the narrow tiles
   bool fft_plane = false;  // x and y transforms of a whole z-plane in one kernel
-  bool fft_mr = false;     // an FFT extent is not a power of two: mixed-radix passes
-  float2 *twfx = nullptr, *twfy = nullptr, *twfz = nullptr;  // full-circle twiddles (mixed radix)
-  size_t fft_plane_lds = 0;
+  FftPlane fp{};           // its LDS layout
+  FftLaunch fxy, fx, fy, fz;  // launch shapes of the plane and of the one-axis passes
   const char* kname[12] = {};  // kernel in each profiling slot
   hipStream_t side = nullptr;   // second stream: element correction beside the grid steps
   hipEvent_t fork = nullptr, join = nullptr;
@@ -216,20 +217,65 @@ void free_dev(pmfem_ctx* c) {
   c->dev = nullptr;
 }
 
-int ilog2(int v) {
-  int l = 0;
-  while ((1 << l) < v) ++l;
-  return l;
-}
-
+// exp(-2 pi i t / n), t < n
 std::vector<float2> twiddles(int n) {
-  std::vector<float2> t(n / 2 > 0 ? n / 2 : 1);
-  for (int k = 0; k < n / 2; ++k) {
-    double a = -2.0 * kPi * k / n;
+  std::vector<float2> t(n);
+  for (int k = 0; k < n; ++k) {
+    const double a = -2.0 * kPi * k / n;
     t[k] = make_float2((float)std::cos(a), (float)std::sin(a));
   }
   return t;
 }
+
+// The fewest passes over a line of n values (of those, the smallest largest
+// radix), radices in ascending order.
+FftAxis fft_axis(int n) {
+  FftAxis best{7, {}, {}};
+  FftAxis cur{0, {}, {}};
+  const int radices[] = {2, 3, 4, 5, 6, 7, 8, 9, 10};
+  std::function<void(int, int)> go = [&](int rest, int lo) {
+    if (rest == 1) {
+      if (cur.np < best.np ||
+          (cur.np == best.np && cur.np > 0 && cur.rad[cur.np - 1] < best.rad[best.np - 1]))
+        best = cur;
+      return;
+    }
+    if (cur.np == 6) return;
+    for (int r : radices)
+      if (r >= lo && rest % r == 0) {
+        cur.rad[cur.np++] = r;
+        go(rest / r, r);
+        --cur.np;
+      }
+  };
+  go(n, 2);
+  for (int p = 0, ns = 1; p < best.np; ++p) best.step[p] = n / (ns *= best.rad[p]);
+  return best;
+}
+
+// Threads of an FFT workgroup: two values each (four: 2 % slower on small
+// grids, the same on large ones).
+int fft_threads(int64_t values, int most) {
+  return (int)std::min<int64_t>(most, std::max<int64_t>(64, (values / 2 + 63) / 64 * 64));
+}
+
+// Launch shape of a one-axis pass over `lines` lines of n values: as many
+// lines per workgroup as leave kFftBlocks workgroups, between lo (which keeps
+// a strided axis' reads to whole 32-byte pieces) and hi. The z pass of 880
+// columns of 30 values took 16 us in 14 workgroups of 64 columns, 7 in 220 of
+// 4; 128, 256 and 512 workgroups wanted make no difference beyond 3 %.
+FftLaunch fft_launch(int64_t lines, int n, int lo, int hi) {
+  FftLaunch f;
+  f.B = hi;
+  while (f.B > lo && ((lines + f.B - 1) / f.B < kFftBlocks || f.B * n > kFftValues)) f.B /= 2;
+  f.T = fft_threads((int64_t)f.B * n, 256);
+  f.lds = (size_t)(n + 2 * f.B * fft_stride(n)) * sizeof(float2);
+  return f;
+}
+
+// Workgroups per z-plane: a grid of few planes shares each among up to eight
+// (they repeat the first of the plane's two axes).
+int fft_split(int64_t planes) { return (int)std::min<int64_t>(8, std::max<int64_t>(1, 256 / planes)); }
 
 // boxes covering each grid index along one axis: (first box, count)
 std::vector<int2> box_ranges(const HostOps& o, int a) {
@@ -737,7 +783,7 @@ int upload_all(pmfem_ctx* c) {
   for (int a = 0; a < 3; ++a) {
     d->g.N[a] = o.N[a];
     d->g.M[a] = o.M[a];
-    d->g.logM[a] = ilog2(o.M[a]);
+    d->g.fa[a] = fft_axis(o.M[a]);
     d->g.nbox[a] = o.nbox[a];
   }
   for (int a = 0; a < 3; ++a) d->g.per[a] = o.per[a];
@@ -763,31 +809,32 @@ int upload_all(pmfem_ctx* c) {
     if ((rc = upload(c, &L.rdesc, rdesc.data(), rdesc.size()))) return rc;
   }
 
-  for (int a = 0; a < 3; ++a)
-    if (o.M[a] & (o.M[a] - 1)) d->fft_mr = true;
   {
-    // whole-plane x/y transforms when a plane (row pairs + half-spectrum
-    // columns) fits in one workgroup's LDS: radix 2 in place with half
-    // twiddle tables, mixed radix with full tables and two buffers
+    // whole-plane x/y transforms when two buffers of a plane's row pairs or
+    // half-spectrum columns fit in one workgroup's LDS
     const int Mx = o.M[0], My = o.M[1], Hx = Mx / 2 + 1, pairs = (o.N[1] + 1) / 2;
-    const size_t cap = std::max((size_t)pairs * Mx, (size_t)Hx * My);
-    d->fft_plane_lds =
-        d->fft_mr ? (size_t)(Mx + My + 2 * cap) * sizeof(float2)
-                  : (size_t)(Mx / 2 + My / 2 + (size_t)pairs * Mx + (size_t)Hx * (My + 1)) *
-                        sizeof(float2);
     int max_lds = 0;
     (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
-    d->fft_ok = d->fft_plane_lds <= (size_t)max_lds;
-    if (d->fft_ok && d->fft_plane_lds > 65536) {
-      const int b = (int)d->fft_plane_lds;
-      const void* fwd = d->fft_mr ? (const void*)k_fft_xy_fwd_mr : (const void*)k_fft_xy_fwd;
-      const void* inv = d->fft_mr ? (const void*)k_fft_yx_inv_mr : (const void*)k_fft_yx_inv;
-      d->fft_ok = hipFuncSetAttribute(fwd, hipFuncAttributeMaxDynamicSharedMemorySize, b) ==
-                      hipSuccess &&
-                  hipFuncSetAttribute(inv, hipFuncAttributeMaxDynamicSharedMemorySize, b) ==
-                      hipSuccess;
+    FftPlane& f = d->fp;
+    f.ldx = fft_stride(Mx);
+    f.ldy = fft_stride(My);
+    f.cap = std::max(pairs * f.ldx, Hx * f.ldy);
+    d->fxy.lds = (size_t)(Mx + My + 2 * f.cap) * sizeof(float2);
+    d->fft_ok = d->fxy.lds <= (size_t)max_lds;
+    f.nsplit = fft_split(o.N[2]);
+    d->fxy.T = fft_threads(std::max(pairs * Mx, Hx * My), 1024);
+    if (d->fft_ok && d->fxy.lds > 65536) {
+      d->fft_ok = hipFuncSetAttribute((const void*)k_fft_xy_fwd,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      max_lds) == hipSuccess &&
+                  hipFuncSetAttribute((const void*)k_fft_yx_inv,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      max_lds) == hipSuccess;
       (void)hipGetLastError();
     }
+    d->fx = fft_launch((int64_t)pairs * o.N[2], Mx, 1, 16);
+    d->fy = fft_launch((int64_t)Hx * o.N[2], My, 4, 16);
+    d->fz = fft_launch((int64_t)My * Hx, o.M[2], 4, 64);
   }
 
   auto bx = box_ranges(o, 0), by = box_ranges(o, 1), bz = box_ranges(o, 2);
@@ -967,20 +1014,6 @@ int upload_all(pmfem_ctx* c) {
   if ((rc = upload(c, &d->twx, tx.data(), tx.size()))) return rc;
   if ((rc = upload(c, &d->twy, ty.data(), ty.size()))) return rc;
   if ((rc = upload(c, &d->twz, tz.data(), tz.size()))) return rc;
-  if (d->fft_mr) {
-    auto full = [](int n) {
-      std::vector<float2> t(n);
-      for (int k = 0; k < n; ++k) {
-        const double a = -2.0 * kPi * k / n;
-        t[k] = make_float2((float)std::cos(a), (float)std::sin(a));
-      }
-      return t;
-    };
-    auto fx = full(o.M[0]), fy = full(o.M[1]), fz = full(o.M[2]);
-    if ((rc = upload(c, &d->twfx, fx.data(), fx.size()))) return rc;
-    if ((rc = upload(c, &d->twfy, fy.data(), fy.size()))) return rc;
-    if ((rc = upload(c, &d->twfz, fz.data(), fz.size()))) return rc;
-  }
   if ((rc = upload(c, &d->mu, o.mu.data(), n))) return rc;
   if ((rc = dalloc(c, &d->hex, 3 * n))) return rc;
   if ((rc = dalloc(c, &d->q, n))) return rc;
@@ -1012,105 +1045,42 @@ void convolve(pmfem_dev* d, hipStream_t s, const float* Qg, float* Ug, float2* s
               Mark&& mark) {
   GridParams g = d->g;
   g.gmode = gmode;
-  const int T = 256;
-  const int Mx = g.M[0], My = g.M[1], Mz = g.M[2], Hx = Mx / 2 + 1;
-  const int Bz = std::max(1, std::min(kFftzB, 4096 / Mz)), Tz = kFftzT;
-  const int64_t cols = (int64_t)My * Hx;
-  if (d->fft_plane && d->fft_mr) {
-    // whole planes in LDS for x and y, the mixed-radix z pass between them
-    const int Bzm = std::max(1, std::min(kFftzMr, 2048 / Mz));
-    mark(2, 0);
-    hipLaunchKernelGGL(k_fft_xy_fwd_mr, dim3((unsigned)g.N[2]), dim3(kFftPlaneMrT),
-                       d->fft_plane_lds, s, g, Qg, spec, d->twfx, d->twfy);
-    mark(2, 1);
+  const int Hx = g.M[0] / 2 + 1;
+  const int64_t cols = (int64_t)g.M[1] * Hx;
+  auto zpass = [&] {
     mark(4, 0);
-    hipLaunchKernelGGL(k_fft_z_mul_mr, dim3((unsigned)((cols + Bzm - 1) / Bzm)), dim3(kFftzT),
-                       (size_t)(Mz + 2 * Bzm * Mz) * sizeof(float2), s, g, spec, d->khat, d->twfz,
-                       Bzm);
+    hipLaunchKernelGGL(k_fft_z_mul, dim3((unsigned)((cols + d->fz.B - 1) / d->fz.B)), dim3(d->fz.T),
+                       d->fz.lds, s, g, spec, d->khat, d->twz, d->fz.B);
     mark(4, 1);
-    mark(6, 0);
-    hipLaunchKernelGGL(k_fft_yx_inv_mr, dim3((unsigned)g.N[2]), dim3(kFftPlaneMrT),
-                       d->fft_plane_lds, s, g, (const float2*)spec, Ug, d->twfx, d->twfy);
-    mark(6, 1);
-    return;
-  }
+  };
   if (d->fft_plane) {
+    const dim3 grid((unsigned)(g.N[2] * d->fp.nsplit)), blk(d->fxy.T);
     mark(2, 0);
-    hipLaunchKernelGGL(k_fft_xy_fwd, dim3((unsigned)(g.N[2] * kFftSplit)), dim3(1024),
-                       d->fft_plane_lds, s, g, Qg, spec, d->twx, d->twy, kFftSplit);
+    hipLaunchKernelGGL(k_fft_xy_fwd, grid, blk, d->fxy.lds, s, g, Qg, spec, d->twx, d->twy, d->fp);
     mark(2, 1);
-    mark(4, 0);
-    hipLaunchKernelGGL(k_fft_z_mul, dim3((unsigned)((cols + Bz - 1) / Bz)), dim3(Tz),
-                       (size_t)(Mz / 2 + Bz * Mz) * sizeof(float2), s, g, spec, d->khat,
-                       d->twz, Bz);
-    mark(4, 1);
+    zpass();
     mark(6, 0);
-    hipLaunchKernelGGL(k_fft_yx_inv, dim3((unsigned)(g.N[2] * kFftSplit)), dim3(1024),
-                       d->fft_plane_lds, s, g, (const float2*)spec, Ug, d->twx, d->twy,
-                       kFftSplit);
+    hipLaunchKernelGGL(k_fft_yx_inv, grid, blk, d->fxy.lds, s, g, (const float2*)spec, Ug, d->twx,
+                       d->twy, d->fp);
     mark(6, 1);
     return;
   }
-  if (d->fft_mr) {
-    // mixed-radix passes: twiddle table and two line buffers in LDS
-    const int lpb = std::max(1, 2048 / Mx);
-    const int64_t xlines = (int64_t)((g.N[1] + 1) / 2) * g.N[2];
-    const int By = std::max(1, std::min(16, 2048 / My));
-    const int gy = (Hx + By - 1) / By;
-    const int Bzm = std::max(1, std::min(kFftzMr, 2048 / Mz));
-    mark(2, 0);
-    hipLaunchKernelGGL(k_r2c_x_mr, dim3((unsigned)((xlines + lpb - 1) / lpb)), dim3(T),
-                       (size_t)(Mx + 2 * lpb * Mx) * sizeof(float2), s, g, Qg, spec, d->twfx, lpb);
-    mark(2, 1);
-    mark(3, 0);
-    hipLaunchKernelGGL(k_fft_y_mr, dim3((unsigned)(g.N[2] * gy)), dim3(T),
-                       (size_t)(My + 2 * By * My) * sizeof(float2), s, g, spec, d->twfy, By, 0,
-                       g.N[1], My);
-    mark(3, 1);
-    mark(4, 0);
-    hipLaunchKernelGGL(k_fft_z_mul_mr, dim3((unsigned)((cols + Bzm - 1) / Bzm)), dim3(kFftzT),
-                       (size_t)(Mz + 2 * Bzm * Mz) * sizeof(float2), s, g, spec, d->khat, d->twfz,
-                       Bzm);
-    mark(4, 1);
-    mark(5, 0);
-    hipLaunchKernelGGL(k_fft_y_mr, dim3((unsigned)(g.N[2] * gy)), dim3(T),
-                       (size_t)(My + 2 * By * My) * sizeof(float2), s, g, spec, d->twfy, By, 1,
-                       My, g.N[1]);
-    mark(5, 1);
-    mark(6, 0);
-    hipLaunchKernelGGL(k_c2r_x_mr, dim3((unsigned)((xlines + lpb - 1) / lpb)), dim3(T),
-                       (size_t)(Mx + 2 * lpb * Mx) * sizeof(float2), s, g, spec, Ug, d->twfx, lpb);
-    mark(6, 1);
-    return;
-  }
-  const int lpb = std::max(1, 2048 / Mx);
   const int64_t xlines = (int64_t)((g.N[1] + 1) / 2) * g.N[2];
+  const dim3 gx((unsigned)((xlines + d->fx.B - 1) / d->fx.B));
+  const dim3 gy((unsigned)(g.N[2] * ((Hx + d->fy.B - 1) / d->fy.B)));
   mark(2, 0);
-  hipLaunchKernelGGL(k_r2c_x, dim3((unsigned)((xlines + lpb - 1) / lpb)), dim3(T),
-                     (size_t)(Mx / 2 + lpb * Mx) * sizeof(float2), s, g, Qg, spec, d->twx,
-                     lpb);
+  hipLaunchKernelGGL(k_r2c_x, gx, dim3(d->fx.T), d->fx.lds, s, g, Qg, spec, d->twx, d->fx.B);
   mark(2, 1);
-  const int By = std::max(1, std::min(16, 4096 / My));
-  const int gy = (Hx + By - 1) / By;
   mark(3, 0);
-  hipLaunchKernelGGL(k_fft_y, dim3((unsigned)(g.N[2] * gy)), dim3(T),
-                     (size_t)(My / 2 + By * My) * sizeof(float2), s, g, spec, d->twy, By, 0,
-                     g.N[1], My);
+  hipLaunchKernelGGL(k_fft_y, gy, dim3(d->fy.T), d->fy.lds, s, g, spec, d->twy, d->fy.B, 0);
   mark(3, 1);
-  mark(4, 0);
-  hipLaunchKernelGGL(k_fft_z_mul, dim3((unsigned)((cols + Bz - 1) / Bz)), dim3(Tz),
-                     (size_t)(Mz / 2 + Bz * Mz) * sizeof(float2), s, g, spec, d->khat, d->twz,
-                     Bz);
-  mark(4, 1);
+  zpass();
   mark(5, 0);
-  hipLaunchKernelGGL(k_fft_y, dim3((unsigned)(g.N[2] * gy)), dim3(T),
-                     (size_t)(My / 2 + By * My) * sizeof(float2), s, g, spec, d->twy, By, 1,
-                     My, g.N[1]);
+  hipLaunchKernelGGL(k_fft_y, gy, dim3(d->fy.T), d->fy.lds, s, g, spec, d->twy, d->fy.B, 1);
   mark(5, 1);
   mark(6, 0);
-  hipLaunchKernelGGL(k_c2r_x, dim3((unsigned)((xlines + lpb - 1) / lpb)), dim3(T),
-                     (size_t)(Mx / 2 + lpb * Mx) * sizeof(float2), s, g, spec, Ug, d->twx,
-                     lpb);
+  hipLaunchKernelGGL(k_c2r_x, gx, dim3(d->fx.T), d->fx.lds, s, g, (const float2*)spec, Ug, d->twx,
+                     d->fx.B);
   mark(6, 1);
 }
 
@@ -1940,10 +1910,10 @@ struct pmfem_batch {
     int32_t* bcell = nullptr;
     int32_t* boff = nullptr;
     unsigned blocks = 0;
-  } sc, sum, xy, zm, yx, ic, r2c, fy, c2r, r2c_mr, fy_mr, zm_mr, xy_mr;
-  size_t lds_sc = 0, lds_plane = 0, lds_z = 0, lds_ic = 0, lds_r2c = 0, lds_fy = 0;
-  size_t lds_r2c_mr = 0, lds_fy_mr = 0, lds_z_mr = 0, lds_plane_mr = 0;
-  int p = 3, W = 5, KC = 2, PT = 4, Bz = 8, Bzm = kFftzMr;
+  } sc, sum, xy, zm, ic, xl, yl;
+  size_t lds_sc = 0, lds_ic = 0;
+  FftLaunch fxy, fx, fy, fz;  // threads and LDS of the FFT passes, the largest of any cell
+  int p = 3, W = 5, KC = 2, PT = 4;
   double bytes = 0.0;
   std::vector<void*> allocs;
   std::string err;
@@ -2083,8 +2053,25 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     return rc;
   // the cell table and the launch tables of the grid kernels
   std::vector<CellTab> tab(K);
-  std::vector<int64_t> nsc(K), nsum(K), nxy(K), nzm(K), nic(K), nr2c(K), nfy(K), nr2c_mr(K),
-      nfy_mr(K), nzm_mr(K), nxy_mr(K);
+  std::vector<int64_t> nsc(K), nsum(K), nxy(K, 0), nzm(K), nic(K), nxl(K, 0), nyl(K, 0);
+  // lines of every FFT pass over all cells, which share one launch
+  int64_t planes = 0, xlines = 0, ylines = 0, zlines = 0;
+  for (size_t c = 0; c < K; ++c) {
+    const GridParams& g = b->cells[c]->dev->g;
+    const int Hx = g.M[0] / 2 + 1;
+    zlines += (int64_t)g.M[1] * Hx;
+    if (b->cells[c]->dev->fft_ok) {
+      planes += g.N[2];
+    } else {
+      xlines += (int64_t)((g.N[1] + 1) / 2) * g.N[2];
+      ylines += (int64_t)Hx * g.N[2];
+    }
+  }
+  auto widest = [](FftLaunch& f, const FftLaunch& one) {
+    f.T = std::max(f.T, one.T);
+    f.lds = std::max(f.lds, one.lds);
+    return one.B;
+  };
   b->p = b->cells[0]->dev->g.p;
   b->W = 2 * b->cells[0]->dev->g.rb + 1;
   b->PT = 4;
@@ -2127,9 +2114,6 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     t.twx = d->twx;
     t.twy = d->twy;
     t.twz = d->twz;
-    t.twfx = d->twfx;
-    t.twfy = d->twfy;
-    t.twfz = d->twfz;
     // interpolation: the cell's tiles, or larger ones where the other cells
     // of the batch fill the launch (its share of the tiles wanted)
     IcPlan ipl = d->ic_ok ? d->icp : d->icp_small;
@@ -2159,82 +2143,39 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     nsc[c] = d->sp.nwg;
     nsum[c] = (ng / b->PT + 255) / 256;
     // FFT: whole z-planes in LDS where they fit, else one axis per pass
-    // (radix 2, or mixed radix where an extent is not a power of two)
-    t.lpb = std::max(1, 2048 / g.M[0]);
-    t.by = std::max(1, std::min(16, 4096 / g.M[1]));
-    nr2c_mr[c] = nfy_mr[c] = nxy_mr[c] = 0;
-    if (d->fft_mr && d->fft_ok) {
-      nxy[c] = nr2c[c] = nfy[c] = 0;
-      nxy_mr[c] = g.N[2];
-      b->lds_plane_mr = std::max(b->lds_plane_mr, d->fft_plane_lds);
-      b->Bzm = std::min(b->Bzm, std::max(1, std::min(kFftzMr, 2048 / g.M[2])));
-    } else if (d->fft_mr) {
-      nxy[c] = nr2c[c] = nfy[c] = 0;
-      t.by = std::max(1, std::min(16, 2048 / g.M[1]));
-      const int64_t xlines = (int64_t)((g.N[1] + 1) / 2) * g.N[2];
-      nr2c_mr[c] = (xlines + t.lpb - 1) / t.lpb;
-      nfy_mr[c] = (int64_t)g.N[2] * ((Hx + t.by - 1) / t.by);
-      b->lds_r2c_mr =
-          std::max(b->lds_r2c_mr, (size_t)(g.M[0] + 2 * t.lpb * g.M[0]) * sizeof(float2));
-      b->lds_fy_mr = std::max(b->lds_fy_mr, (size_t)(g.M[1] + 2 * t.by * g.M[1]) * sizeof(float2));
-      b->Bzm = std::min(b->Bzm, std::max(1, std::min(kFftzMr, 2048 / g.M[2])));
-    } else if (d->fft_ok) {
-      nxy[c] = (int64_t)g.N[2] * kFftSplit;
-      nr2c[c] = nfy[c] = 0;
-      b->lds_plane = std::max(b->lds_plane, d->fft_plane_lds);
+    t.fp = d->fp;
+    t.bx = t.by = 1;
+    if (d->fft_ok) {
+      t.fp.nsplit = fft_split(planes);
+      nxy[c] = (int64_t)g.N[2] * t.fp.nsplit;
+      widest(b->fxy, d->fxy);
     } else {
-      nxy[c] = 0;
-      const int64_t xlines = (int64_t)((g.N[1] + 1) / 2) * g.N[2];
-      nr2c[c] = (xlines + t.lpb - 1) / t.lpb;
-      nfy[c] = (int64_t)g.N[2] * ((Hx + t.by - 1) / t.by);
-      b->lds_r2c = std::max(b->lds_r2c, (size_t)(g.M[0] / 2 + t.lpb * g.M[0]) * sizeof(float2));
-      b->lds_fy = std::max(b->lds_fy, (size_t)(g.M[1] / 2 + t.by * g.M[1]) * sizeof(float2));
+      t.bx = widest(b->fx, fft_launch(xlines, g.M[0], 1, 16));
+      t.by = widest(b->fy, fft_launch(ylines, g.M[1], 4, 16));
+      nxl[c] = ((int64_t)((g.N[1] + 1) / 2) * g.N[2] + t.bx - 1) / t.bx;
+      nyl[c] = (int64_t)g.N[2] * ((Hx + t.by - 1) / t.by);
     }
-    if (!d->fft_mr) b->Bz = std::min(b->Bz, std::max(1, std::min(kFftzB, 4096 / g.M[2])));
+    t.bz = widest(b->fz, fft_launch(zlines, g.M[2], 4, 64));
+    nzm[c] = ((int64_t)g.M[1] * Hx + t.bz - 1) / t.bz;
     nic[c] = ipl.nwg;
     b->lds_sc = std::max(b->lds_sc, (size_t)d->sp.lds_bytes);
     b->lds_ic = std::max(b->lds_ic, (size_t)ipl.lds_bytes);
     b->KC = std::max(b->KC, ipl.kc);
   }
-  for (size_t c = 0; c < K; ++c) {
-    const GridParams& g = b->cells[c]->dev->g;
-    const int64_t cols = (int64_t)g.M[1] * (g.M[0] / 2 + 1);
-    if (b->cells[c]->dev->fft_mr) {
-      nzm[c] = 0;
-      nzm_mr[c] = (cols + b->Bzm - 1) / b->Bzm;
-      b->lds_z_mr = std::max(b->lds_z_mr, (size_t)(g.M[2] + 2 * b->Bzm * g.M[2]) * sizeof(float2));
-    } else {
-      nzm_mr[c] = 0;
-      nzm[c] = (cols + b->Bz - 1) / b->Bz;
-      b->lds_z = std::max(b->lds_z, (size_t)(g.M[2] / 2 + b->Bz * g.M[2]) * sizeof(float2));
-    }
-  }
   if ((rc = bupload(b, &b->tab, tab.data(), K)) || (rc = batch_launch_table(b, nsc, b->sc)) ||
       (rc = batch_launch_table(b, nsum, b->sum)) || (rc = batch_launch_table(b, nxy, b->xy)) ||
-      (rc = batch_launch_table(b, nxy, b->yx)) || (rc = batch_launch_table(b, nzm, b->zm)) ||
-      (rc = batch_launch_table(b, nic, b->ic)) || (rc = batch_launch_table(b, nr2c, b->r2c)) ||
-      (rc = batch_launch_table(b, nfy, b->fy)) || (rc = batch_launch_table(b, nr2c, b->c2r)) ||
-      (rc = batch_launch_table(b, nr2c_mr, b->r2c_mr)) ||
-      (rc = batch_launch_table(b, nfy_mr, b->fy_mr)) ||
-      (rc = batch_launch_table(b, nzm_mr, b->zm_mr)) ||
-      (rc = batch_launch_table(b, nxy_mr, b->xy_mr)))
+      (rc = batch_launch_table(b, nzm, b->zm)) || (rc = batch_launch_table(b, nic, b->ic)) ||
+      (rc = batch_launch_table(b, nxl, b->xl)) || (rc = batch_launch_table(b, nyl, b->yl)))
     return rc;
   if (!scatter_lds(b->p, true, (int)b->lds_sc))
     return batch_err(b, PMFEM_EINVAL, "scatter tiles of the batch do not fit in LDS");
-  if (b->lds_plane_mr > 65536) {
-    const int lb = (int)b->lds_plane_mr;
-    if (hipFuncSetAttribute((const void*)k_fft_xy_fwd_mr_cells,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lb) != hipSuccess ||
-        hipFuncSetAttribute((const void*)k_fft_yx_inv_mr_cells,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lb) != hipSuccess)
-      return batch_err(b, PMFEM_EINVAL, "FFT planes of the batch do not fit in LDS");
-  }
-  if (b->lds_plane > 65536) {
-    const int lb = (int)b->lds_plane;
+  if (b->fxy.lds > 65536) {
+    int max_lds = 0;
+    (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, b->device);
     if (hipFuncSetAttribute((const void*)k_fft_xy_fwd_cells,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lb) != hipSuccess ||
+                            hipFuncAttributeMaxDynamicSharedMemorySize, max_lds) != hipSuccess ||
         hipFuncSetAttribute((const void*)k_fft_yx_inv_cells,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lb) != hipSuccess)
+                            hipFuncAttributeMaxDynamicSharedMemorySize, max_lds) != hipSuccess)
       return batch_err(b, PMFEM_EINVAL, "FFT planes of the batch do not fit in LDS");
   }
   return PMFEM_OK;
@@ -2326,51 +2267,18 @@ int batch_heff(pmfem_batch* b, const float* m, float* h, uint32_t terms) {
                          (const int32_t*)b->sum.bcell, (const int32_t*)b->sum.boff);
     // cells whose z-planes fit in LDS take the plane passes, the others the
     // per-axis passes; the z pass with the K multiply serves both
-    if (b->xy.blocks)
-      hipLaunchKernelGGL(k_fft_xy_fwd_cells, dim3(b->xy.blocks), dim3(1024), b->lds_plane, s, tab,
-                         (const int32_t*)b->xy.bcell, (const int32_t*)b->xy.boff, kFftSplit);
-    if (b->r2c.blocks) {
-      hipLaunchKernelGGL(k_r2c_x_cells, dim3(b->r2c.blocks), dim3(T), b->lds_r2c, s, tab,
-                         (const int32_t*)b->r2c.bcell, (const int32_t*)b->r2c.boff);
-      hipLaunchKernelGGL(k_fft_y_cells, dim3(b->fy.blocks), dim3(T), b->lds_fy, s, tab,
-                         (const int32_t*)b->fy.bcell, (const int32_t*)b->fy.boff, 0);
-    }
-    if (b->xy_mr.blocks)
-      hipLaunchKernelGGL(k_fft_xy_fwd_mr_cells, dim3(b->xy_mr.blocks), dim3(kFftPlaneMrT),
-                         b->lds_plane_mr, s, tab, (const int32_t*)b->xy_mr.bcell,
-                         (const int32_t*)b->xy_mr.boff);
-    if (b->r2c_mr.blocks) {
-      hipLaunchKernelGGL(k_r2c_x_mr_cells, dim3(b->r2c_mr.blocks), dim3(T), b->lds_r2c_mr, s, tab,
-                         (const int32_t*)b->r2c_mr.bcell, (const int32_t*)b->r2c_mr.boff);
-      hipLaunchKernelGGL(k_fft_y_mr_cells, dim3(b->fy_mr.blocks), dim3(T), b->lds_fy_mr, s, tab,
-                         (const int32_t*)b->fy_mr.bcell, (const int32_t*)b->fy_mr.boff, 0);
-    }
-    if (b->zm_mr.blocks)
-      hipLaunchKernelGGL(k_fft_z_mul_mr_cells, dim3(b->zm_mr.blocks), dim3(kFftzT), b->lds_z_mr,
-                         s, tab, (const int32_t*)b->zm_mr.bcell, (const int32_t*)b->zm_mr.boff,
-                         b->Bzm);
-    if (b->xy_mr.blocks)
-      hipLaunchKernelGGL(k_fft_yx_inv_mr_cells, dim3(b->xy_mr.blocks), dim3(kFftPlaneMrT),
-                         b->lds_plane_mr, s, tab, (const int32_t*)b->xy_mr.bcell,
-                         (const int32_t*)b->xy_mr.boff);
-    if (b->r2c_mr.blocks) {
-      hipLaunchKernelGGL(k_fft_y_mr_cells, dim3(b->fy_mr.blocks), dim3(T), b->lds_fy_mr, s, tab,
-                         (const int32_t*)b->fy_mr.bcell, (const int32_t*)b->fy_mr.boff, 1);
-      hipLaunchKernelGGL(k_c2r_x_mr_cells, dim3(b->r2c_mr.blocks), dim3(T), b->lds_r2c_mr, s, tab,
-                         (const int32_t*)b->r2c_mr.bcell, (const int32_t*)b->r2c_mr.boff);
-    }
-    if (b->zm.blocks)
-      hipLaunchKernelGGL(k_fft_z_mul_cells, dim3(b->zm.blocks), dim3(kFftzT), b->lds_z, s, tab,
-                         (const int32_t*)b->zm.bcell, (const int32_t*)b->zm.boff, b->Bz);
-    if (b->yx.blocks)
-      hipLaunchKernelGGL(k_fft_yx_inv_cells, dim3(b->yx.blocks), dim3(1024), b->lds_plane, s, tab,
-                         (const int32_t*)b->yx.bcell, (const int32_t*)b->yx.boff, kFftSplit);
-    if (b->r2c.blocks) {
-      hipLaunchKernelGGL(k_fft_y_cells, dim3(b->fy.blocks), dim3(T), b->lds_fy, s, tab,
-                         (const int32_t*)b->fy.bcell, (const int32_t*)b->fy.boff, 1);
-      hipLaunchKernelGGL(k_c2r_x_cells, dim3(b->c2r.blocks), dim3(T), b->lds_r2c, s, tab,
-                         (const int32_t*)b->c2r.bcell, (const int32_t*)b->c2r.boff);
-    }
+    auto pass = [&](auto kernel, const pmfem_batch::Launch& L, const FftLaunch& f, auto... more) {
+      if (L.blocks)
+        hipLaunchKernelGGL(kernel, dim3(L.blocks), dim3(f.T), f.lds, s, tab,
+                           (const int32_t*)L.bcell, (const int32_t*)L.boff, more...);
+    };
+    pass(k_fft_xy_fwd_cells, b->xy, b->fxy);
+    pass(k_r2c_x_cells, b->xl, b->fx);
+    pass(k_fft_y_cells, b->yl, b->fy, 0);
+    pass(k_fft_z_mul_cells, b->zm, b->fz);
+    pass(k_fft_yx_inv_cells, b->xy, b->fxy);
+    pass(k_fft_y_cells, b->yl, b->fy, 1);
+    pass(k_c2r_x_cells, b->xl, b->fx);
     if (overlap) (void)hipStreamWaitEvent(s, b->join, 0);
     switch (b->W) {
       case 1:

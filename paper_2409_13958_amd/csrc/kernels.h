@@ -6,10 +6,17 @@
 
 namespace pmfem {
 
+// passes of a transform: radices 2 .. 10 whose product is its length n, and n
+// divided by the product of the radices up to each pass
+struct FftAxis {
+  int np;
+  int rad[6], step[6];
+};
+
 struct GridParams {
   int N[3];     // grid points per axis
   int M[3];     // FFT extents (N periodic, 2N otherwise)
-  int logM[3];
+  FftAxis fa[3];
   int nbox[3];  // boxes per axis
   int per[3];   // periodic axes
   int p;        // Lagrange order
@@ -70,6 +77,15 @@ struct ScPlan {
   int lds_bytes;
 };
 
+// LDS stride of a line of n values (odd)
+__host__ __device__ constexpr int fft_stride(int n) { return n | 1; }
+
+// whole z-planes in LDS: workgroups per plane, values of each of the two
+// buffers, line strides of the x lines and of the columns
+struct FftPlane {
+  int nsplit, cap, ldx, ldy;
+};
+
 // One unit cell of a batch: its grid and kernel plans, its own operator
 // arrays, and its slices of the batch's per-unknown vectors. The multi-cell
 // kernels (k_*_cells) take every workgroup's cell from a block-to-cell table
@@ -88,12 +104,12 @@ struct CellTab {
   float2* spec;
   const float* khat;
   const float2 *twx, *twy, *twz;
-  const float2 *twfx, *twfy, *twfz;  // full-circle tables of the mixed-radix passes
   const int32_t *ic_list, *ic_lstart, *ic_wseg;
   const uint32_t* ic_rdesc;
   const int32_t* prp;
   const float* pv;
-  int lpb, by;      // per-axis FFT form: x lines per block, y columns per block
+  FftPlane fp;
+  int bx, by, bz;   // x lines, y columns and z columns per workgroup
   const float* q;   // the cell's charges in the batch vector
   const float* uz;  // element correction
   float* u;         // potential
@@ -127,43 +143,18 @@ __global__ void k_anterp_scatter(GridParams g, ScPlan pl, const float* q, const 
 template <int PT>
 __global__ void k_anterp_sum(GridParams g, ScPlan pl, const int2* tabx, const int2* taby,
                              const int2* tabz, const float* part, float* Q);
-__global__ void k_r2c_x(GridParams g, const float* Q, float2* spec, const float2* twx,
-                        int lines_per_block);
-__global__ void k_fft_y(GridParams g, float2* spec, const float2* twy, int B, int inverse,
-                        int n_in, int n_out);
-// nsplit workgroups per z-plane (1 or 2)
+// FFT passes (fft.hip); tw*[t] = exp(-2 pi i t / M), t < M; dynamic LDS: the
+// tables of the axes and two buffers of lines
 __global__ void k_fft_xy_fwd(GridParams g, const float* Q, float2* spec, const float2* twx,
-                             const float2* twy, int nsplit);
+                             const float2* twy, FftPlane pl);
 __global__ void k_fft_yx_inv(GridParams g, const float2* spec, float* U, const float2* twx,
-                             const float2* twy, int nsplit);
+                             const float2* twy, FftPlane pl);
+__global__ void k_r2c_x(GridParams g, const float* Q, float2* spec, const float2* twx, int B);
+__global__ void k_c2r_x(GridParams g, const float2* spec, float* U, const float2* twx, int B);
+// inverse = 0: rows y < N_y in, all M_y out; 1: all in, y < N_y out
+__global__ void k_fft_y(GridParams g, float2* spec, const float2* twy, int B, int inverse);
 __global__ void k_fft_z_mul(GridParams g, float2* spec, const float* khat, const float2* twz,
                             int B);
-__global__ void k_c2r_x(GridParams g, const float2* spec, float* U, const float2* twx,
-                        int lines_per_block);
-// mixed-radix forms (extents that are products of 2, 3, 5, 7); twf[t] =
-// exp(-2 pi i t / M) for t < M; dynamic LDS: (M + 2 lines M) complex values
-__global__ void k_r2c_x_mr(GridParams g, const float* Q, float2* spec, const float2* twf,
-                           int lines_per_block);
-__global__ void k_fft_y_mr(GridParams g, float2* spec, const float2* twf, int B, int inverse,
-                           int n_in, int n_out);
-__global__ void k_fft_z_mul_mr(GridParams g, float2* spec, const float* khat, const float2* twf,
-                               int B);
-__global__ void k_c2r_x_mr(GridParams g, const float2* spec, float* U, const float2* twf,
-                           int lines_per_block);
-__global__ void k_fft_xy_fwd_mr(GridParams g, const float* Q, float2* spec, const float2* twfx,
-                                const float2* twfy);
-__global__ void k_fft_yx_inv_mr(GridParams g, const float2* spec, float* U, const float2* twfx,
-                                const float2* twfy);
-__global__ void k_fft_xy_fwd_mr_cells(const CellTab* tab, const int32_t* bcell,
-                                      const int32_t* boff);
-__global__ void k_fft_yx_inv_mr_cells(const CellTab* tab, const int32_t* bcell,
-                                      const int32_t* boff);
-__global__ void k_r2c_x_mr_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
-__global__ void k_fft_y_mr_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff,
-                                 int inverse);
-__global__ void k_fft_z_mul_mr_cells(const CellTab* tab, const int32_t* bcell,
-                                     const int32_t* boff, int B);
-__global__ void k_c2r_x_mr_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
 
 // lanes per observer row of k_interp_tile (8 x 16 B = one 128 B line per
 // load; 4 and 16 measured slower)
@@ -180,18 +171,15 @@ __global__ void k_anterp_scatter_cells(const CellTab* tab, const int32_t* bcell,
                                        const int32_t* boff);
 template <int PT>
 __global__ void k_anterp_sum_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
-__global__ void k_fft_xy_fwd_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff,
-                                   int nsplit);
-__global__ void k_fft_yx_inv_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff,
-                                   int nsplit);
-__global__ void k_fft_z_mul_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff,
-                                  int B);
-template <int WT, int KC>
-__global__ void k_interp_tile_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
+__global__ void k_fft_xy_fwd_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
+__global__ void k_fft_yx_inv_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
 __global__ void k_r2c_x_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
+__global__ void k_c2r_x_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
 __global__ void k_fft_y_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff,
                               int inverse);
-__global__ void k_c2r_x_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
+__global__ void k_fft_z_mul_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
+template <int WT, int KC>
+__global__ void k_interp_tile_cells(const CellTab* tab, const int32_t* bcell, const int32_t* boff);
 template <int G, typename MT>
 __global__ void k_exch(int64_t n, const int32_t* rp, const int2* lrec, const MT* m, float* hex);
 template <int G>

@@ -4,10 +4,7 @@
 //   k_rowdot3      q = D m (Eq. hms_d1); on a second stream u_Z = Z0 m (Eq. hms_d2b)
 //   k_anterp_scatter, k_anterp_sum  Q = W^T q      (Sec. 3.2.2, step 1; other forms:
 //                  k_anterp_line by grid lines, k_anterp by tiles, both gathers)
-//   k_fft_xy_fwd   real-to-complex FFT along x, FFT along y, per z-plane (step 2)
-//   k_fft_z_mul    FFT along z, multiply by the PGF spectrum, inverse along z
-//   k_fft_yx_inv   inverse FFT along y, complex-to-real along x -> U = (1/4 pi) K * Q
-//                  (k_r2c_x, k_fft_y, k_c2r_x: the same passes one axis at a time)
+//   (fft.hip)      U = (1/4 pi) K * Q             (step 2)
 //   k_interp_tile  u = W U + P q + u_Z            (steps 3 and 4)
 //   k_exch         H_ex = L m, as differences     (Eqs. hex, lapl_2; second stream)
 //   k_mprod        q, u_Z and H_ex in one launch  (small cells; no second stream)
@@ -18,6 +15,7 @@
 
 #include <cstdint>
 
+#include "device.h"
 #include "kernels.h"
 
 namespace pmfem {
@@ -63,43 +61,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Grid storage (GridParams::gmode). BF16 is the upper half of an FP32 word,
-// rounded to nearest even (the grid values are finite); the pair form keeps
-// the rounding residual as a second BF16 value, so hi + lo carries 16
-// significant bits. Arithmetic stays FP32: values are widened on load.
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) {
-  return __uint_as_float((uint32_t)h << 16);
-}
-
-__device__ __forceinline__ int64_t grid_points(const GridParams& g) {
-  return (int64_t)g.N[0] * g.N[1] * g.N[2];
-}
-
-__device__ __forceinline__ void grid_store(float* G, int64_t i, float v, const GridParams& g) {
-  if (g.gmode == 0) {
-    G[i] = v;
-    return;
-  }
-  uint16_t* H = reinterpret_cast<uint16_t*>(G);
-  const uint16_t hi = f32_to_bf16(v);
-  H[i] = hi;
-  if (g.gmode == 2) H[grid_points(g) + i] = f32_to_bf16(v - bf16_to_f32(hi));
-}
-
-__device__ __forceinline__ float grid_load(const float* G, int64_t i, const GridParams& g) {
-  if (g.gmode == 0) return G[i];
-  const uint16_t* H = reinterpret_cast<const uint16_t*>(G);
-  float v = bf16_to_f32(H[i]);
-  if (g.gmode == 2) v += bf16_to_f32(H[grid_points(g) + i]);
-  return v;
-}
-
 __device__ __forceinline__ int st_of(uint32_t packed, int axis) {
   return (int)((packed >> (10 * axis)) & 1023u);
 }
@@ -122,25 +83,6 @@ __device__ __forceinline__ int row_cum(const int32_t* box_start, int64_t srow, i
   return box_start[srow + min(max(x, 0), nbx)];
 }
 
-// Block-strided copy loop with K loads in flight per thread: load(i) for K
-// indices first, then store(i, value) for the same K.
-template <int K, class Load, class Store>
-__device__ __forceinline__ void batched(int n, Load&& load, Store&& store) {
-  for (int i0 = threadIdx.x; i0 < n; i0 += K * blockDim.x) {
-    decltype(load(0)) v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = i0 + k * blockDim.x;
-      if (i < n) v[k] = load(i);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = i0 + k * blockDim.x;
-      if (i < n) store(i, v[k]);
-    }
-  }
-}
-
 // node index of staged element e: rows [base[j], base[j+1]) hold the nodes
 // of box row j from cumulative index c0[j] on (wrapping inside the row on a
 // periodic x axis, where the row has tot[j] nodes starting at b0[j])
@@ -158,15 +100,6 @@ __device__ __forceinline__ int staged_node(int e, int nrow, const int* base, con
   int rel = (c - b0[lo]) % tot[lo];
   if (rel < 0) rel += tot[lo];
   return b0[lo] + rel;
-}
-
-// n / d for 0 <= n < 2^22 and 1 <= d < 2^10 without an integer divide: the
-// float quotient is off by at most one, which the correction removes.
-__device__ __forceinline__ int fdiv(int n, int d, float inv_d) {
-  int q = (int)((float)n * inv_d);
-  if (q * d > n) --q;
-  else if ((q + 1) * d <= n) ++q;
-  return q;
 }
 
 template <int W>
@@ -608,7 +541,7 @@ __device__ __forceinline__ void anterp_scatter_body(
   __syncthreads();
   const float* s = reinterpret_cast<const float*>(smem4);
   const int FX = pl.fd[0], FXY = FX * pl.fd[1];
-  const float ifx = 1.0f / (float)FX, ifxy = 1.0f / (float)FXY;
+  const float ifx = recip(FX), ifxy = recip(FXY);
   for (int i = threadIdx.x; i < pl.fsize; i += T) {
     const int cz = fdiv(i, FXY, ifxy), r = i - cz * FXY, cy = fdiv(r, FX, ifx);
     const int o = cz * pl.sz + cy * pl.sy + (r - cy * FX);
@@ -737,966 +670,6 @@ template __global__ void k_anterp_sum<4>(GridParams, ScPlan, const int2*, const 
                                          const int2*, const float*, float*);
 template __global__ void k_anterp_sum_cells<1>(const CellTab*, const int32_t*, const int32_t*);
 template __global__ void k_anterp_sum_cells<4>(const CellTab*, const int32_t*, const int32_t*);
-
-// ---------------------------------------------------------------------------
-// LDS radix-2 FFT on `lines` lines of length n, lines `stride` elements apart
-// (a stride of n + 1 keeps column-wise access free of bank conflicts), input
-// in bit-reversed order; decimation in time, natural-order output. lds_fft is
-// the contiguous case.
-
-__device__ __forceinline__ void radix2(float2& a, float2& b, float2 w) {
-  const float2 t = make_float2(b.x * w.x - b.y * w.y, b.x * w.y + b.y * w.x);
-  b = make_float2(a.x - t.x, a.y - t.y);
-  a = make_float2(a.x + t.x, a.y + t.y);
-}
-
-__device__ void lds_fft_s(float2* buf, int n, int logn, int lines, int stride, const float2* tw,
-                          float sign) {
-  // radix-2 decimation in time; n = 2^logn, so every index split is a shift.
-  // Three stages s, s + 1, s + 2 are done together by one thread per 8
-  // elements (the same twelve butterflies, in registers), then a pair, then a
-  // single stage as needed, so every pass costs one LDS round trip and one
-  // barrier.
-  int s = 1;
-  for (; s + 2 <= logn; s += 3) {
-    const int ls = s - 1;  // log2(h), h the half of stage s
-    const int h = 1 << ls;
-    const int total = lines << (logn - 3);
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int line = idx >> (logn - 3);
-      const int j = idx & ((1 << (logn - 3)) - 1);
-      const int k = j & (h - 1);
-      const int i0 = line * stride + ((j >> ls) << (ls + 3)) + k;
-      float2 w1 = tw[k << (logn - s)];
-      float2 w2 = tw[k << (logn - s - 1)], w3 = tw[(k + h) << (logn - s - 1)];
-      float2 w4 = tw[k << (logn - s - 2)], w5 = tw[(k + h) << (logn - s - 2)];
-      float2 w6 = tw[(k + 2 * h) << (logn - s - 2)], w7 = tw[(k + 3 * h) << (logn - s - 2)];
-      w1.y *= sign;
-      w2.y *= sign;
-      w3.y *= sign;
-      w4.y *= sign;
-      w5.y *= sign;
-      w6.y *= sign;
-      w7.y *= sign;
-      float2 a[8];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) a[m] = buf[i0 + m * h];
-      radix2(a[0], a[1], w1);
-      radix2(a[2], a[3], w1);
-      radix2(a[4], a[5], w1);
-      radix2(a[6], a[7], w1);
-      radix2(a[0], a[2], w2);
-      radix2(a[1], a[3], w3);
-      radix2(a[4], a[6], w2);
-      radix2(a[5], a[7], w3);
-      radix2(a[0], a[4], w4);
-      radix2(a[1], a[5], w5);
-      radix2(a[2], a[6], w6);
-      radix2(a[3], a[7], w7);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) buf[i0 + m * h] = a[m];
-    }
-    __syncthreads();
-  }
-  for (; s + 1 <= logn; s += 2) {
-    const int ls = s - 1;  // log2(h), h the half of stage s
-    const int h = 1 << ls;
-    const int total = lines << (logn - 2);
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int line = idx >> (logn - 2);
-      const int j = idx & ((1 << (logn - 2)) - 1);
-      const int k = j & (h - 1);
-      const int i0 = line * stride + ((j >> ls) << (ls + 2)) + k;
-      float2 w1 = tw[k << (logn - s)];
-      float2 w2 = tw[k << (logn - s - 1)];
-      float2 w3 = tw[(k + h) << (logn - s - 1)];
-      w1.y *= sign;
-      w2.y *= sign;
-      w3.y *= sign;
-      float2 a0 = buf[i0], a1 = buf[i0 + h], a2 = buf[i0 + 2 * h], a3 = buf[i0 + 3 * h];
-      radix2(a0, a1, w1);
-      radix2(a2, a3, w1);
-      radix2(a0, a2, w2);
-      radix2(a1, a3, w3);
-      buf[i0] = a0;
-      buf[i0 + h] = a1;
-      buf[i0 + 2 * h] = a2;
-      buf[i0 + 3 * h] = a3;
-    }
-    __syncthreads();
-  }
-  if (s == logn) {  // a last single stage
-    const int ls = s - 1;
-    const int half = 1 << ls;
-    const int lh = logn - 1;
-    const int total = lines << lh;
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int line = idx >> lh;
-      const int j = idx & ((1 << lh) - 1);
-      const int k = j & (half - 1);
-      const int i0 = line * stride + ((j >> ls) << (ls + 1)) + k;
-      float2 w = tw[k];  // tw step 1 in the last stage
-      w.y *= sign;
-      float2 a = buf[i0], b = buf[i0 + half];
-      radix2(a, b, w);
-      buf[i0] = a;
-      buf[i0 + half] = b;
-    }
-    __syncthreads();
-  }
-}
-
-__device__ void lds_fft(float2* buf, int n, int logn, int lines, const float2* tw, float sign) {
-  lds_fft_s(buf, n, logn, lines, n, tw, sign);
-}
-
-__device__ __forceinline__ int bitrev(int i, int logn) { return (int)(__brev((unsigned)i) >> (32 - logn)); }
-
-// R2C along x: pairs of real rows (y, y+1) of plane z form one complex line.
-// grid [Nz][Ny][Nx] real -> spec [Nz][My][Hx] complex (rows y < Ny written).
-__device__ __forceinline__ void r2c_x_body(GridParams g, const float* __restrict__ Q,
-                                               float2* __restrict__ spec, const float2* __restrict__ twx,
-                                               int lines_per_block, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], logM = g.logM[0], Hx = Mx / 2 + 1;
-  float2* tw = sh;
-  float2* buf = sh + Mx / 2;
-  for (int i = threadIdx.x; i < Mx / 2; i += blockDim.x) tw[i] = twx[i];
-  const int pairs = (g.N[1] + 1) / 2;
-  const int64_t total_lines = (int64_t)pairs * g.N[2];
-  const int64_t l0 = (int64_t)blk * lines_per_block;
-  int nl = (int)((total_lines - l0) < lines_per_block ? (total_lines - l0) : lines_per_block);
-  for (int idx = threadIdx.x; idx < nl * Mx; idx += blockDim.x) {
-    int li = idx / Mx, x = idx - li * Mx;
-    int64_t L = l0 + li;
-    int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    float re = 0.f, im = 0.f;
-    if (x < g.N[0]) {
-      re = grid_load(Q, ((int64_t)z * g.N[1] + y) * g.N[0] + x, g);
-      if (y + 1 < g.N[1]) im = grid_load(Q, ((int64_t)z * g.N[1] + y + 1) * g.N[0] + x, g);
-    }
-    buf[li * Mx + bitrev(x, logM)] = make_float2(re, im);
-  }
-  __syncthreads();
-  lds_fft(buf, Mx, logM, nl, tw, 1.0f);
-  for (int idx = threadIdx.x; idx < nl * Hx; idx += blockDim.x) {
-    int li = idx / Hx, k = idx - li * Hx;
-    int64_t L = l0 + li;
-    int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    float2 a = buf[li * Mx + k];
-    float2 b = buf[li * Mx + ((Mx - k) & (Mx - 1))];
-    // X_y = (Z[k] + conj Z[-k]) / 2, X_{y+1} = (Z[k] - conj Z[-k]) / (2i)
-    float2 x0 = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
-    float2 x1 = make_float2(0.5f * (a.y + b.y), -0.5f * (a.x - b.x));
-    spec[((int64_t)z * g.M[1] + y) * Hx + k] = x0;
-    if (y + 1 < g.N[1]) spec[((int64_t)z * g.M[1] + y + 1) * Hx + k] = x1;
-  }
-}
-
-__global__ void __launch_bounds__(256) k_r2c_x(GridParams g, const float* __restrict__ Q,
-                                               float2* __restrict__ spec, const float2* __restrict__ twx,
-                                               int lines_per_block) {
-  r2c_x_body(g, Q, spec, twx, lines_per_block, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_r2c_x_cells(const CellTab* __restrict__ tab,
-                                                     const int32_t* __restrict__ bcell,
-                                                     const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  r2c_x_body(t.g, t.grid, t.spec, t.twx, t.lpb, blockIdx.x - boff[c]);
-}
-
-// Forward transform of one z-plane held whole in LDS: real rows y < Ny are
-// paired into complex lines (R2C along x), separated into the half spectrum
-// kx < Hx, transposed into columns (stride My + 1) and transformed along y.
-// Q[z][y][x] -> spec[z][ky][kx] for all ky < My. nsplit workgroups share a
-// plane: each does the x pass and the y pass of its share of the columns.
-__device__ __forceinline__ void fft_xy_fwd_body(GridParams g, const float* __restrict__ Q,
-                                                     float2* __restrict__ spec,
-                                                     const float2* __restrict__ twx,
-                                                     const float2* __restrict__ twy,
-                                                     int nsplit, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], My = g.M[1], Hx = Mx / 2 + 1, lx = g.logM[0], ly = g.logM[1];
-  const int Nx = g.N[0], Ny = g.N[1], pairs = (Ny + 1) / 2, cs = My + 1;
-  float2* tx = sh;
-  float2* ty = tx + Mx / 2;
-  float2* A = ty + My / 2;        // [pairs][Mx]
-  float2* C = A + pairs * Mx;     // [Hx][My + 1]
-  const int z = blk / nsplit, part = blk - z * nsplit;
-  const int kw = (Hx + nsplit - 1) / nsplit, k0 = part * kw, nk = min(Hx, k0 + kw) - k0;
-  const float invnk = 1.0f / (float)nk;
-  for (int i = threadIdx.x; i < Mx / 2; i += blockDim.x) tx[i] = twx[i];
-  for (int i = threadIdx.x; i < My / 2; i += blockDim.x) ty[i] = twy[i];
-  const int64_t qz = (int64_t)z * Ny * Nx;
-  const float invHx = 1.0f / (float)Hx;
-  batched<8>(
-      pairs * Mx,
-      [&](int idx) {
-        const int li = idx >> lx, x = idx & (Mx - 1), y = 2 * li;
-        float2 v = make_float2(0.f, 0.f);
-        if (x < Nx) {
-          v.x = grid_load(Q, qz + (int64_t)y * Nx + x, g);
-          if (y + 1 < Ny) v.y = grid_load(Q, qz + (int64_t)(y + 1) * Nx + x, g);
-        }
-        return v;
-      },
-      [&](int idx, float2 v) {
-        const int li = idx >> lx, x = idx & (Mx - 1);
-        A[li * Mx + bitrev(x, lx)] = v;
-      });
-  // rows Ny..My-1 of the columns are the zero padding
-  for (int idx = threadIdx.x; idx < nk * (My - 2 * pairs); idx += blockDim.x) {
-    const int yq = fdiv(idx, nk, invnk);
-    const int k = k0 + idx - yq * nk, y = 2 * pairs + yq;
-    C[k * cs + bitrev(y, ly)] = make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  lds_fft_s(A, Mx, lx, pairs, Mx, tx, 1.0f);
-  for (int idx = threadIdx.x; idx < pairs * nk; idx += blockDim.x) {
-    const int li = fdiv(idx, nk, invnk), k = k0 + idx - li * nk, y = 2 * li;
-    const float2 a = A[li * Mx + k];
-    const float2 b = A[li * Mx + ((Mx - k) & (Mx - 1))];
-    // X_y = (Z[k] + conj Z[-k]) / 2, X_{y+1} = (Z[k] - conj Z[-k]) / (2i)
-    C[k * cs + bitrev(y, ly)] = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
-    C[k * cs + bitrev(y + 1, ly)] =
-        y + 1 < Ny ? make_float2(0.5f * (a.y + b.y), -0.5f * (a.x - b.x)) : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  lds_fft_s(C + k0 * cs, My, ly, nk, cs, ty, 1.0f);
-  float2* Sz = spec + (int64_t)z * My * Hx;
-  for (int idx = threadIdx.x; idx < My * nk; idx += blockDim.x) {
-    const int ky = fdiv(idx, nk, invnk), k = k0 + idx - ky * nk;
-    Sz[ky * Hx + k] = C[k * cs + ky];
-  }
-}
-
-__global__ void __launch_bounds__(1024) k_fft_xy_fwd(GridParams g, const float* __restrict__ Q,
-                                                     float2* __restrict__ spec,
-                                                     const float2* __restrict__ twx,
-                                                     const float2* __restrict__ twy,
-                                                     int nsplit) {
-  fft_xy_fwd_body(g, Q, spec, twx, twy, nsplit, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(1024) k_fft_xy_fwd_cells(const CellTab* __restrict__ tab,
-                                                           const int32_t* __restrict__ bcell,
-                                                           const int32_t* __restrict__ boff,
-                                                           int nsplit) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_xy_fwd_body(t.g, t.grid, t.spec, t.twx, t.twy, nsplit, blockIdx.x - boff[c]);
-}
-
-// Inverse of k_fft_xy_fwd for one z-plane: inverse FFT along y of the half
-// spectrum columns, rows y < Ny paired into complex lines with Hermitian
-// extension (C2R along x), inverse FFT along x. spec[z] -> U[z][y][x].
-// nsplit workgroups share a plane: each does the y pass and the x pass of
-// its share of the row pairs.
-__device__ __forceinline__ void fft_yx_inv_body(GridParams g, const float2* __restrict__ spec,
-                                                     float* __restrict__ U,
-                                                     const float2* __restrict__ twx,
-                                                     const float2* __restrict__ twy,
-                                                     int nsplit, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], My = g.M[1], Hx = Mx / 2 + 1, lx = g.logM[0], ly = g.logM[1];
-  const int Nx = g.N[0], Ny = g.N[1], pairs = (Ny + 1) / 2, cs = My + 1;
-  float2* tx = sh;
-  float2* ty = tx + Mx / 2;
-  float2* A = ty + My / 2;
-  float2* C = A + pairs * Mx;
-  const int z = blk / nsplit, part = blk - z * nsplit;
-  const int lw = (pairs + nsplit - 1) / nsplit, l0 = part * lw, nl = min(pairs, l0 + lw) - l0;
-  for (int i = threadIdx.x; i < Mx / 2; i += blockDim.x) tx[i] = twx[i];
-  for (int i = threadIdx.x; i < My / 2; i += blockDim.x) ty[i] = twy[i];
-  const float2* Sz = spec + (int64_t)z * My * Hx;
-  const float invHx = 1.0f / (float)Hx;
-  batched<8>(
-      My * Hx, [&](int idx) { return Sz[idx]; },
-      [&](int idx, float2 v) {
-        const int ky = fdiv(idx, Hx, invHx), k = idx - ky * Hx;
-        C[k * cs + bitrev(ky, ly)] = v;
-      });
-  __syncthreads();
-  lds_fft_s(C, My, ly, Hx, cs, ty, -1.0f);
-  for (int idx = threadIdx.x; idx < nl * Mx; idx += blockDim.x) {
-    const int li = l0 + (idx >> lx), k = idx & (Mx - 1), y = 2 * li;
-    const int kk = k <= Mx / 2 ? k : Mx - k;
-    float2 a = C[kk * cs + y];
-    float2 b = y + 1 < Ny ? C[kk * cs + y + 1] : make_float2(0.f, 0.f);
-    if (k > Mx / 2) {
-      a.y = -a.y;
-      b.y = -b.y;
-    }
-    // Z = X_y + i X_{y+1}
-    A[li * Mx + bitrev(k, lx)] = make_float2(a.x - b.y, a.y + b.x);
-  }
-  __syncthreads();
-  lds_fft_s(A + l0 * Mx, Mx, lx, nl, Mx, tx, -1.0f);
-  const int64_t uzo = (int64_t)z * Ny * Nx;
-  const float invNx = 1.0f / (float)Nx;
-  for (int idx = threadIdx.x; idx < nl * Nx; idx += blockDim.x) {
-    const int li = l0 + fdiv(idx, Nx, invNx), x = idx - (li - l0) * Nx, y = 2 * li;
-    const float2 v = A[li * Mx + x];
-    grid_store(U, uzo + (int64_t)y * Nx + x, v.x, g);
-    if (y + 1 < Ny) grid_store(U, uzo + (int64_t)(y + 1) * Nx + x, v.y, g);
-  }
-}
-
-__global__ void __launch_bounds__(1024) k_fft_yx_inv(GridParams g, const float2* __restrict__ spec,
-                                                     float* __restrict__ U,
-                                                     const float2* __restrict__ twx,
-                                                     const float2* __restrict__ twy,
-                                                     int nsplit) {
-  fft_yx_inv_body(g, spec, U, twx, twy, nsplit, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(1024) k_fft_yx_inv_cells(const CellTab* __restrict__ tab,
-                                                           const int32_t* __restrict__ bcell,
-                                                           const int32_t* __restrict__ boff,
-                                                           int nsplit) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_yx_inv_body(t.g, t.spec, t.grid, t.twx, t.twy, nsplit, blockIdx.x - boff[c]);
-}
-
-// FFT along y for lines (z < Nz, kx): groups of B consecutive kx per block.
-// Forward: input rows y < Ny (others zero), all My outputs written.
-// Inverse: all My inputs, outputs y < n_out written.
-__device__ __forceinline__ void fft_y_body(GridParams g, float2* __restrict__ spec,
-                                               const float2* __restrict__ twy, int B, int inverse,
-                                               int n_in, int n_out, const int blk) {
-  extern __shared__ float2 sh[];
-  const int My = g.M[1], logM = g.logM[1], Hx = g.M[0] / 2 + 1;
-  float2* tw = sh;
-  float2* buf = sh + My / 2;
-  for (int i = threadIdx.x; i < My / 2; i += blockDim.x) tw[i] = twy[i];
-  const int groups_per_plane = (Hx + B - 1) / B;
-  const int z = blk / groups_per_plane;
-  const int kx0 = (blk - z * groups_per_plane) * B;
-  const int nb = (Hx - kx0) < B ? (Hx - kx0) : B;
-  for (int idx = threadIdx.x; idx < nb * My; idx += blockDim.x) {
-    int y = idx / nb, li = idx - y * nb;
-    float2 v = make_float2(0.f, 0.f);
-    if (y < n_in) v = spec[((int64_t)z * My + y) * Hx + kx0 + li];
-    buf[li * My + bitrev(y, logM)] = v;
-  }
-  __syncthreads();
-  lds_fft(buf, My, logM, nb, tw, inverse ? -1.0f : 1.0f);
-  for (int idx = threadIdx.x; idx < nb * n_out; idx += blockDim.x) {
-    int y = idx / nb, li = idx - y * nb;
-    spec[((int64_t)z * My + y) * Hx + kx0 + li] = buf[li * My + y];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_fft_y(GridParams g, float2* __restrict__ spec,
-                                               const float2* __restrict__ twy, int B, int inverse,
-                                               int n_in, int n_out) {
-  fft_y_body(g, spec, twy, B, inverse, n_in, n_out, blockIdx.x);
-}
-
-// inverse = 0: rows y < N_y in, all M_y out; inverse = 1: all in, y < N_y out
-__global__ void __launch_bounds__(256) k_fft_y_cells(const CellTab* __restrict__ tab,
-                                                     const int32_t* __restrict__ bcell,
-                                                     const int32_t* __restrict__ boff,
-                                                     int inverse) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  const int ny = t.g.N[1], my = t.g.M[1];
-  fft_y_body(t.g, t.spec, t.twy, t.by, inverse, inverse ? my : ny, inverse ? ny : my,
-             blockIdx.x - boff[c]);
-}
-
-// FFT along z of lines c = ky*Hx + kx (B consecutive per block), multiply by
-// the real spectrum khat[kz][c], inverse FFT, write z < Nz.
-__device__ __forceinline__ void fft_z_mul_body(GridParams g, float2* __restrict__ spec,
-                                                   const float* __restrict__ khat,
-                                                   const float2* __restrict__ twz, int B, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mz = g.M[2], logM = g.logM[2], Hx = g.M[0] / 2 + 1;
-  const int64_t plane = (int64_t)g.M[1] * Hx;
-  float2* tw = sh;
-  float2* buf = sh + Mz / 2;
-  for (int i = threadIdx.x; i < Mz / 2; i += blockDim.x) tw[i] = twz[i];
-  const int64_t c0 = (int64_t)blk * B;
-  const int nb = (int)((plane - c0) < B ? (plane - c0) : B);
-  batched<8>(
-      nb * Mz,
-      [&](int idx) {
-        const int z = idx / nb, li = idx - z * nb;
-        return z < g.N[2] ? spec[(int64_t)z * plane + c0 + li] : make_float2(0.f, 0.f);
-      },
-      [&](int idx, float2 v) {
-        const int z = idx / nb, li = idx - z * nb;
-        buf[li * Mz + bitrev(z, logM)] = v;
-      });
-  __syncthreads();
-  lds_fft(buf, Mz, logM, nb, tw, 1.0f);
-  // multiply and scatter back in bit-reversed order for the inverse
-  batched<8>(
-      nb * Mz,
-      [&](int idx) {
-        const int kz = idx / nb, li = idx - kz * nb;
-        return khat[(int64_t)kz * plane + c0 + li];
-      },
-      [&](int idx, float kk) {
-        const int kz = idx / nb, li = idx - kz * nb;
-        const float2 v = buf[li * Mz + kz];
-        buf[li * Mz + kz] = make_float2(v.x * kk, v.y * kk);  // same element, same thread
-      });
-  __syncthreads();
-  // bit-reverse permutation in place
-  for (int idx = threadIdx.x; idx < nb * Mz; idx += blockDim.x) {
-    int i = idx / nb, li = idx - i * nb;
-    int j = bitrev(i, logM);
-    if (i < j) {
-      float2 a = buf[li * Mz + i];
-      buf[li * Mz + i] = buf[li * Mz + j];
-      buf[li * Mz + j] = a;
-    }
-  }
-  __syncthreads();
-  lds_fft(buf, Mz, logM, nb, tw, -1.0f);
-  for (int idx = threadIdx.x; idx < nb * g.N[2]; idx += blockDim.x) {
-    int z = idx / nb, li = idx - z * nb;
-    spec[(int64_t)z * plane + c0 + li] = buf[li * Mz + z];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_fft_z_mul(GridParams g, float2* __restrict__ spec,
-                                                   const float* __restrict__ khat,
-                                                   const float2* __restrict__ twz, int B) {
-  fft_z_mul_body(g, spec, khat, twz, B, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_fft_z_mul_cells(const CellTab* __restrict__ tab,
-                                                         const int32_t* __restrict__ bcell,
-                                                         const int32_t* __restrict__ boff,
-                                                         int B) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_z_mul_body(t.g, t.spec, t.khat, t.twz, B, blockIdx.x - boff[c]);
-}
-
-// C2R along x: rows (y, y+1) of plane z from their half spectra -> U[z][y][x].
-__device__ __forceinline__ void c2r_x_body(GridParams g, const float2* __restrict__ spec,
-                                               float* __restrict__ U, const float2* __restrict__ twx,
-                                               int lines_per_block, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], logM = g.logM[0], Hx = Mx / 2 + 1;
-  float2* tw = sh;
-  float2* buf = sh + Mx / 2;
-  for (int i = threadIdx.x; i < Mx / 2; i += blockDim.x) tw[i] = twx[i];
-  const int pairs = (g.N[1] + 1) / 2;
-  const int64_t total_lines = (int64_t)pairs * g.N[2];
-  const int64_t l0 = (int64_t)blk * lines_per_block;
-  int nl = (int)((total_lines - l0) < lines_per_block ? (total_lines - l0) : lines_per_block);
-  for (int idx = threadIdx.x; idx < nl * Mx; idx += blockDim.x) {
-    int li = idx / Mx, k = idx - li * Mx;
-    int64_t L = l0 + li;
-    int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    int kk = k <= Mx / 2 ? k : Mx - k;
-    float2 a = spec[((int64_t)z * g.M[1] + y) * Hx + kk];
-    float2 b = make_float2(0.f, 0.f);
-    if (y + 1 < g.N[1]) b = spec[((int64_t)z * g.M[1] + y + 1) * Hx + kk];
-    if (k > Mx / 2) {
-      a.y = -a.y;
-      b.y = -b.y;
-    }
-    // Z = X_y + i X_{y+1}
-    buf[li * Mx + bitrev(k, logM)] = make_float2(a.x - b.y, a.y + b.x);
-  }
-  __syncthreads();
-  lds_fft(buf, Mx, logM, nl, tw, -1.0f);
-  for (int idx = threadIdx.x; idx < nl * g.N[0]; idx += blockDim.x) {
-    int li = idx / g.N[0], x = idx - li * g.N[0];
-    int64_t L = l0 + li;
-    int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    float2 v = buf[li * Mx + x];
-    grid_store(U, ((int64_t)z * g.N[1] + y) * g.N[0] + x, v.x, g);
-    if (y + 1 < g.N[1]) grid_store(U, ((int64_t)z * g.N[1] + y + 1) * g.N[0] + x, v.y, g);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_c2r_x(GridParams g, const float2* __restrict__ spec,
-                                               float* __restrict__ U, const float2* __restrict__ twx,
-                                               int lines_per_block) {
-  c2r_x_body(g, spec, U, twx, lines_per_block, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_c2r_x_cells(const CellTab* __restrict__ tab,
-                                                     const int32_t* __restrict__ bcell,
-                                                     const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  c2r_x_body(t.g, t.spec, t.grid, t.twx, t.lpb, blockIdx.x - boff[c]);
-}
-
-// ---------------------------------------------------------------------------
-// Mixed-radix FFT passes (extents that are products of 2, 3, 5 and 7):
-// Stockham autosort in LDS, natural order in and out, ping-pong between two
-// buffers, radices 4, 2, 3, 5, 7 taken in that order of preference. Pass
-// with Ns = product of the radices done so far and radix R: element j of
-// the n/R groups reads a_q = src[j + q n/R], q < R, multiplies a_q by the
-// twiddle w^(q k) with k = j mod Ns and w = exp(-2 pi i / (Ns R)) (conjugated
-// for the inverse), forms the R-point DFT b_p = sum_q a_q exp(-2 pi i q p / R)
-// and writes b_p to dst[(j / Ns) Ns R + k + p Ns]. tw[t] = exp(-2 pi i t / n).
-
-__device__ __forceinline__ float2 cmulf(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// R-point DFT in place, sign +1 forward (exp(-i ...)), -1 inverse
-template <int R>
-__device__ __forceinline__ void dft_small(float2* v, float sign) {
-  // cos and sin of 2 pi m / R, m < R
-  float c[R], sn[R];
-  if constexpr (R == 2) {
-    c[0] = 1.f; sn[0] = 0.f; c[1] = -1.f; sn[1] = 0.f;
-  } else if constexpr (R == 3) {
-    c[0] = 1.f; sn[0] = 0.f;
-    c[1] = -0.5f; sn[1] = 0.86602540378443865f;
-    c[2] = -0.5f; sn[2] = -0.86602540378443865f;
-  } else if constexpr (R == 4) {
-    c[0] = 1.f; sn[0] = 0.f; c[1] = 0.f; sn[1] = 1.f;
-    c[2] = -1.f; sn[2] = 0.f; c[3] = 0.f; sn[3] = -1.f;
-  } else if constexpr (R == 5) {
-    c[0] = 1.f; sn[0] = 0.f;
-    c[1] = 0.30901699437494742f; sn[1] = 0.95105651629515357f;
-    c[2] = -0.80901699437494742f; sn[2] = 0.58778525229247313f;
-    c[3] = -0.80901699437494742f; sn[3] = -0.58778525229247313f;
-    c[4] = 0.30901699437494742f; sn[4] = -0.95105651629515357f;
-  } else {
-    c[0] = 1.f; sn[0] = 0.f;
-    c[1] = 0.62348980185873353f; sn[1] = 0.78183148246802981f;
-    c[2] = -0.22252093395631440f; sn[2] = 0.97492791218182361f;
-    c[3] = -0.90096886790241913f; sn[3] = 0.43388373911755812f;
-    c[4] = -0.90096886790241913f; sn[4] = -0.43388373911755812f;
-    c[5] = -0.22252093395631440f; sn[5] = -0.97492791218182361f;
-    c[6] = 0.62348980185873353f; sn[6] = -0.78183148246802981f;
-  }
-  float2 out[R];
-#pragma unroll
-  for (int p = 0; p < R; ++p) {
-    float2 acc = v[0];
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-      const int m = (q * p) % R;
-      // exp(-i sign 2 pi m / R)
-      const float2 w = make_float2(c[m], -sign * sn[m]);
-      const float2 t = cmulf(v[q], w);
-      acc.x += t.x;
-      acc.y += t.y;
-    }
-    out[p] = acc;
-  }
-#pragma unroll
-  for (int p = 0; p < R; ++p) v[p] = out[p];
-}
-
-template <int R>
-__device__ __forceinline__ void stockham_pass(const float2* src, float2* dst, int n, int Ns,
-                                              int lines, int ld, const float2* tw, float sign) {
-  const int nR = n / R, step = n / (Ns * R);
-  const int total = lines * nR;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int line = idx / nR, j = idx - line * nR;
-    const float2* s = src + line * ld;
-    float2* d = dst + line * ld;
-    const int k = j % Ns;
-    float2 v[R];
-#pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = s[j + q * nR];
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-      float2 w = tw[q * k * step];  // q k step < n
-      w.y *= sign;
-      v[q] = cmulf(v[q], w);
-    }
-    dft_small<R>(v, sign);
-    const int base = (j / Ns) * Ns * R + k;
-#pragma unroll
-    for (int p = 0; p < R; ++p) d[base + p * Ns] = v[p];
-  }
-}
-
-// lines of length n, line stride ld, in a; returns the buffer (a or b)
-// holding the transform
-__device__ float2* lds_fft_mr(float2* a, float2* b, int n, int lines, int ld, const float2* tw,
-                              float sign) {
-  int Ns = 1;
-  while (Ns < n) {
-    const int rem = n / Ns;
-    if (rem % 4 == 0) {
-      stockham_pass<4>(a, b, n, Ns, lines, ld, tw, sign);
-      Ns *= 4;
-    } else if (rem % 2 == 0) {
-      stockham_pass<2>(a, b, n, Ns, lines, ld, tw, sign);
-      Ns *= 2;
-    } else if (rem % 3 == 0) {
-      stockham_pass<3>(a, b, n, Ns, lines, ld, tw, sign);
-      Ns *= 3;
-    } else if (rem % 5 == 0) {
-      stockham_pass<5>(a, b, n, Ns, lines, ld, tw, sign);
-      Ns *= 5;
-    } else {
-      stockham_pass<7>(a, b, n, Ns, lines, ld, tw, sign);
-      Ns *= 7;
-    }
-    __syncthreads();
-    float2* t = a;
-    a = b;
-    b = t;
-  }
-  return a;
-}
-
-// Whole z-plane x and y passes, mixed radix (as k_fft_xy_fwd / k_fft_yx_inv
-// for powers of two): one workgroup per plane; LDS: the two twiddle tables
-// and two buffers of max(pairs Mx, Hx My) values. Forward: the pairs of real
-// rows as complex lines along x, their half spectra unpacked into the
-// columns of the plane, the columns along y. Inverse: the columns along y,
-// the pairs of rows rebuilt as complex lines with the Hermitian half, the
-// lines along x.
-__device__ __forceinline__ void fft_xy_fwd_mr_body(GridParams g, const float* __restrict__ Q,
-                                                   float2* __restrict__ spec,
-                                                   const float2* __restrict__ twfx,
-                                                   const float2* __restrict__ twfy,
-                                                   const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], My = g.M[1], Hx = Mx / 2 + 1, Ny = g.N[1];
-  const int pairs = (Ny + 1) / 2;
-  const int cap = max(pairs * Mx, Hx * My);
-  float2* twx = sh;
-  float2* twy = twx + Mx;
-  float2* A = twy + My;
-  float2* Bf = A + cap;
-  for (int i = threadIdx.x; i < Mx; i += blockDim.x) twx[i] = twfx[i];
-  for (int i = threadIdx.x; i < My; i += blockDim.x) twy[i] = twfy[i];
-  const int z = blk;
-  for (int idx = threadIdx.x; idx < pairs * Mx; idx += blockDim.x) {
-    const int l = idx / Mx, x = idx - l * Mx, y = 2 * l;
-    float re = 0.f, im = 0.f;
-    if (x < g.N[0]) {
-      re = grid_load(Q, ((int64_t)z * Ny + y) * g.N[0] + x, g);
-      if (y + 1 < Ny) im = grid_load(Q, ((int64_t)z * Ny + y + 1) * g.N[0] + x, g);
-    }
-    A[idx] = make_float2(re, im);
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(A, Bf, Mx, pairs, Mx, twx, 1.0f);
-  float2* C = R == A ? Bf : A;
-  float2* D = R == A ? A : Bf;
-  // X_y = (Z[k] + conj Z[-k]) / 2, X_{y+1} = (Z[k] - conj Z[-k]) / (2i), as
-  // the columns C[kx My + y], zero past the rows
-  for (int idx = threadIdx.x; idx < Hx * My; idx += blockDim.x) {
-    const int kx = idx / My, y = idx - kx * My;
-    float2 v = make_float2(0.f, 0.f);
-    if (y < Ny) {
-      const int l = y >> 1;
-      const float2 a = R[l * Mx + kx];
-      const float2 b = R[l * Mx + (kx == 0 ? 0 : Mx - kx)];
-      v = (y & 1) ? make_float2(0.5f * (a.y + b.y), -0.5f * (a.x - b.x))
-                  : make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
-    }
-    C[idx] = v;
-  }
-  __syncthreads();
-  const float2* S = lds_fft_mr(C, D, My, Hx, My, twy, 1.0f);
-  for (int idx = threadIdx.x; idx < My * Hx; idx += blockDim.x) {
-    const int ky = idx / Hx, kx = idx - ky * Hx;
-    spec[((int64_t)z * My + ky) * Hx + kx] = S[kx * My + ky];
-  }
-}
-
-__device__ __forceinline__ void fft_yx_inv_mr_body(GridParams g, const float2* __restrict__ spec,
-                                                   float* __restrict__ U,
-                                                   const float2* __restrict__ twfx,
-                                                   const float2* __restrict__ twfy,
-                                                   const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], My = g.M[1], Hx = Mx / 2 + 1, Ny = g.N[1];
-  const int pairs = (Ny + 1) / 2;
-  const int cap = max(pairs * Mx, Hx * My);
-  float2* twx = sh;
-  float2* twy = twx + Mx;
-  float2* A = twy + My;
-  float2* Bf = A + cap;
-  for (int i = threadIdx.x; i < Mx; i += blockDim.x) twx[i] = twfx[i];
-  for (int i = threadIdx.x; i < My; i += blockDim.x) twy[i] = twfy[i];
-  const int z = blk;
-  for (int idx = threadIdx.x; idx < My * Hx; idx += blockDim.x) {
-    const int ky = idx / Hx, kx = idx - ky * Hx;
-    A[kx * My + ky] = spec[((int64_t)z * My + ky) * Hx + kx];
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(A, Bf, My, Hx, My, twy, -1.0f);
-  float2* L = R == A ? Bf : A;
-  float2* D = R == A ? A : Bf;
-  // Z = X_y + i X_{y+1} over the full line, X[k] = conj X[Mx - k] for k >= Hx
-  for (int idx = threadIdx.x; idx < pairs * Mx; idx += blockDim.x) {
-    const int l = idx / Mx, k = idx - l * Mx, y = 2 * l;
-    const int kk = k < Hx ? k : Mx - k;
-    float2 a = R[kk * My + y];
-    float2 b = make_float2(0.f, 0.f);
-    if (y + 1 < Ny) b = R[kk * My + y + 1];
-    if (k >= Hx) {
-      a.y = -a.y;
-      b.y = -b.y;
-    }
-    L[idx] = make_float2(a.x - b.y, a.y + b.x);
-  }
-  __syncthreads();
-  const float2* S = lds_fft_mr(L, D, Mx, pairs, Mx, twx, -1.0f);
-  for (int idx = threadIdx.x; idx < pairs * g.N[0]; idx += blockDim.x) {
-    const int l = idx / g.N[0], x = idx - l * g.N[0], y = 2 * l;
-    const float2 v = S[l * Mx + x];
-    grid_store(U, ((int64_t)z * Ny + y) * g.N[0] + x, v.x, g);
-    if (y + 1 < Ny) grid_store(U, ((int64_t)z * Ny + y + 1) * g.N[0] + x, v.y, g);
-  }
-}
-
-__global__ void __launch_bounds__(512) k_fft_xy_fwd_mr(GridParams g, const float* __restrict__ Q,
-                                                       float2* __restrict__ spec,
-                                                       const float2* __restrict__ twfx,
-                                                       const float2* __restrict__ twfy) {
-  fft_xy_fwd_mr_body(g, Q, spec, twfx, twfy, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(512) k_fft_yx_inv_mr(GridParams g,
-                                                       const float2* __restrict__ spec,
-                                                       float* __restrict__ U,
-                                                       const float2* __restrict__ twfx,
-                                                       const float2* __restrict__ twfy) {
-  fft_yx_inv_mr_body(g, spec, U, twfx, twfy, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(512) k_fft_xy_fwd_mr_cells(const CellTab* __restrict__ tab,
-                                                             const int32_t* __restrict__ bcell,
-                                                             const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_xy_fwd_mr_body(t.g, t.grid, t.spec, t.twfx, t.twfy, blockIdx.x - boff[c]);
-}
-
-__global__ void __launch_bounds__(512) k_fft_yx_inv_mr_cells(const CellTab* __restrict__ tab,
-                                                             const int32_t* __restrict__ bcell,
-                                                             const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_yx_inv_mr_body(t.g, t.spec, t.grid, t.twfx, t.twfy, blockIdx.x - boff[c]);
-}
-
-// R2C along x, mixed radix: as k_r2c_x (pairs of real rows y, y + 1 as one
-// complex line, half spectrum of each), LDS: twiddles [Mx], two line buffers.
-__device__ __forceinline__ void r2c_x_mr_body(GridParams g, const float* __restrict__ Q,
-                                              float2* __restrict__ spec,
-                                              const float2* __restrict__ twf,
-                                              int lines_per_block, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], Hx = Mx / 2 + 1;
-  float2* tw = sh;
-  float2* A = sh + Mx;
-  float2* Bf = A + lines_per_block * Mx;
-  for (int i = threadIdx.x; i < Mx; i += blockDim.x) tw[i] = twf[i];
-  const int pairs = (g.N[1] + 1) / 2;
-  const int64_t total_lines = (int64_t)pairs * g.N[2];
-  const int64_t l0 = (int64_t)blk * lines_per_block;
-  const int nl = (int)((total_lines - l0) < lines_per_block ? (total_lines - l0) : lines_per_block);
-  for (int idx = threadIdx.x; idx < nl * Mx; idx += blockDim.x) {
-    const int li = idx / Mx, x = idx - li * Mx;
-    const int64_t L = l0 + li;
-    const int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    float re = 0.f, im = 0.f;
-    if (x < g.N[0]) {
-      re = grid_load(Q, ((int64_t)z * g.N[1] + y) * g.N[0] + x, g);
-      if (y + 1 < g.N[1]) im = grid_load(Q, ((int64_t)z * g.N[1] + y + 1) * g.N[0] + x, g);
-    }
-    A[li * Mx + x] = make_float2(re, im);
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(A, Bf, Mx, nl, Mx, tw, 1.0f);
-  for (int idx = threadIdx.x; idx < nl * Hx; idx += blockDim.x) {
-    const int li = idx / Hx, k = idx - li * Hx;
-    const int64_t L = l0 + li;
-    const int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    const float2 a = R[li * Mx + k];
-    const float2 b = R[li * Mx + (k == 0 ? 0 : Mx - k)];
-    // X_y = (Z[k] + conj Z[-k]) / 2, X_{y+1} = (Z[k] - conj Z[-k]) / (2i)
-    spec[((int64_t)z * g.M[1] + y) * Hx + k] = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
-    if (y + 1 < g.N[1])
-      spec[((int64_t)z * g.M[1] + y + 1) * Hx + k] =
-          make_float2(0.5f * (a.y + b.y), -0.5f * (a.x - b.x));
-  }
-}
-
-__global__ void __launch_bounds__(256) k_r2c_x_mr(GridParams g, const float* __restrict__ Q,
-                                                  float2* __restrict__ spec,
-                                                  const float2* __restrict__ twf,
-                                                  int lines_per_block) {
-  r2c_x_mr_body(g, Q, spec, twf, lines_per_block, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_r2c_x_mr_cells(const CellTab* __restrict__ tab,
-                                                        const int32_t* __restrict__ bcell,
-                                                        const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  r2c_x_mr_body(t.g, t.grid, t.spec, t.twfx, t.lpb, blockIdx.x - boff[c]);
-}
-
-// FFT along y, mixed radix, as k_fft_y (B columns kx per block)
-__device__ __forceinline__ void fft_y_mr_body(GridParams g, float2* __restrict__ spec,
-                                              const float2* __restrict__ twf, int B, int inverse,
-                                              int n_in, int n_out, const int blk) {
-  extern __shared__ float2 sh[];
-  const int My = g.M[1], Hx = g.M[0] / 2 + 1;
-  float2* tw = sh;
-  float2* A = sh + My;
-  float2* Bf = A + B * My;
-  for (int i = threadIdx.x; i < My; i += blockDim.x) tw[i] = twf[i];
-  const int groups_per_plane = (Hx + B - 1) / B;
-  const int z = blk / groups_per_plane;
-  const int kx0 = (blk - z * groups_per_plane) * B;
-  const int nb = (Hx - kx0) < B ? (Hx - kx0) : B;
-  for (int idx = threadIdx.x; idx < nb * My; idx += blockDim.x) {
-    const int y = idx / nb, li = idx - y * nb;
-    float2 v = make_float2(0.f, 0.f);
-    if (y < n_in) v = spec[((int64_t)z * My + y) * Hx + kx0 + li];
-    A[li * My + y] = v;
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(A, Bf, My, nb, My, tw, inverse ? -1.0f : 1.0f);
-  for (int idx = threadIdx.x; idx < nb * n_out; idx += blockDim.x) {
-    const int y = idx / nb, li = idx - y * nb;
-    spec[((int64_t)z * My + y) * Hx + kx0 + li] = R[li * My + y];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_fft_y_mr(GridParams g, float2* __restrict__ spec,
-                                                  const float2* __restrict__ twf, int B,
-                                                  int inverse, int n_in, int n_out) {
-  fft_y_mr_body(g, spec, twf, B, inverse, n_in, n_out, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_fft_y_mr_cells(const CellTab* __restrict__ tab,
-                                                        const int32_t* __restrict__ bcell,
-                                                        const int32_t* __restrict__ boff,
-                                                        int inverse) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  const int ny = t.g.N[1], my = t.g.M[1];
-  fft_y_mr_body(t.g, t.spec, t.twfy, t.by, inverse, inverse ? my : ny, inverse ? ny : my,
-                blockIdx.x - boff[c]);
-}
-
-// FFT along z, K multiply, inverse FFT along z, mixed radix, as k_fft_z_mul
-__device__ __forceinline__ void fft_z_mul_mr_body(GridParams g, float2* __restrict__ spec,
-                                                  const float* __restrict__ khat,
-                                                  const float2* __restrict__ twf, int B,
-                                                  const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mz = g.M[2], Hx = g.M[0] / 2 + 1;
-  const int64_t plane = (int64_t)g.M[1] * Hx;
-  float2* tw = sh;
-  float2* A = sh + Mz;
-  float2* Bf = A + B * Mz;
-  for (int i = threadIdx.x; i < Mz; i += blockDim.x) tw[i] = twf[i];
-  const int64_t c0 = (int64_t)blk * B;
-  const int nb = (int)((plane - c0) < B ? (plane - c0) : B);
-  for (int idx = threadIdx.x; idx < nb * Mz; idx += blockDim.x) {
-    const int z = idx / nb, li = idx - z * nb;
-    A[li * Mz + z] = z < g.N[2] ? spec[(int64_t)z * plane + c0 + li] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  float2* F = lds_fft_mr(A, Bf, Mz, nb, Mz, tw, 1.0f);
-  float2* other = F == A ? Bf : A;
-  for (int idx = threadIdx.x; idx < nb * Mz; idx += blockDim.x) {
-    const int kz = idx / nb, li = idx - kz * nb;
-    const float kk = khat[(int64_t)kz * plane + c0 + li];
-    const float2 v = F[li * Mz + kz];
-    F[li * Mz + kz] = make_float2(v.x * kk, v.y * kk);  // same element, same thread
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(F, other, Mz, nb, Mz, tw, -1.0f);
-  for (int idx = threadIdx.x; idx < nb * g.N[2]; idx += blockDim.x) {
-    const int z = idx / nb, li = idx - z * nb;
-    spec[(int64_t)z * plane + c0 + li] = R[li * Mz + z];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_fft_z_mul_mr(GridParams g, float2* __restrict__ spec,
-                                                      const float* __restrict__ khat,
-                                                      const float2* __restrict__ twf, int B) {
-  fft_z_mul_mr_body(g, spec, khat, twf, B, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_fft_z_mul_mr_cells(const CellTab* __restrict__ tab,
-                                                            const int32_t* __restrict__ bcell,
-                                                            const int32_t* __restrict__ boff,
-                                                            int B) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  fft_z_mul_mr_body(t.g, t.spec, t.khat, t.twfz, B, blockIdx.x - boff[c]);
-}
-
-// C2R along x, mixed radix, as k_c2r_x
-__device__ __forceinline__ void c2r_x_mr_body(GridParams g, const float2* __restrict__ spec,
-                                              float* __restrict__ U,
-                                              const float2* __restrict__ twf,
-                                              int lines_per_block, const int blk) {
-  extern __shared__ float2 sh[];
-  const int Mx = g.M[0], Hx = Mx / 2 + 1;
-  float2* tw = sh;
-  float2* A = sh + Mx;
-  float2* Bf = A + lines_per_block * Mx;
-  for (int i = threadIdx.x; i < Mx; i += blockDim.x) tw[i] = twf[i];
-  const int pairs = (g.N[1] + 1) / 2;
-  const int64_t total_lines = (int64_t)pairs * g.N[2];
-  const int64_t l0 = (int64_t)blk * lines_per_block;
-  const int nl = (int)((total_lines - l0) < lines_per_block ? (total_lines - l0) : lines_per_block);
-  for (int idx = threadIdx.x; idx < nl * Mx; idx += blockDim.x) {
-    const int li = idx / Mx, k = idx - li * Mx;
-    const int64_t L = l0 + li;
-    const int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    const int kk = k < Hx ? k : Mx - k;
-    float2 a = spec[((int64_t)z * g.M[1] + y) * Hx + kk];
-    float2 b = make_float2(0.f, 0.f);
-    if (y + 1 < g.N[1]) b = spec[((int64_t)z * g.M[1] + y + 1) * Hx + kk];
-    if (k >= Hx) {
-      a.y = -a.y;
-      b.y = -b.y;
-    }
-    // Z = X_y + i X_{y+1}
-    A[li * Mx + k] = make_float2(a.x - b.y, a.y + b.x);
-  }
-  __syncthreads();
-  const float2* R = lds_fft_mr(A, Bf, Mx, nl, Mx, tw, -1.0f);
-  for (int idx = threadIdx.x; idx < nl * g.N[0]; idx += blockDim.x) {
-    const int li = idx / g.N[0], x = idx - li * g.N[0];
-    const int64_t L = l0 + li;
-    const int z = (int)(L / pairs), y = 2 * (int)(L % pairs);
-    const float2 v = R[li * Mx + x];
-    grid_store(U, ((int64_t)z * g.N[1] + y) * g.N[0] + x, v.x, g);
-    if (y + 1 < g.N[1]) grid_store(U, ((int64_t)z * g.N[1] + y + 1) * g.N[0] + x, v.y, g);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_c2r_x_mr(GridParams g, const float2* __restrict__ spec,
-                                                  float* __restrict__ U,
-                                                  const float2* __restrict__ twf,
-                                                  int lines_per_block) {
-  c2r_x_mr_body(g, spec, U, twf, lines_per_block, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_c2r_x_mr_cells(const CellTab* __restrict__ tab,
-                                                        const int32_t* __restrict__ bcell,
-                                                        const int32_t* __restrict__ boff) {
-  const int c = bcell[blockIdx.x];
-  const CellTab& t = tab[c];
-  c2r_x_mr_body(t.g, t.spec, t.grid, t.twfx, t.lpb, blockIdx.x - boff[c]);
-}
 
 // ---------------------------------------------------------------------------
 // interpolation + precorrection (steps 3 and 4), tile form. A workgroup

@@ -96,3 +96,37 @@ def test_scatter_anterpolation_against_the_tile_gather(p, rb, nx, grid):
     # two FP32 sums of the same charges in other orders; the far field is a
     # part of H_ms of at most its size
     assert float((h[0] - h[1]).norm() / h[1].norm()) < 1e-5
+
+
+@pytest.mark.parametrize("grid", [
+    (16, 16, 4), (14, 15, 18), (18, 20, 21), (25, 24, 27), (28, 32, 30), (36, 35, 40),
+    (42, 45, 16), (49, 50, 4), (54, 56, 5), (63, 60, 6), (64, 70, 4), (72, 75, 7), (81, 80, 4),
+    (90, 84, 4), (96, 98, 4), (100, 105, 4), (108, 112, 5), (120, 125, 4), (126, 128, 4),
+    (140, 140, 4), (144, 150, 4), (160, 162, 4), (243, 343, 4), (486, 500, 4), (512, 448, 4),
+])
+@pytest.mark.parametrize("fft", [1, 2])
+def test_grid_convolution_of_every_kind_of_extent(grid, fft):
+    """The transform passes against the same convolution by numpy in 64 bits:
+    one to five passes, every radix, whole planes (shared by one to eight
+    workgroups) and one axis at a time, padded and periodic axes."""
+    prob = mg.kuhn_box((4, 4, 2), 1e-9, periodic=0b011, grid=grid, m=[0.0, 0.0, 1.0])
+    ctx = B.Context.from_problem(prob, device=0)
+    try:
+        ctx.set_variant("fft", fft)
+    except B.PmfemError:
+        pytest.skip("the planes do not fit in LDS")
+    info = ctx.export("grid_info")
+    N, M = info[:3].astype(int), info[3:6].astype(int)
+    rng = np.random.default_rng(grid[0] * 1000 + grid[1])
+    q = rng.standard_normal(N[::-1])
+    qt = torch.tensor(q, dtype=torch.float32, device="cuda")
+    u = torch.empty_like(qt)
+    ctx.grid_convolve(qt, u)
+    khat = ctx.export("khat").reshape(M[2], M[1], M[0] // 2 + 1).astype(np.float64)
+    s = tuple(M[::-1])
+    ref = np.fft.irfftn(np.fft.rfftn(qt.cpu().numpy().astype(np.float64), s=s) * khat, s=s)
+    ref = ref[:N[2], :N[1], :N[0]] * np.prod(M)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
+    # about log2(M) roundings of 2^-24 per axis and direction, at most doubled
+    assert err < 2 * 2 * np.log2(np.prod(M)) * 2.0 ** -24
