@@ -97,7 +97,7 @@ struct pmfem_dev {
   float* hex = nullptr;  // [n][3] exchange field for pmfem_energy / heff_parts
   float *q = nullptr, *uz = nullptr, *u = nullptr, *grid = nullptr;
   float2* spec = nullptr;
-  double *mst = nullptr, *kk = nullptr, *acc = nullptr;
+  double *mst = nullptr, *acc = nullptr;
   float *m32 = nullptr, *h32 = nullptr;
   double* part = nullptr;
   int nparts = 0;
@@ -1024,7 +1024,6 @@ int upload_all(pmfem_ctx* c) {
   const int64_t nspec = (int64_t)o.N[2] * o.M[1] * (o.M[0] / 2 + 1);
   if ((rc = dalloc(c, &d->spec, nspec))) return rc;
   if ((rc = dalloc(c, &d->mst, 3 * n))) return rc;
-  if ((rc = dalloc(c, &d->kk, 3 * n))) return rc;
   if ((rc = dalloc(c, &d->acc, 3 * n))) return rc;
   if ((rc = dalloc(c, &d->m32, 3 * n))) return rc;
   if ((rc = dalloc(c, &d->h32, 3 * n))) return rc;
@@ -1316,7 +1315,8 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
 // One classic RK4 step of Eq. llg on the FP64 master m (four FP32 field
 // evaluations, FP64 combination, norm restored after the step), enqueued on
 // the context's stream.
-int enqueue_rk4(pmfem_ctx* c, double* m_dev, double dt, double alpha, const double* happ) {
+int enqueue_rk4(pmfem_ctx* c, double* m_dev, double dt, double alpha, const double* happ,
+                bool first) {
   pmfem_dev* d = c->dev;
   hipStream_t s = stream_of(c);
   const int64_t n = d->n;
@@ -1324,23 +1324,22 @@ int enqueue_rk4(pmfem_ctx* c, double* m_dev, double dt, double alpha, const doub
   const double pref = -kGamma0 / (1.0 + alpha * alpha);
   const uint32_t terms = PMFEM_TERM_EX | PMFEM_TERM_MS;
   int rc;
-  // stage 1 at m
-  hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, m_dev, (const double*)nullptr, 0.0,
-                     (double*)nullptr, d->m32);
-  if ((rc = run_heff(c, d->m32, d->h32, terms, happ))) return rc;
-  hipLaunchKernelGGL(k_rk_rhs, dim3(b1), dim3(256), 0, s, n, (const double*)m_dev, d->h32, pref,
-                     alpha, d->kk, d->acc, 1.0, 1);
+  // stage 1 at m; the later steps of a call start from the copy that the step
+  // before left
+  if (first)
+    hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, (const double*)m_dev, d->m32);
   const double cs[3] = {0.5 * dt, 0.5 * dt, dt};
-  const double ws[3] = {2.0, 2.0, 1.0};
+  const double ws[3] = {1.0, 2.0, 2.0};
   for (int k = 0; k < 3; ++k) {
-    hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, (const double*)m_dev,
-                       (const double*)d->kk, cs[k], d->mst, d->m32);
     if ((rc = run_heff(c, d->m32, d->h32, terms, happ))) return rc;
-    hipLaunchKernelGGL(k_rk_rhs, dim3(b1), dim3(256), 0, s, n, (const double*)d->mst, d->h32, pref,
-                       alpha, d->kk, d->acc, ws[k], 0);
+    hipLaunchKernelGGL(k_rk_next, dim3(b1), dim3(256), 0, s, n, (const double*)m_dev,
+                       (const double*)(k == 0 ? m_dev : d->mst), d->h32, pref, alpha, ws[k],
+                       k == 0, cs[k], d->mst, d->m32, d->acc);
   }
-  hipLaunchKernelGGL(k_rk_final, dim3(b1), dim3(256), 0, s, n, m_dev, (const double*)d->acc,
-                     dt / 6.0);
+  if ((rc = run_heff(c, d->m32, d->h32, terms, happ))) return rc;
+  hipLaunchKernelGGL(k_rk_last, dim3(b1), dim3(256), 0, s, n, m_dev, (const double*)d->mst,
+                     (const float*)d->h32, pref, alpha, (const double*)d->acc, dt / 6.0,
+                     d->m32);
   return PMFEM_OK;
 }
 
@@ -1904,7 +1903,7 @@ struct pmfem_batch {
   int lanes_l = 4, lanes_z = 8;
   float *q = nullptr, *uz = nullptr, *u = nullptr, *hex = nullptr;
   float *m32 = nullptr, *h32 = nullptr;
-  double *mst = nullptr, *kk = nullptr, *acc = nullptr;
+  double *mst = nullptr, *acc = nullptr;
   pmfem::CellTab* tab = nullptr;
   struct Launch {
     int32_t* bcell = nullptr;
@@ -2049,7 +2048,7 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
   if ((rc = balloc(b, &b->q, n)) || (rc = balloc(b, &b->uz, n)) || (rc = balloc(b, &b->u, n)) ||
       (rc = balloc(b, &b->hex, 3 * n)) || (rc = balloc(b, &b->m32, 3 * n)) ||
       (rc = balloc(b, &b->h32, 3 * n)) || (rc = balloc(b, &b->mst, 3 * n)) ||
-      (rc = balloc(b, &b->kk, 3 * n)) || (rc = balloc(b, &b->acc, 3 * n)))
+      (rc = balloc(b, &b->acc, 3 * n)))
     return rc;
   // the cell table and the launch tables of the grid kernels
   std::vector<CellTab> tab(K);
@@ -2315,28 +2314,29 @@ int batch_heff(pmfem_batch* b, const float* m, float* h, uint32_t terms) {
 }
 
 // one RK4 step of every cell on the packed FP64 master magnetisation
-int batch_rk4(pmfem_batch* b, double* m, double dt, double alpha) {
+int batch_rk4(pmfem_batch* b, double* m, double dt, double alpha, bool first) {
   hipStream_t s = b->stream;
   const int64_t n = b->n;
   const unsigned b3 = (unsigned)((3 * n + 255) / 256), b1 = (unsigned)((n + 255) / 256);
   const double pref = -kGamma0 / (1.0 + alpha * alpha);
   const uint32_t terms = PMFEM_TERM_EX | PMFEM_TERM_MS;
   int rc;
-  hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, m, (const double*)nullptr, 0.0,
-                     (double*)nullptr, b->m32);
-  if ((rc = batch_heff(b, b->m32, b->h32, terms))) return rc;
-  hipLaunchKernelGGL(k_rk_rhs, dim3(b1), dim3(256), 0, s, n, (const double*)m, b->h32, pref, alpha,
-                     b->kk, b->acc, 1.0, 1);
+  // stage 1 at m; the later steps of a call start from the copy that the step
+  // before left
+  if (first)
+    hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, (const double*)m, b->m32);
   const double cs[3] = {0.5 * dt, 0.5 * dt, dt};
-  const double ws[3] = {2.0, 2.0, 1.0};
+  const double ws[3] = {1.0, 2.0, 2.0};
   for (int k = 0; k < 3; ++k) {
-    hipLaunchKernelGGL(k_rk_stage, dim3(b3), dim3(256), 0, s, n, (const double*)m,
-                       (const double*)b->kk, cs[k], b->mst, b->m32);
     if ((rc = batch_heff(b, b->m32, b->h32, terms))) return rc;
-    hipLaunchKernelGGL(k_rk_rhs, dim3(b1), dim3(256), 0, s, n, (const double*)b->mst, b->h32, pref,
-                       alpha, b->kk, b->acc, ws[k], 0);
+    hipLaunchKernelGGL(k_rk_next, dim3(b1), dim3(256), 0, s, n, (const double*)m,
+                       (const double*)(k == 0 ? m : b->mst), b->h32, pref, alpha, ws[k],
+                       k == 0, cs[k], b->mst, b->m32, b->acc);
   }
-  hipLaunchKernelGGL(k_rk_final, dim3(b1), dim3(256), 0, s, n, m, (const double*)b->acc, dt / 6.0);
+  if ((rc = batch_heff(b, b->m32, b->h32, terms))) return rc;
+  hipLaunchKernelGGL(k_rk_last, dim3(b1), dim3(256), 0, s, n, m, (const double*)b->mst,
+                     (const float*)b->h32, pref, alpha, (const double*)b->acc, dt / 6.0,
+                     b->m32);
   return PMFEM_OK;
 }
 
@@ -2578,7 +2578,7 @@ int pmfem_llg_step(pmfem_ctx* c, double* m_dev, double dt, double alpha, int32_t
   if (!m_dev || n_steps < 0 || !(dt > 0.0) || !(alpha >= 0.0))
     return set_err(c, PMFEM_EINVAL, "bad llg arguments");
   for (int32_t st = 0; st < n_steps; ++st)
-    if ((rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied))) return rc;
+    if ((rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied, st == 0))) return rc;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_err(c, e, "kernel launch");
   return PMFEM_OK;
@@ -2617,7 +2617,7 @@ int pmfem_llg_step_graph(pmfem_ctx* c, double* m_dev, double dt, double alpha, i
     d->prof_max = d->prof_calls;  // no profiling events inside the graph
     c->stream = G.cap;
     e = hipStreamBeginCapture(G.cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied);
+    if (e == hipSuccess) rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied, true);
     hipGraph_t g = nullptr;
     const hipError_t e2 = e == hipSuccess ? hipStreamEndCapture(G.cap, &g) : e;
     c->stream = saved;
@@ -2707,7 +2707,7 @@ int pmfem_energy(pmfem_ctx* c, const double* m_dev, double* e_ex, double* e_ms) 
   hipStream_t s = stream_of(c);
   const int64_t n = d->n;
   hipLaunchKernelGGL(k_rk_stage, dim3((unsigned)((3 * n + 255) / 256)), dim3(256), 0, s, n, m_dev,
-                     (const double*)nullptr, 0.0, (double*)nullptr, d->m32);
+                     d->m32);
   // the both-terms evaluation leaves H_ex in d->hex and q, u in their buffers
   if ((rc = run_heff(c, d->m32, d->h32, PMFEM_TERM_EX | PMFEM_TERM_MS, nullptr))) return rc;
   hipLaunchKernelGGL(k_energy, dim3(d->nparts), dim3(256), 0, s, n, m_dev, (const double*)d->mu,
@@ -2933,7 +2933,7 @@ int pmfem_batch_llg_step(pmfem_batch* b, double* m_dev, double dt, double alpha,
   hipError_t e = hipSetDevice(b->device);
   if (e != hipSuccess) return batch_err(b, PMFEM_EHIP, "hipSetDevice");
   for (int32_t st = 0; st < n_steps; ++st) {
-    const int rc = batch_rk4(b, m_dev, dt, alpha);
+    const int rc = batch_rk4(b, m_dev, dt, alpha, st == 0);
     if (rc) return rc;
   }
   e = hipGetLastError();
@@ -2968,7 +2968,7 @@ int pmfem_batch_llg_step_graph(pmfem_batch* b, double* m_dev, double dt, double 
     b->stream = b->cap;
     int rc = PMFEM_OK;
     e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) rc = batch_rk4(b, m_dev, dt, alpha);
+    if (e == hipSuccess) rc = batch_rk4(b, m_dev, dt, alpha, true);
     hipGraph_t g = nullptr;
     const hipError_t e2 = e == hipSuccess ? hipStreamEndCapture(b->cap, &g) : e;
     b->stream = saved;
@@ -3306,7 +3306,7 @@ int pmfem_llg_step_judged(pmfem_ctx* c, double* m_dev, double dt, double alpha, 
       }
     }
     d->net_on = use;
-    if ((rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied))) break;
+    if ((rc = enqueue_rk4(c, m_dev, dt, alpha, h_applied, st == 0))) break;
   }
   d->net_on = was_on;
   if (rc) return rc;

@@ -186,11 +186,12 @@ template <int G>
 __global__ void k_gsum(int64_t n, const int32_t* rp, const int4* grec, const float* u,
                        const float* hex, float* h, float hax, float hay, float haz, int with_hex,
                        int with_ms);
-__global__ void k_rk_stage(int64_t n, const double* m, const double* k, double c, double* mst,
-                           float* m32);
-__global__ void k_rk_rhs(int64_t n, const double* mst, const float* h, double pref,
-                         double alpha, double* kout, double* acc, double weight, int first);
-__global__ void k_rk_final(int64_t n, double* m, const double* acc, double dt6);
+__global__ void k_rk_stage(int64_t n, const double* m, float* m32);
+__global__ void k_rk_next(int64_t n, const double* m, const double* mcur, const float* h,
+                          double pref, double alpha, double weight, int first, double c,
+                          double* mst, float* m32, double* acc);
+__global__ void k_rk_last(int64_t n, double* m, const double* mst, const float* h, double pref,
+                          double alpha, const double* acc, double dt6, float* m32);
 __global__ void k_mid_normalize(int64_t n, double* x);
 __global__ void k_energy(int64_t n, const double* m, const double* mu, const float* hex,
                          const float* q, const float* u, double* part);

@@ -1074,29 +1074,27 @@ PMFEM_MPROD(16, 16)
 // ---------------------------------------------------------------------------
 // LLG (unit-vector Landau-Lifshitz form), classic RK4 in FP64
 
-__global__ void k_rk_stage(int64_t n, const double* __restrict__ m, const double* __restrict__ k,
-                           double c, double* __restrict__ mst, float* __restrict__ m32) {
+// the FP32 copy of m
+__global__ void k_rk_stage(int64_t n, const double* __restrict__ m, float* __restrict__ m32) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 3 * n) return;
-  double v = m[i];
-  if (k) v += c * k[i];
-  if (mst) mst[i] = v;
-  m32[i] = (float)v;
+  if (i < 3 * n) m32[i] = (float)m[i];
 }
 
-__global__ void k_rk_rhs(int64_t n, const double* __restrict__ mst, const float* __restrict__ h,
-                         double pref, double alpha, double* __restrict__ kout,
-                         double* __restrict__ acc, double weight, int first) {
+// k_rk_rhs of stage k and k_rk_stage of the next one: the slope at mst goes into
+// acc, and m + c k into the next stage's mst (in place of this one's) and m32.
+// One launch instead of two, and the slope itself goes to no array of its own:
+// with small cells a step is bound by its launches.
+__global__ void k_rk_next(int64_t n, const double* __restrict__ m, const double* mcur,
+                          const float* __restrict__ h, double pref, double alpha, double weight,
+                          int first, double c, double* mst, float* __restrict__ m32,
+                          double* __restrict__ acc) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  double mx = mst[3 * i], my = mst[3 * i + 1], mz = mst[3 * i + 2];
+  double mx = mcur[3 * i], my = mcur[3 * i + 1], mz = mcur[3 * i + 2];
   double hx = h[3 * i], hy = h[3 * i + 1], hz = h[3 * i + 2];
   double cx = my * hz - mz * hy, cy = mz * hx - mx * hz, cz = mx * hy - my * hx;   // m x H
   double dx = my * cz - mz * cy, dy = mz * cx - mx * cz, dz = mx * cy - my * cx;   // m x (m x H)
   double kx = pref * (cx + alpha * dx), ky = pref * (cy + alpha * dy), kz = pref * (cz + alpha * dz);
-  kout[3 * i] = kx;
-  kout[3 * i + 1] = ky;
-  kout[3 * i + 2] = kz;
   if (first) {
     acc[3 * i] = weight * kx;
     acc[3 * i + 1] = weight * ky;
@@ -1106,19 +1104,40 @@ __global__ void k_rk_rhs(int64_t n, const double* __restrict__ mst, const float*
     acc[3 * i + 1] += weight * ky;
     acc[3 * i + 2] += weight * kz;
   }
+  const double x = m[3 * i] + c * kx, y = m[3 * i + 1] + c * ky, z = m[3 * i + 2] + c * kz;
+  mst[3 * i] = x;
+  mst[3 * i + 1] = y;
+  mst[3 * i + 2] = z;
+  m32[3 * i] = (float)x;
+  m32[3 * i + 1] = (float)y;
+  m32[3 * i + 2] = (float)z;
 }
 
-__global__ void k_rk_final(int64_t n, double* __restrict__ m, const double* __restrict__ acc,
-                           double dt6) {
+// the last stage's slope, the step m + dt / 6 (acc + k) and its norm, and the
+// FP32 copy that the next step starts from
+__global__ void k_rk_last(int64_t n, double* __restrict__ m, const double* __restrict__ mst,
+                          const float* __restrict__ h, double pref, double alpha,
+                          const double* __restrict__ acc, double dt6, float* __restrict__ m32) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  double x = m[3 * i] + dt6 * acc[3 * i];
-  double y = m[3 * i + 1] + dt6 * acc[3 * i + 1];
-  double z = m[3 * i + 2] + dt6 * acc[3 * i + 2];
+  double mx = mst[3 * i], my = mst[3 * i + 1], mz = mst[3 * i + 2];
+  double hx = h[3 * i], hy = h[3 * i + 1], hz = h[3 * i + 2];
+  double cx = my * hz - mz * hy, cy = mz * hx - mx * hz, cz = mx * hy - my * hx;
+  double dx = my * cz - mz * cy, dy = mz * cx - mx * cz, dz = mx * cy - my * cx;
+  double kx = pref * (cx + alpha * dx), ky = pref * (cy + alpha * dy), kz = pref * (cz + alpha * dz);
+  double x = m[3 * i] + dt6 * (acc[3 * i] + kx);
+  double y = m[3 * i + 1] + dt6 * (acc[3 * i + 1] + ky);
+  double z = m[3 * i + 2] + dt6 * (acc[3 * i + 2] + kz);
   double r = 1.0 / sqrt(x * x + y * y + z * z);
-  m[3 * i] = x * r;
-  m[3 * i + 1] = y * r;
-  m[3 * i + 2] = z * r;
+  x *= r;
+  y *= r;
+  z *= r;
+  m[3 * i] = x;
+  m[3 * i + 1] = y;
+  m[3 * i + 2] = z;
+  m32[3 * i] = (float)x;
+  m32[3 * i + 1] = (float)y;
+  m32[3 * i + 2] = (float)z;
 }
 
 // energy partial sums: block b writes {sum mu m.Hex, sum q u}

@@ -130,3 +130,51 @@ def test_grid_convolution_of_every_kind_of_extent(grid, fft):
     err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
     # about log2(M) roundings of 2^-24 per axis and direction, at most doubled
     assert err < 2 * 2 * np.log2(np.prod(M)) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("nx, ny", [(4, 4), (5, 7), (9, 16)])
+def test_rk4_steps_against_the_formula_and_across_calls(nx, ny):
+    """Stage kernels against the RK4 formula on the library's own field; the
+    steps of one call, of one call each, of a graph and of a batch agree."""
+    probs = [film(nx, ny), film(4, 4)]
+    ctxs = [B.Context.from_problem(p, device=0) for p in probs]
+    ms = [torch.tensor(p.m[c.query()[2]], dtype=torch.float64, device="cuda")
+          for p, c in zip(probs, ctxs)]
+    ctx, m0 = ctxs[0], ms[0]
+    dt, alpha, happ = 2e-14, 0.3, [1e4, -2e4, 3e4]
+    gamma0 = 4e-7 * np.pi * 1.76086e11
+    hmax = [0.0]
+
+    def slope(v):
+        h = torch.empty(v.shape, dtype=torch.float32, device="cuda")
+        ctx.heff(v.to(torch.float32), h, h_applied=happ)
+        h = h.to(torch.float64)
+        hmax[0] = max(hmax[0], float(h.norm(dim=1).max()))
+        c = torch.linalg.cross(v, h)
+        return -gamma0 / (1 + alpha ** 2) * (c + alpha * torch.linalg.cross(v, c))
+
+    ref = m0.clone()
+    for _ in range(3):
+        k1 = slope(ref)
+        k2 = slope(ref + dt / 2 * k1)
+        k3 = slope(ref + dt / 2 * k2)
+        k4 = slope(ref + dt * k3)
+        ref = ref + dt / 6 * (k1 + 2 * k2 + 2 * k3 + k4)
+        ref = ref / ref.norm(dim=1, keepdim=True)
+    one, each, graph = m0.clone(), m0.clone(), m0.clone()
+    ctx.llg_step(one, dt, alpha, 3, h_applied=happ)
+    for _ in range(3):
+        ctx.llg_step(each, dt, alpha, 1, h_applied=happ)
+    ctx.llg_step_graph(graph, dt, alpha, 3, h_applied=happ)
+    torch.cuda.synchronize()
+    assert torch.equal(one, each) and torch.equal(one, graph)
+    # a last-bit difference of a stage may round one FP32 input of the field
+    # the other way: 2^-24 of a field that sums a few dozen of them
+    assert float((one - ref).abs().max()) <= 3 * gamma0 * dt * hmax[0] * 2.0 ** -18
+    batch = B.Batch(ctxs)
+    packed, single = torch.cat(ms), torch.cat(ms)
+    batch.llg_step(packed, dt, alpha, 3)
+    for _ in range(3):
+        batch.llg_step(single, dt, alpha, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(packed, single)
