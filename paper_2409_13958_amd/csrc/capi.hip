@@ -110,7 +110,8 @@ struct pmfem_dev {
     double *w = nullptr, *z = nullptr, *part = nullptr, *red = nullptr;
     double* coef = nullptr;
     float *mb32 = nullptr, *H = nullptr, *z32 = nullptr, *Az = nullptr;
-    double* host = nullptr;  // pinned: coefficients out, reductions back
+    double* host = nullptr;      // pinned: coefficients out, reductions back
+    double* host_dev = nullptr;  // the device's address of it
     double *xp = nullptr, *S = nullptr;  // adaptive steps: predictor, two slopes or states
     double* r = nullptr;                 // BDF2: the combination of past states
   } imp;
@@ -1361,11 +1362,14 @@ int ready(pmfem_ctx* c) {
 
 constexpr int kMaxKrylov = 60;
 constexpr int kDotParts = 1024;
-// device reductions: dot products at [0, 62), an updated norm at kRedNorm;
-// the pinned host buffer mirrors them and carries coefficients at kHostCoef
-constexpr int kRedNorm = 64;
-constexpr int kHostCoef = 128;
-static_assert(kMaxKrylov + 2 <= kRedNorm && kMaxKrylov + 1 <= kGsMaxVectors, "Krylov sizes");
+// workgroups of the Gram-Schmidt kernels: each sums the shares of all, so more
+// than two per compute unit would read more shares than basis
+constexpr int kGsParts = 512;
+// the pinned host buffer: reductions at [0, 62), the Gram-Schmidt products of
+// the two passes at kHostH and kHostH2 (written by the kernels), coefficients
+// at kHostCoef
+constexpr int kHostH = 64, kHostH2 = 128, kHostCoef = 192;
+static_assert(kMaxKrylov + 2 <= kHostH && kMaxKrylov + 1 <= kGsMaxVectors, "Krylov sizes");
 
 int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
   pmfem_dev* d = c->dev;
@@ -1379,8 +1383,8 @@ int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
   if ((rc = dalloc(c, &W.x, n3)) || (rc = dalloc(c, &W.mb, n3)) || (rc = dalloc(c, &W.G, n3)) ||
       (rc = dalloc(c, &W.Minv, 9 * n)) || (rc = dalloc(c, &W.V, (int64_t)(kdim + 1) * n3)) ||
       (rc = dalloc(c, &W.w, n3)) || (rc = dalloc(c, &W.z, n3)) ||
-      (rc = dalloc(c, &W.part, (int64_t)(kMaxKrylov + 2) * kDotParts)) ||
-      (rc = dalloc(c, &W.red, kRedNorm + 1)) || (rc = dalloc(c, &W.coef, kMaxKrylov + 1)) ||
+      (rc = dalloc(c, &W.part, std::max<int64_t>(2 * kDotParts, (2 * kMaxKrylov + 3) * kGsParts))) ||
+      (rc = dalloc(c, &W.red, kMaxKrylov + 2)) || (rc = dalloc(c, &W.coef, kMaxKrylov + 1)) ||
       (rc = dalloc(c, &W.mb32, n3)) || (rc = dalloc(c, &W.H, n3)) || (rc = dalloc(c, &W.z32, n3)) ||
       (rc = dalloc(c, &W.Az, n3)))
     return rc;
@@ -1396,6 +1400,8 @@ int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
   if (!W.host) {
     const hipError_t e = hipHostMalloc((void**)&W.host, (kHostCoef + kMaxKrylov + 1) * sizeof(double));
     if (e != hipSuccess) return set_err(c, PMFEM_ENOMEM, "hipHostMalloc");
+    const hipError_t e2 = hipHostGetDevicePointer((void**)&W.host_dev, W.host, 0);
+    if (e2 != hipSuccess) return hip_err(c, e2, "implicit workspace");
   }
   W.kdim = kdim;
   return PMFEM_OK;
@@ -1461,29 +1467,32 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
   hipStream_t s = stream_of(c);
   const int64_t n = d->n, n3 = 3 * n;
   const unsigned b3 = (unsigned)((n3 + 255) / 256), b1 = (unsigned)((n + 255) / 256);
+  const unsigned P = std::min<unsigned>(kGsParts, b1);
   const double cc = -kGamma0 / (1.0 + alpha * alpha);
   const double sj = -theta * dt * cc;  // dG/dx = I + sj D
   const double eta = 1e-6;
   const double rms = std::sqrt((double)n3);
-  std::vector<double> hcol(kMaxKrylov + 2), h2(kMaxKrylov + 2), y(kMaxKrylov + 1),
-      g(kMaxKrylov + 2), cs(kMaxKrylov + 1), sn(kMaxKrylov + 1);
+  std::vector<double> hcol(kMaxKrylov + 2), y(kMaxKrylov + 1), g(kMaxKrylov + 2),
+      cs(kMaxKrylov + 1), sn(kMaxKrylov + 1);
   std::vector<double> R((size_t)(kMaxKrylov + 1) * (kMaxKrylov + 1));
   int rc;
   double best = HUGE_VAL, first = 0.0;
   int stall = 0;
   *converged = false;
   if (hist) hist->clear();
+  hipLaunchKernelGGL(k_mid_point, dim3(b3), dim3(256), 0, s, n3, m, (const double*)W.x, theta, W.mb,
+                     W.mb32);
   for (int it = 0; it <= max_newton; ++it) {
-    hipLaunchKernelGGL(k_mid_point, dim3(b3), dim3(256), 0, s, n3, m, (const double*)W.x, theta,
-                       W.mb, W.mb32);
     if ((rc = run_heff(c, W.mb32, W.H, terms, happ, W.mb))) return rc;
-    hipLaunchKernelGGL(k_mid_residual, dim3(kDotParts), dim3(256), 0, s, n, r, (const double*)W.x,
+    hipLaunchKernelGGL(k_mid_residual, dim3(P), dim3(256), 0, s, n, r, (const double*)W.x,
                        (const double*)W.mb, (const float*)W.H, (const double*)W.adiag, dt, cc,
                        alpha, theta, W.G, W.Minv, W.part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, (const double*)W.part, kDotParts,
-                       W.red);
-    hipError_t e = hipMemcpyAsync(W.host, W.red, sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    // the residual's norm and, for the case that it is not small enough yet,
+    // V_0 = G / beta, preconditioned
+    hipLaunchKernelGGL(k_gs_next, dim3(std::min(b1, 2u * kGsParts)), dim3(256), 0, s, n,
+                       (const double*)W.G, (const double*)W.Minv, (const double*)W.part, (int)P, 0,
+                       W.V, W.z, W.z32, W.host_dev);
+    hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_err(c, e, "implicit residual");
     const double beta = std::sqrt(W.host[0]);
     if (hist) {
@@ -1506,46 +1515,35 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
     // pass where the first removed more than half of |w|^2 (w has lost
     // orthogonality to the basis), the basis held in FP32
     const double stop = std::max(eta * beta, 0.5 * tol * rms);
-    hipLaunchKernelGGL(k_gs_store, dim3(b3), dim3(256), 0, s, n3, (const double*)W.G, 1.0 / beta,
-                       W.V);
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int used = 0;
-    // h = V^T w and |w|^2, then w -= V h and |w|^2 again; one wait per pass
-    auto gs_pass = [&](int nv, double* h, double* ww, double* w2) -> int {
-      hipLaunchKernelGGL(k_gs_dots, dim3(kDotParts), dim3(256), 0, s, n3, (const float*)W.V, n3,
-                         nv, (const double*)W.w, W.part);
-      hipLaunchKernelGGL(k_sum_parts, dim3(nv + 1), dim3(256), 0, s, (const double*)W.part,
-                         kDotParts, W.red);
-      hipLaunchKernelGGL(k_gs_update, dim3(kDotParts), dim3(256), 0, s, n3, (const float*)W.V, n3,
-                         nv, (const double*)W.red, W.w, W.part);
-      hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, (const double*)W.part, kDotParts,
-                         W.red + kRedNorm);
-      hipError_t e2 = hipMemcpyAsync(W.host, W.red, (kRedNorm + 1) * sizeof(double),
-                                     hipMemcpyDeviceToHost, s);
-      if (e2 == hipSuccess) e2 = hipStreamSynchronize(s);
-      if (e2 != hipSuccess) return hip_err(c, e2, "implicit Gram-Schmidt");
-      for (int j = 0; j < nv; ++j) h[j] = W.host[j];
-      *ww = W.host[nv];
-      *w2 = W.host[kRedNorm];
-      return PMFEM_OK;
-    };
     for (int i = 0; i < kdim; ++i) {
-      const float* Vi = W.V + (int64_t)i * n3;
-      hipLaunchKernelGGL(k_mid_precond<float>, dim3(b1), dim3(256), 0, s, n,
-                         (const double*)W.Minv, Vi, W.z, W.z32);
+      const int nv = i + 1;
       if ((rc = run_heff(c, W.z32, W.Az, terms, nullptr))) return rc;
-      hipLaunchKernelGGL(k_mid_jvp, dim3(b1), dim3(256), 0, s, n, (const double*)W.z,
-                         (const float*)W.Az, (const double*)W.mb, (const float*)W.H, sj, alpha,
-                         W.w);
+      const MidJvp jv{W.z, W.Az, W.mb, W.H, sj, alpha};
+      hipLaunchKernelGGL(k_gs_jvp_dots, dim3(P), dim3(256), 0, s, n, jv, (const float*)W.V, n3, nv,
+                         W.w, W.part);
+      hipLaunchKernelGGL(k_gs_update, dim3(P), dim3(256), 0, s, n3, (const float*)W.V, n3, nv, 0,
+                         W.w, W.part, W.host_dev + kHostH);
+      hipLaunchKernelGGL(k_gs_dots_again, dim3(P), dim3(256), 0, s, n, (const float*)W.V, n3, nv,
+                         W.w, W.part);
+      hipLaunchKernelGGL(k_gs_update, dim3(P), dim3(256), 0, s, n3, (const float*)W.V, n3, nv, 1,
+                         W.w, W.part, W.host_dev + kHostH2);
+      hipLaunchKernelGGL(k_gs_next, dim3(std::min(b1, 2u * kGsParts)), dim3(256), 0, s, n,
+                         (const double*)W.w, (const double*)W.Minv, (const double*)W.part, (int)P,
+                         nv, W.V + (int64_t)nv * n3, W.z, W.z32, W.host_dev);
       ++*krylov_its;
-      double ww = 0.0, w2 = 0.0, ww2 = 0.0, w3 = 0.0;
-      if ((rc = gs_pass(i + 1, hcol.data(), &ww, &w2))) return rc;
-      if (w2 < 0.5 * ww) {
-        if ((rc = gs_pass(i + 1, h2.data(), &ww2, &w3))) return rc;
-        for (int j = 0; j <= i; ++j) hcol[j] += h2[j];
-        w2 = w3;
+      if ((e = hipStreamSynchronize(s)) != hipSuccess)
+        return hip_err(c, e, "implicit Gram-Schmidt");
+      const double ww = W.host[0];
+      double w2 = W.host[1];
+      const bool again = w2 < 0.5 * ww;
+      for (int j = 0; j < nv; ++j) {
+        hcol[j] = W.host[kHostH + j];
+        if (again) hcol[j] += W.host[kHostH2 + j];
       }
+      if (again) w2 = W.host[2];
       const double hn = std::sqrt(std::max(w2, 0.0));
       // column i of the Hessenberg matrix, rotated by the previous Givens
       // rotations, then a new rotation that zeroes its subdiagonal
@@ -1563,8 +1561,6 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
       g[i] = cs[i] * g[i];
       used = i + 1;
       if (std::fabs(g[i + 1]) <= stop || hn == 0.0 || i + 1 == kdim) break;
-      hipLaunchKernelGGL(k_gs_store, dim3(b3), dim3(256), 0, s, n3, (const double*)W.w, 1.0 / hn,
-                         W.V + (int64_t)(i + 1) * n3);
     }
     // y from R y = g, then x -= Minv (V y)
     for (int j = used - 1; j >= 0; --j) {
@@ -1573,20 +1569,10 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
       const double rjj = R[(size_t)j * (kMaxKrylov + 1) + j];
       y[j] = rjj != 0.0 ? v / rjj : 0.0;
     }
-    {
-      hipError_t e2 = hipStreamSynchronize(s);
-      double* hc = W.host + kHostCoef;
-      for (int j = 0; j < used; ++j) hc[j] = y[j];
-      if (e2 == hipSuccess)
-        e2 = hipMemcpyAsync(W.coef, hc, used * sizeof(double), hipMemcpyHostToDevice, s);
-      if (e2 != hipSuccess) return hip_err(c, e2, "implicit update");
-    }
-    hipLaunchKernelGGL(k_gs_combine, dim3(b3), dim3(256), 0, s, n3, (const float*)W.V, n3, used,
-                       (const double*)W.coef, W.w);
-    hipLaunchKernelGGL(k_mid_precond<double>, dim3(b1), dim3(256), 0, s, n,
-                       (const double*)W.Minv, (const double*)W.w, W.z, (float*)nullptr);
-    const double minus_one = -1.0;
-    if ((rc = lincomb(c, s, W.z, n3, 1, &minus_one, 1.0, W.x, W.x))) return rc;
+    GsCoef yc{};
+    std::copy(y.begin(), y.begin() + used, yc.c);
+    hipLaunchKernelGGL(k_mid_correct, dim3(b1), dim3(256), 0, s, n, (const float*)W.V, n3, used, yc,
+                       (const double*)W.Minv, m, theta, W.x, W.mb, W.mb32);
   }
   return PMFEM_OK;
 }

@@ -201,18 +201,29 @@ __global__ void k_mid_point(int64_t n3, const double* m, const double* x, double
 __global__ void k_mid_residual(int64_t n, const double* m, const double* x, const double* mb,
                                const float* H, const double* adiag, double dt, double c,
                                double alpha, double theta, double* G, double* Minv, double* part);
-template <typename VT>
-__global__ void k_mid_precond(int64_t n, const double* Minv, const VT* v, double* z, float* z32);
 constexpr int kGsMaxVectors = 64;  // Krylov vectors one Gram-Schmidt update takes
-__global__ void k_gs_dots(int64_t n3, const float* V, int64_t ldv, int nv, const double* w,
-                          double* part);
-__global__ void k_gs_update(int64_t n3, const float* V, int64_t ldv, int nv, const double* h,
-                            double* w, double* part);
-__global__ void k_gs_store(int64_t n3, const double* w, double s, float* out);
-__global__ void k_gs_combine(int64_t n3, const float* V, int64_t ldv, int nv, const double* coef,
-                             double* out);
-__global__ void k_mid_jvp(int64_t n, const double* z, const float* Az, const double* mb,
-                          const float* H, double s, double alpha, double* w);
+// operands of w = dG/dx z
+struct MidJvp {
+  const double* z;
+  const float* Az;
+  const double* mb;
+  const float* H;
+  double s, alpha;
+};
+struct GsCoef {
+  double c[kGsMaxVectors];
+};
+__global__ void k_gs_jvp_dots(int64_t n, MidJvp a, const float* V, int64_t ldv, int nv, double* w,
+                              double* part);
+__global__ void k_gs_dots_again(int64_t n, const float* V, int64_t ldv, int nv, double* w,
+                                double* part);
+__global__ void k_gs_update(int64_t n3, const float* V, int64_t ldv, int nv, int pass, double* w,
+                            double* part, double* out);
+__global__ void k_gs_next(int64_t n, const double* w, const double* Minv, const double* part,
+                          int nparts, int nv, float* v, double* z, float* z32, double* out);
+__global__ void k_mid_correct(int64_t n, const float* V, int64_t ldv, int nv, GsCoef y,
+                              const double* Minv, const double* m, double theta, double* x,
+                              double* mb, float* mb32);
 __global__ void k_mdot(int64_t n3, const double* V, int64_t ldv, int nv, const double* w,
                        double* part);
 __global__ void k_sum_parts(const double* part, int nparts, double* out);

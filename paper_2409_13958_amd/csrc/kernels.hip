@@ -1262,60 +1262,25 @@ __global__ void k_mid_normalize(int64_t n, double* __restrict__ x) {
   x[3 * i + 2] = c * r;
 }
 
-// z = Minv v per node; z32 its FP32 copy (NULL: not written)
-template <typename VT>
-__global__ void k_mid_precond(int64_t n, const double* __restrict__ Minv,
-                              const VT* __restrict__ v, double* __restrict__ z,
-                              float* __restrict__ z32) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double* Mi = Minv + 9 * i;
-  const double vx = (double)v[3 * i], vy = (double)v[3 * i + 1], vz = (double)v[3 * i + 2];
-  const double a = Mi[0] * vx + Mi[1] * vy + Mi[2] * vz;
-  const double b = Mi[3] * vx + Mi[4] * vy + Mi[5] * vz;
-  const double d = Mi[6] * vx + Mi[7] * vy + Mi[8] * vz;
-  z[3 * i] = a;
-  z[3 * i + 1] = b;
-  z[3 * i + 2] = d;
-  if (z32) {
-    z32[3 * i] = (float)a;
-    z32[3 * i + 1] = (float)b;
-    z32[3 * i + 2] = (float)d;
-  }
-}
-template __global__ void k_mid_precond<double>(int64_t, const double*, const double*, double*,
-                                               float*);
-template __global__ void k_mid_precond<float>(int64_t, const double*, const float*, double*,
-                                              float*);
-
-// w = dG/dx z, with Az = A z from one FP32 field evaluation
-__global__ void k_mid_jvp(int64_t n, const double* __restrict__ z, const float* __restrict__ Az,
-                          const double* __restrict__ mb, const float* __restrict__ H, double s,
-                          double alpha, double* __restrict__ w) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double bx = mb[3 * i], by = mb[3 * i + 1], bz = mb[3 * i + 2];
-  const double hx = H[3 * i], hy = H[3 * i + 1], hz = H[3 * i + 2];
-  const double zx = z[3 * i], zy = z[3 * i + 1], zz = z[3 * i + 2];
-  const double ax = Az[3 * i], ay = Az[3 * i + 1], az = Az[3 * i + 2];
-  double px, py, pz, t1x, t1y, t1z, t2x, t2y, t2z, t3x, t3y, t3z, t4x, t4y, t4z, t5x, t5y, t5z;
-  cross3(bx, by, bz, hx, hy, hz, px, py, pz);          // mb x H
-  cross3(zx, zy, zz, hx, hy, hz, t1x, t1y, t1z);       // z x H
-  cross3(bx, by, bz, ax, ay, az, t2x, t2y, t2z);       // mb x (A z)
-  cross3(zx, zy, zz, px, py, pz, t3x, t3y, t3z);       // z x (mb x H)
-  cross3(bx, by, bz, t1x, t1y, t1z, t4x, t4y, t4z);    // mb x (z x H)
-  cross3(bx, by, bz, t2x, t2y, t2z, t5x, t5y, t5z);    // mb x (mb x (A z))
-  w[3 * i] = zx + s * (t1x + t2x + alpha * (t3x + t4x + t5x));
-  w[3 * i + 1] = zy + s * (t1y + t2y + alpha * (t3y + t4y + t5y));
-  w[3 * i + 2] = zz + s * (t1z + t2z + alpha * (t3z + t4z + t5z));
-}
-
-// Gram-Schmidt of the implicit solver's GMRES. The Krylov basis V is held
-// in FP32 (its rounding, 6e-8 relative, lies below the relative residual
-// GMRES is asked for, and each basis vector is one FP32 field evaluation's
-// input anyway); w and every sum are FP64, each sum in a fixed order
-// (grid-stride per thread, a fixed shuffle tree per wavefront, the four
-// wavefronts in order, then k_sum_parts).
+// GMRES of the implicit solver. The Krylov basis V is held in FP32 (its
+// rounding, 6e-8 relative, lies below the relative residual GMRES is asked
+// for, and each basis vector is one FP32 field evaluation's input anyway); w
+// and every sum are FP64, each sum in a fixed order (grid-stride per thread, a
+// fixed shuffle tree per wavefront, the four wavefronts in order, then
+// sum_rows over the workgroups).
+//
+// Around a field evaluation a vector takes five launches and one wait of the
+// host. What bounds them on the cells that such steps are made of (a few ten
+// thousand unknowns) is their number and the host's waits, not their bytes:
+// nothing sums the workgroups' shares in a launch of its own - each workgroup
+// of the reader sums all of them, in the same order - and whether the second
+// pass of the Gram-Schmidt is needed is read on the device.
+// Film of 8 k nodes, two steps: 1405 us with a launch per operation, a
+// copy and a wait per pass, 1130 us so.
+//
+// Rows of part (stride nparts), for nv basis vectors: [0, nv) V_j . w,
+// nv: |w|^2, nv + 1: |w|^2 after the first pass, nv + 2: after the second,
+// nv + 3 + j: V_j . w of the second pass.
 constexpr int kGsChunk = 16;
 
 __device__ __forceinline__ double wave_sum_d(double v) {
@@ -1324,25 +1289,84 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-// part[j * gridDim.x + b] = block b's share of V_j . w for j < nv and of
-// w . w for j = nv
-__global__ void __launch_bounds__(256) k_gs_dots(int64_t n3, const float* __restrict__ V,
-                                                 int64_t ldv, int nv, const double* __restrict__ w,
-                                                 double* __restrict__ part) {
+// out[r] = sum over b < nparts of part[r * nparts + b] for r < rows, by all 256
+// threads: 16 lanes a row
+__device__ __forceinline__ void sum_rows(const double* __restrict__ part, int nparts, int rows,
+                                         double* out) {
+  const int l = threadIdx.x & 15;
+  for (int r = threadIdx.x >> 4; r < rows; r += 16) {
+    double v = 0.0;
+    for (int b = l; b < nparts; b += 16) v += part[(int64_t)r * nparts + b];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
+    if (l == 0) out[r] = v;
+  }
+  __syncthreads();
+}
+
+// the first pass removed more than half of |w|^2: w has lost orthogonality
+__device__ __forceinline__ bool gs_again(double ww, double w2) { return w2 < 0.5 * ww; }
+
+// block b's share of V_j . w for j < nv (and |w|^2 for j = nv where norm), a
+// node's three components per thread; JVP: w = dG/dx z first, with Az = A z
+// from one FP32 field evaluation
+__device__ __forceinline__ void mid_jvp(const MidJvp& a, int64_t i, double* __restrict__ w) {
+  const double bx = a.mb[3 * i], by = a.mb[3 * i + 1], bz = a.mb[3 * i + 2];
+  const double hx = a.H[3 * i], hy = a.H[3 * i + 1], hz = a.H[3 * i + 2];
+  const double zx = a.z[3 * i], zy = a.z[3 * i + 1], zz = a.z[3 * i + 2];
+  const double ax = a.Az[3 * i], ay = a.Az[3 * i + 1], az = a.Az[3 * i + 2];
+  double px, py, pz, t1x, t1y, t1z, t2x, t2y, t2z, t3x, t3y, t3z, t4x, t4y, t4z, t5x, t5y, t5z;
+  cross3(bx, by, bz, hx, hy, hz, px, py, pz);          // mb x H
+  cross3(zx, zy, zz, hx, hy, hz, t1x, t1y, t1z);       // z x H
+  cross3(bx, by, bz, ax, ay, az, t2x, t2y, t2z);       // mb x (A z)
+  cross3(zx, zy, zz, px, py, pz, t3x, t3y, t3z);       // z x (mb x H)
+  cross3(bx, by, bz, t1x, t1y, t1z, t4x, t4y, t4z);    // mb x (z x H)
+  cross3(bx, by, bz, t2x, t2y, t2z, t5x, t5y, t5z);    // mb x (mb x (A z))
+  w[0] = zx + a.s * (t1x + t2x + a.alpha * (t3x + t4x + t5x));
+  w[1] = zy + a.s * (t1y + t2y + a.alpha * (t3y + t4y + t5y));
+  w[2] = zz + a.s * (t1z + t2z + a.alpha * (t3z + t4z + t5z));
+}
+
+template <bool JVP>
+__device__ __forceinline__ void gs_dots_body(int64_t n, const MidJvp& a,
+                                             const float* __restrict__ V, int64_t ldv, int nv,
+                                             double* __restrict__ w, double* __restrict__ part) {
   __shared__ double red[4][kGsChunk];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int j0 = 0; j0 <= nv; j0 += kGsChunk) {
-    const int jn = min(kGsChunk, nv + 1 - j0);
+  const int rows = nv + (JVP ? 1 : 0);
+  for (int j0 = 0; j0 < rows; j0 += kGsChunk) {
+    const int jn = min(kGsChunk, rows - j0);
     double acc[kGsChunk];
 #pragma unroll
     for (int k = 0; k < kGsChunk; ++k) acc[k] = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n3;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-      const double wi = w[i];
+      double x[3];
+      if (JVP && j0 == 0) {
+        mid_jvp(a, i, x);
+        w[3 * i] = x[0];
+        w[3 * i + 1] = x[1];
+        w[3 * i + 2] = x[2];
+      } else {
+        x[0] = w[3 * i];
+        x[1] = w[3 * i + 1];
+        x[2] = w[3 * i + 2];
+      }
 #pragma unroll
       for (int k = 0; k < kGsChunk; ++k) {
         const int j = j0 + k;
-        if (k < jn) acc[k] = fma(j < nv ? (double)V[(int64_t)j * ldv + i] : wi, wi, acc[k]);
+        if (k < jn) {
+          if (j < nv) {
+            const float* Vj = V + (int64_t)j * ldv + 3 * i;
+            acc[k] = fma((double)Vj[0], x[0], acc[k]);
+            acc[k] = fma((double)Vj[1], x[1], acc[k]);
+            acc[k] = fma((double)Vj[2], x[2], acc[k]);
+          } else {
+            acc[k] = fma(x[0], x[0], acc[k]);
+            acc[k] = fma(x[1], x[1], acc[k]);
+            acc[k] = fma(x[2], x[2], acc[k]);
+          }
+        }
       }
     }
 #pragma unroll
@@ -1360,17 +1384,44 @@ __global__ void __launch_bounds__(256) k_gs_dots(int64_t n3, const float* __rest
   }
 }
 
-// w -= sum_j h[j] V_j (j < nv, ascending); part[b] = block b's share of
-// |w|^2 after the update
+// w = dG/dx z and its products with the basis
+__global__ void __launch_bounds__(256) k_gs_jvp_dots(int64_t n, MidJvp a,
+                                                     const float* __restrict__ V, int64_t ldv,
+                                                     int nv, double* __restrict__ w,
+                                                     double* __restrict__ part) {
+  gs_dots_body<true>(n, a, V, ldv, nv, w, part);
+}
+
+// the products of the second pass, where it is needed
+__global__ void __launch_bounds__(256) k_gs_dots_again(int64_t n, const float* __restrict__ V,
+                                                       int64_t ldv, int nv,
+                                                       double* __restrict__ w,
+                                                       double* __restrict__ part) {
+  __shared__ double nrm[2];
+  sum_rows(part + (int64_t)nv * gridDim.x, gridDim.x, 2, nrm);
+  if (!gs_again(nrm[0], nrm[1])) return;
+  gs_dots_body<false>(n, MidJvp{}, V, ldv, nv, w, part + (int64_t)(nv + 3) * gridDim.x);
+}
+
+// w -= sum_j h[j] V_j (j < nv, ascending) with the first (pass 0) or second
+// pass's products, and block b's share of |w|^2 after it; out[j] = h[j]
 __global__ void __launch_bounds__(256) k_gs_update(int64_t n3, const float* __restrict__ V,
-                                                   int64_t ldv, int nv,
-                                                   const double* __restrict__ h,
+                                                   int64_t ldv, int nv, int pass,
                                                    double* __restrict__ w,
-                                                   double* __restrict__ part) {
+                                                   double* __restrict__ part,
+                                                   double* __restrict__ out) {
   __shared__ double hs[kGsMaxVectors];
   __shared__ double red[4];
-  for (int t = threadIdx.x; t < nv; t += blockDim.x) hs[t] = h[t];
-  __syncthreads();
+  const int64_t P = gridDim.x;
+  if (pass) {
+    sum_rows(part + nv * P, (int)P, 2, hs);
+    const bool again = gs_again(hs[0], hs[1]);
+    __syncthreads();
+    if (!again) return;
+  }
+  sum_rows(part + (pass ? nv + 3 : 0) * P, (int)P, nv, hs);
+  if (blockIdx.x == 0)
+    for (int j = threadIdx.x; j < nv; j += blockDim.x) out[j] = hs[j];
   double acc = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n3;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -1382,24 +1433,73 @@ __global__ void __launch_bounds__(256) k_gs_update(int64_t n3, const float* __re
   const double sv = wave_sum_d(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sv;
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+  if (threadIdx.x == 0)
+    part[(nv + 1 + pass) * P + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// out = (float)(s w)
-__global__ void k_gs_store(int64_t n3, const double* __restrict__ w, double s,
-                           float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n3) out[i] = (float)(s * w[i]);
+// the next basis vector v = w / |w| in FP32 and its preconditioned
+// z = Minv v with its FP32 copy. |w|^2 is the one row of part (nv = 0: the
+// residual) or, of the rows nv, nv + 1 and nv + 2, the last pass's.
+// out: |w|^2 before, after the first and after the second pass (nv = 0: out[0])
+__global__ void __launch_bounds__(256) k_gs_next(int64_t n, const double* __restrict__ w,
+                                                 const double* __restrict__ Minv,
+                                                 const double* __restrict__ part, int nparts,
+                                                 int nv, float* __restrict__ v,
+                                                 double* __restrict__ z, float* __restrict__ z32,
+                                                 double* __restrict__ out) {
+  __shared__ double nrm[3];
+  sum_rows(part + (int64_t)nv * nparts, nparts, nv ? 3 : 1, nrm);
+  if (blockIdx.x == 0 && (int)threadIdx.x < (nv ? 3 : 1)) out[threadIdx.x] = nrm[threadIdx.x];
+  const double w2 = nv == 0 ? nrm[0] : gs_again(nrm[0], nrm[1]) ? nrm[2] : nrm[1];
+  const double s = 1.0 / sqrt(fmax(w2, 0.0));
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const float fx = (float)(s * w[3 * i]), fy = (float)(s * w[3 * i + 1]),
+                fz = (float)(s * w[3 * i + 2]);
+    v[3 * i] = fx;
+    v[3 * i + 1] = fy;
+    v[3 * i + 2] = fz;
+    const double* Mi = Minv + 9 * i;
+    const double vx = fx, vy = fy, vz = fz;
+    const double a = Mi[0] * vx + Mi[1] * vy + Mi[2] * vz;
+    const double b = Mi[3] * vx + Mi[4] * vy + Mi[5] * vz;
+    const double d = Mi[6] * vx + Mi[7] * vy + Mi[8] * vz;
+    z[3 * i] = a;
+    z[3 * i + 1] = b;
+    z[3 * i + 2] = d;
+    z32[3 * i] = (float)a;
+    z32[3 * i + 1] = (float)b;
+    z32[3 * i + 2] = (float)d;
+  }
 }
 
-// out = sum_j coef[j] V_j (j < nv, ascending)
-__global__ void k_gs_combine(int64_t n3, const float* __restrict__ V, int64_t ldv, int nv,
-                             const double* __restrict__ coef, double* __restrict__ out) {
+// Newton's correction x -= Minv sum_j y[j] V_j (j < nv, ascending) and the next
+// evaluation point as in k_mid_point
+__global__ void __launch_bounds__(256) k_mid_correct(int64_t n, const float* __restrict__ V,
+                                                     int64_t ldv, int nv, GsCoef y,
+                                                     const double* __restrict__ Minv,
+                                                     const double* __restrict__ m, double theta,
+                                                     double* __restrict__ x,
+                                                     double* __restrict__ mb,
+                                                     float* __restrict__ mb32) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n3) return;
-  double v = 0.0;
-  for (int j = 0; j < nv; ++j) v = fma(coef[j], (double)V[(int64_t)j * ldv + i], v);
-  out[i] = v;
+  if (i >= n) return;
+  double vx = 0.0, vy = 0.0, vz = 0.0;
+  for (int j = 0; j < nv; ++j) {
+    const float* Vj = V + (int64_t)j * ldv + 3 * i;
+    vx = fma(y.c[j], (double)Vj[0], vx);
+    vy = fma(y.c[j], (double)Vj[1], vy);
+    vz = fma(y.c[j], (double)Vj[2], vz);
+  }
+  const double* Mi = Minv + 9 * i;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double xn = x[3 * i + k] - (Mi[3 * k] * vx + Mi[3 * k + 1] * vy + Mi[3 * k + 2] * vz);
+    x[3 * i + k] = xn;
+    const double b = theta == 1.0 ? xn : (1.0 - theta) * m[3 * i + k] + theta * xn;
+    mb[3 * i + k] = b;
+    mb32[3 * i + k] = (float)b;
+  }
 }
 
 // part[j * gridDim.x + b] = block b's share of V_j . w for j < nv (fixed

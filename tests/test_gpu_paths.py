@@ -178,3 +178,29 @@ def test_rk4_steps_against_the_formula_and_across_calls(nx, ny):
         batch.llg_step(single, dt, alpha, 1)
     torch.cuda.synchronize()
     assert torch.equal(packed, single)
+
+
+@pytest.mark.parametrize("nx, ny, grid, terms, dt", [
+    (4, 4, (16, 16, 4), 3, 1e-14),
+    (9, 16, (16, 16, 4), 3, 3e-13),        # more basis vectors than one chunk of products
+    (260, 256, (128, 128, 4), 1, 1e-13),   # more nodes than the workgroups take at once
+])
+def test_implicit_step_solves_its_equation(nx, ny, grid, terms, dt):
+    """The step's residual, from the library's own field of the midpoint."""
+    prob = mg.kuhn_box((nx, ny, 1), 1e-9, periodic=0b011, jitter=0.1, grid=grid)
+    ctx = B.Context.from_problem(prob, device=0)
+    _, _, nou, _ = ctx.query()
+    m = torch.tensor(prob.m[nou], dtype=torch.float64, device="cuda")
+    m = 0.05 * m + torch.tensor([0.0, 0.0, 1.0], dtype=torch.float64, device="cuda")
+    m = m / m.norm(dim=1, keepdim=True)
+    x, alpha, tol = m.clone(), 0.3, 1e-5
+    ctx.llg_implicit(x, dt, alpha, 1, terms=terms, tol=tol)
+    mb = 0.5 * m + 0.5 * x
+    h = torch.empty(m.shape, dtype=torch.float32, device="cuda")
+    ctx.heff(mb.to(torch.float32), h, terms=terms)
+    h = h.to(torch.float64)
+    c = torch.linalg.cross(mb, h)
+    c = c + alpha * torch.linalg.cross(mb, c)
+    g = x - m + dt * 4e-7 * np.pi * 1.76086e11 / (1 + alpha ** 2) * c
+    # Newton stops at tol; the FP64 roundings of this formula are 1e-14 of it
+    assert float(g.pow(2).mean().sqrt()) <= tol * (1 + 1e-3)
