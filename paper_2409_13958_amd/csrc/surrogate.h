@@ -63,7 +63,7 @@ struct Surrogate {
   float *win = nullptr, *wout = nullptr, *woutt = nullptr;  // [C][27] (BF16 values)
   // work buffers
   float* act = nullptr;   // inference: 2 x [nvox][C]; training: (depth-1) x [nvox][C]
-  float *gA = nullptr, *gB = nullptr, *xpad = nullptr, *gpad = nullptr;  // [nvox][C]
+  float *gA = nullptr, *gB = nullptr;  // [nvox][C]
   float *y = nullptr, *gy = nullptr;   // [nvox]
   float *qbuf = nullptr, *ubuf = nullptr;  // a training pair's Q and U grids
   float* part = nullptr;                // weight-gradient partial sums [kSgWPart][C*C*27]

@@ -17,6 +17,8 @@ constexpr int kRedBlocks = 1024;   // blocks of the device reductions (partials 
 constexpr int kSgWS = 48;          // LDS point stride (floats) of the weight-gradient kernel
 constexpr size_t kSgWgradLds = (size_t)(kSgTX * kSgTY + kSgHalo) * kSgWS * sizeof(float);
 
+constexpr int kSgThin = kSgC * 32;   // a thin layer's partial sums: 27 offsets, the bias, 4 unused
+
 // FP32 -> BF16, round to nearest even (finite inputs)
 __device__ __forceinline__ uint32_t bf16_bits(float f) {
   uint32_t u = __float_as_uint(f);
@@ -388,31 +390,124 @@ __global__ __launch_bounds__(512) void k_sg_wgrad(SgGrid g, const float* __restr
       P[((dz * 9 + j) * kSgC + mt * 16 + 4 * kq + r) * kSgC + nt * 16 + li] = acc[j][r];
 }
 
+// Weight gradient of the layers with one channel on a side, from their wide
+// array a[v][C] and their narrow one x[v]: part[P][o][c] = sum over points v
+// of a[v][c] x[v + o] xs (circular in x, y; zero outside in z) for the 27
+// offsets, and at o = 27 the plain sum of a[v][c]. The first layer has a =
+// its output gradient, x = Q; the last layer a = its input, x = dL/dy, and
+// the offsets reversed. FP32 products and sums on the matrix cores
+// (v_mfma_f32_16x16x4f32: M = 16 channels, N = 16 offsets, K = 4 points): 32
+// channels x 32 columns in four accumulators. A is read once, straight into
+// the operand layout (lane li holds channels 2 li and 2 li + 1, so that four
+// points are one 512-byte load of the wavefront), x with its halo from LDS.
+// A workgroup takes the 32 x 8 tiles blockIdx.x, + P, ..., each of its four
+// wavefronts two rows with all sixteen loads in flight, and adds the four
+// wavefronts in a fixed order. Bound by reading A: 131 k points in 8.7 us
+// (2 TB/s; the sums after it 5 us), where the 32 x 32 kernel of the middle
+// layers, fed the narrow array padded to 32 channels, took 91 and 20.
+__global__ __launch_bounds__(kT) void k_sg_wgrad_thin(SgGrid g, const float* __restrict__ a,
+                                                       const float* __restrict__ x, float xs,
+                                                       float* __restrict__ part) {
+  __shared__ float sx[3 * kSgHalo];
+  __shared__ float red[4][kSgThin];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, kq = lane >> 4;
+  const int tiles_x = (g.nx + kSgTX - 1) / kSgTX, tiles_y = (g.ny + kSgTY - 1) / kSgTY;
+  const int tpp = tiles_x * tiles_y, ntiles = tpp * g.nz;
+  // staged position of offset o relative to that of a point's (dz, dy, dx) = (-1, -1, -1)
+  auto rel = [](int o) { return (o / 9) * kSgHalo + ((o % 9) / 3) * kSgHX + o % 3; };
+  const int r0 = rel(li), r1 = rel(min(16 + li, 26));
+  const bool o1 = li < 11;
+  const float c1 = li == 11 ? 1.f : 0.f;  // columns 27 (plain sum) and 28 .. 31
+  f32x4 acc[2][2] = {};
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int z = tile / tpp, r = tile - z * tpp;
+    const int x0 = (r % tiles_x) * kSgTX, y0 = (r / tiles_x) * kSgTY;
+    float2 av[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int gy = y0 + 2 * wv + k / 8, gx = x0 + (k % 8) * 4 + kq;
+      av[k] = make_float2(0.f, 0.f);
+      if (gx < g.nx && gy < g.ny)
+        av[k] = reinterpret_cast<const float2*>(a + vox_of(g, z, gy, gx) * kSgC)[li];
+    }
+    __syncthreads();  // the previous tile has been used
+    for (int i = t; i < 3 * kSgHalo; i += kT) {
+      const int pl = i / kSgHalo, h = i - pl * kSgHalo;
+      const int hy = h / kSgHX, hx = h - hy * kSgHX, gz = z + pl - 1;
+      float v = 0.f;
+      if (gz >= 0 && gz < g.nz)
+        v = x[vox_of(g, gz, wrapi(y0 + hy - 1, g.ny), wrapi(x0 + hx - 1, g.nx))] * xs;
+      sx[i] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int base = (2 * wv + k / 8) * kSgHX + (k % 8) * 4 + kq;
+      const float b0 = sx[base + r0], bx = sx[base + r1], b1 = o1 ? bx : c1;
+      acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].x, b0, acc[0][0], 0, 0, 0);
+      acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].y, b0, acc[1][0], 0, 0, 0);
+      acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].x, b1, acc[0][1], 0, 0, 0);
+      acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].y, b1, acc[1][1], 0, 0, 0);
+    }
+  }
+  // D block: lane holds rows 4 kq + r of the (even or odd) channels, column li
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[wv][(c * 16 + li) * kSgC + 2 * (4 * kq + r) + h] = acc[h][c][r];
+  __syncthreads();
+  for (int e = t; e < kSgThin; e += kT)
+    part[(int64_t)blockIdx.x * kSgThin + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+}
+
+// Sum of the thin layers' partial sums part[P][o][c] into W[c][27] (offsets
+// reversed for the last layer) and, where bias is given, the plain sums. One
+// workgroup per offset, 32 shares of the P sums added in a fixed order (FP64).
+__global__ __launch_bounds__(1024) void k_sg_reduce_thin(int P, const float* __restrict__ part,
+                                                          int reversed, float* __restrict__ w,
+                                                          float* __restrict__ bias) {
+  __shared__ double red[32][kSgC];
+  const int o = blockIdx.x, c = threadIdx.x & 31, sh = threadIdx.x >> 5;
+  double sum = 0.0;
+#pragma unroll 8
+  for (int p = sh; p < P; p += 32) sum += part[(int64_t)p * kSgThin + o * kSgC + c];
+  red[sh][c] = sum;
+  __syncthreads();
+  if (sh) return;
+  sum = 0.0;
+  for (int k = 0; k < 32; ++k) sum += red[k][c];
+  if (o < 27)
+    w[c * 27 + (reversed ? 26 - o : o)] = (float)sum;
+  else if (bias)
+    bias[c] = (float)sum;
+}
+
 // Sum of the weight-gradient partial sums part[P][27][C][C] into a layer's
-// W[co][ci][27] (ci < Ci, co < Co). A workgroup takes 64 consecutive partial
-// entries (contiguous loads) and four quarters of the P sums; the quarters
-// are added in a fixed order (FP64 throughout).
-__global__ __launch_bounds__(256) void k_sg_reduce_w(int P, const float* __restrict__ part, int Ci,
-                                                      int Co, float* __restrict__ dst) {
+// W[co][ci][27]. A workgroup takes 64 consecutive partial entries (contiguous
+// loads) and four quarters of the P sums; the quarters are added in a fixed
+// order (FP64 throughout).
+__global__ __launch_bounds__(256) void k_sg_reduce_w(int P, const float* __restrict__ part,
+                                                      float* __restrict__ dst) {
   __shared__ double red[4][64];
   const int el = threadIdx.x & 63, qt = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + el;
   const int o = e / (kSgC * kSgC), co = (e / kSgC) % kSgC, ci = e % kSgC;
-  const bool used = e < 27 * kSgC * kSgC && co < Co && ci < Ci;
   double sum = 0.0;
-  if (used) {
 #pragma unroll 8
-    for (int p = qt; p < P; p += 4) sum += part[(int64_t)p * (27 * kSgC * kSgC) + e];
-  }
+  for (int p = qt; p < P; p += 4) sum += part[(int64_t)p * (27 * kSgC * kSgC) + e];
   red[qt][el] = sum;
   __syncthreads();
-  if (qt == 0 && used)
-    dst[(co * Ci + ci) * 27 + o] = (float)(((red[0][el] + red[1][el]) + red[2][el]) + red[3][el]);
+  if (qt == 0)
+    dst[(co * kSgC + ci) * 27 + o] = (float)(((red[0][el] + red[1][el]) + red[2][el]) + red[3][el]);
 }
 
-// Column sums of g[V][C] (C divides 256): partial per workgroup -> part[P][C].
-__global__ __launch_bounds__(kT) void k_sg_colsum(int64_t V, int C, const float* __restrict__ g,
+// Column sums of g[V][C]: partial per workgroup -> part[P][C].
+__global__ __launch_bounds__(kT) void k_sg_colsum(int64_t V, const float* __restrict__ g,
                                                    float* __restrict__ part) {
+  constexpr int C = kSgC;
   __shared__ float red[kT];
   const int t = threadIdx.x, c = t % C, grp = t / C, ng = kT / C;
   float acc = 0.f;
@@ -427,25 +522,20 @@ __global__ __launch_bounds__(kT) void k_sg_colsum(int64_t V, int C, const float*
   }
 }
 
-// dst[i] = sum_p part[p * n + src(i)], src(i) = (i / run) * stride + i % run:
-// one workgroup per output, the P partial sums split over its threads and
-// added by a fixed-order tree (FP64)
-__global__ __launch_bounds__(256) void k_sg_reduce(int P, int64_t n, const float* __restrict__ part,
-                                                    int64_t count, int run, int64_t stride,
+// dst[i] = sum_p part[p * n + i]: one workgroup per output, the P partial
+// sums split over its threads and added by a fixed-order tree (FP64)
+__global__ __launch_bounds__(256) void k_sg_reduce(int P, int n, const float* __restrict__ part,
                                                     float* __restrict__ dst) {
   __shared__ double red[256];
-  const int64_t i = blockIdx.x;
-  if (i >= count) return;  // the same for the whole workgroup
-  const int64_t src = (i / run) * stride + i % run;
   double sum = 0.0;
-  for (int p = threadIdx.x; p < P; p += blockDim.x) sum += part[(int64_t)p * n + src];
+  for (int p = threadIdx.x; p < P; p += blockDim.x) sum += part[(int64_t)p * n + blockIdx.x];
   red[threadIdx.x] = sum;
   __syncthreads();
   for (int w = blockDim.x / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) dst[i] = (float)red[0];
+  if (threadIdx.x == 0) dst[blockIdx.x] = (float)red[0];
 }
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -459,32 +549,43 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return red[0];
 }
 
-// Mean-squared loss against t tscale: gy = dL/dy = 2 (y - t tscale) / V
-// (also into channel 0 of gpad), per-workgroup sums of squares to part.
+// Mean-squared loss against t tscale: gy = dL/dy = 2 (y - t tscale) / V;
+// per-workgroup sums of squares to part[0 .. P) and of gy to part[P .. 2 P).
 __global__ __launch_bounds__(kT) void k_sg_loss(int64_t V, const float* __restrict__ y,
                                                  const float* __restrict__ tg, float tscale,
-                                                 float* __restrict__ gy, float* __restrict__ gpad,
+                                                 float* __restrict__ gy,
                                                  double* __restrict__ part) {
   __shared__ double red[kT];
-  double s = 0.0;
+  double s = 0.0, sg = 0.0;
   const float k = 2.f / (float)V;
   for (int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x; v < V; v += (int64_t)gridDim.x * kT) {
-    const float d = y[v] - tg[v] * tscale;
+    const float d = y[v] - tg[v] * tscale, kd = k * d;
     s += (double)d * d;
-    gy[v] = k * d;
-    gpad[v * kSgC] = k * d;
+    sg += (double)kd;
+    gy[v] = kd;
   }
   s = block_sum(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  __syncthreads();
+  sg = block_sum(sg, red);
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = s;
+    part[gridDim.x + blockIdx.x] = sg;
+  }
 }
 
-__global__ __launch_bounds__(kT) void k_sg_sumd(int P, const double* __restrict__ part,
-                                                 double scale, double* __restrict__ out) {
+// block 0: the loss, the mean of squares; block 1: the last layer's bias gradient
+__global__ __launch_bounds__(kT) void k_sg_loss_sum(int P, const double* __restrict__ part,
+                                                     double scale, double* __restrict__ loss,
+                                                     float* __restrict__ bias) {
   __shared__ double red[kT];
   double s = 0.0;
-  for (int p = threadIdx.x; p < P; p += kT) s += part[p];
+  for (int p = threadIdx.x; p < P; p += kT) s += part[(int64_t)blockIdx.x * P + p];
   s = block_sum(s, red);
-  if (threadIdx.x == 0) *out = s * scale;
+  if (threadIdx.x) return;
+  if (blockIdx.x == 0)
+    *loss = s * scale;
+  else
+    *bias = (float)s;
 }
 
 // per-workgroup sums of |a - b|^2 (b may be null: |a|^2) and |b|^2
@@ -505,11 +606,6 @@ __global__ __launch_bounds__(kT) void k_sg_sq2(int64_t n, const float* __restric
     part[2 * blockIdx.x] = s0;
     part[2 * blockIdx.x + 1] = s1;
   }
-}
-
-__global__ void k_sg_pad(int64_t V, const float* __restrict__ x, float xs, float* __restrict__ dst) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < V) dst[v * kSgC] = x[v] * xs;
 }
 
 __global__ void k_sg_adam(int64_t n, float* __restrict__ p, const float* __restrict__ g,
@@ -649,8 +745,8 @@ void forward(Surrogate* s, hipStream_t st, const float* Q, bool train, float* yo
   if (ev) (void)hipEventRecord(ev[2 * D - 1], st);
 }
 
-// weight and bias gradients of a layer from its output gradient g [V][C]
-// (channel 0 only for the last layer) and its input a [V][C]
+// weight and bias gradients of a middle layer from its output gradient g
+// [V][C] and its input a [V][C]
 void layer_grads(Surrogate* s, hipStream_t st, int l, const float* g, const float* a) {
   const SgGrid& gd = s->gd;
   const int ntiles = (int)tile_grid(gd).x * gd.nz;
@@ -658,19 +754,23 @@ void layer_grads(Surrogate* s, hipStream_t st, int l, const float* g, const floa
   const int64_t nW = (int64_t)kSgC * kSgC * 27;
   hipLaunchKernelGGL(k_sg_wgrad, dim3((unsigned)P, 3), dim3(512), kSgWgradLds, st, gd, g, a,
                      s->part);
-  const int D = s->depth;
-  const int ci = l == 0 ? 1 : kSgC, co = l == D - 1 ? 1 : kSgC;
-  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)((nW + 63) / 64)), dim3(kT), 0, st, 2 * P,
-                     s->part, ci, co, s->grad + s->woff[l]);
+  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)(nW / 64)), dim3(kT), 0, st, 2 * P, s->part,
+                     s->grad + s->woff[l]);
   // bias: column sums of the output gradient
   float* bpart = s->part;  // reused after the reduction above (same stream)
-  if (co == 1) {
-    hipLaunchKernelGGL(k_sg_colsum, dim3(kRedBlocks), dim3(kT), 0, st, s->nvox, 1, s->gy, bpart);
-  } else {
-    hipLaunchKernelGGL(k_sg_colsum, dim3(kRedBlocks), dim3(kT), 0, st, s->nvox, kSgC, g, bpart);
-  }
-  hipLaunchKernelGGL(k_sg_reduce, dim3((unsigned)co), dim3(kT), 0, st, kRedBlocks, (int64_t)co, bpart,
-                     (int64_t)co, co, (int64_t)0, s->grad + s->boff[l]);
+  hipLaunchKernelGGL(k_sg_colsum, dim3(kRedBlocks), dim3(kT), 0, st, s->nvox, g, bpart);
+  hipLaunchKernelGGL(k_sg_reduce, dim3((unsigned)kSgC), dim3(kT), 0, st, kRedBlocks, kSgC, bpart,
+                     s->grad + s->boff[l]);
+}
+
+// weight gradient of the first (l = 0, with its bias) or last layer from its
+// 32-channel array a and its one-channel array x, scaled by xs
+void thin_grads(Surrogate* s, hipStream_t st, int l, const float* a, const float* x, float xs) {
+  const SgGrid& gd = s->gd;
+  const int P = std::min(kSgWPart, (int)tile_grid(gd).x * gd.nz);
+  hipLaunchKernelGGL(k_sg_wgrad_thin, dim3((unsigned)P), dim3(kT), 0, st, gd, a, x, xs, s->part);
+  hipLaunchKernelGGL(k_sg_reduce_thin, dim3(l == 0 ? 28 : 27), dim3(1024), 0, st, P, s->part,
+                     (int)(l != 0), s->grad + s->woff[l], l == 0 ? s->grad + s->boff[0] : nullptr);
 }
 
 }  // namespace
@@ -723,13 +823,12 @@ hipError_t sg_ensure_training(Surrogate* s, int n_loss) {
     const int64_t nb = (int64_t)std::max(2, s->depth - 1) * s->nvox * kSgC;
     const int64_t vc = s->nvox * kSgC;
     if ((e = alloc(&s->act, nb)) || (e = alloc(&s->gA, vc)) || (e = alloc(&s->gB, vc)) ||
-        (e = alloc(&s->xpad, vc)) || (e = alloc(&s->gpad, vc)) || (e = alloc(&s->y, s->nvox)) ||
+        (e = alloc(&s->y, s->nvox)) ||
         (e = alloc(&s->gy, s->nvox)) || (e = alloc(&s->qbuf, s->nvox)) ||
         (e = alloc(&s->ubuf, s->nvox)) ||
         (e = alloc(&s->part, std::max<int64_t>((int64_t)kSgWPart * kSgC * kSgC * 27,
                                                (int64_t)kRedBlocks * kSgC))))
       return e;
-    if ((e = hipMemset(s->xpad, 0, vc * 4)) || (e = hipMemset(s->gpad, 0, vc * 4))) return e;
     s->trained_buffers = true;
   }
   if (n_loss > s->loss_cap) {
@@ -744,7 +843,7 @@ hipError_t sg_ensure_training(Surrogate* s, int n_loss) {
 
 void sg_destroy(Surrogate* s) {
   void* bufs[] = {s->p,   s->grad, s->m1,   s->m2,   s->wmid, s->wmidt, s->win, s->wout,
-                  s->woutt, s->act, s->gA,  s->gB,   s->xpad, s->gpad, s->y,    s->gy,
+                  s->woutt, s->act, s->gA,  s->gB,   s->y,    s->gy,
                   s->qbuf, s->ubuf, s->part, s->dred, s->loss, s->pos,  s->m64, s->m32,
                   s->ha,  s->hs};
   for (void* b : bufs)
@@ -831,13 +930,12 @@ hipError_t sg_loss_grad(Surrogate* s, hipStream_t st, const float* Q, const floa
   const SgGrid& gd = s->gd;
   const dim3 grid = tile_grid(gd);
   forward(s, st, Q, true, s->y, 1.f);
-  hipLaunchKernelGGL(k_sg_pad, dim3(blocks(s->nvox)), dim3(kT), 0, st, s->nvox, Q, s->s_in, s->xpad);
   hipLaunchKernelGGL(k_sg_loss, dim3(kRedBlocks), dim3(kT), 0, st, s->nvox, s->y, tg, tscale, s->gy,
-                     s->gpad, s->dred);
-  hipLaunchKernelGGL(k_sg_sumd, dim3(1), dim3(kT), 0, st, kRedBlocks, s->dred,
-                     1.0 / (double)s->nvox, s->loss + slot);
+                     s->dred);
+  hipLaunchKernelGGL(k_sg_loss_sum, dim3(2), dim3(kT), 0, st, kRedBlocks, s->dred,
+                     1.0 / (double)s->nvox, s->loss + slot, s->grad + s->boff[D - 1]);
   // last layer
-  layer_grads(s, st, D - 1, s->gpad, act_of(s, D - 2, true));
+  thin_grads(s, st, D - 1, act_of(s, D - 2, true), s->gy, 1.f);
   hipLaunchKernelGGL(k_sg_in, grid, dim3(kT), 0, st, gd, s->gy, 1.f, s->woutt, (const float*)nullptr,
                      s->gB, 0, act_of(s, D - 2, true));
   float *gcur = s->gB, *gnext = s->gA;
@@ -847,7 +945,7 @@ hipError_t sg_loss_grad(Surrogate* s, hipStream_t st, const float* Q, const floa
                act_of(s, l - 1, true));
     std::swap(gcur, gnext);
   }
-  layer_grads(s, st, 0, gcur, s->xpad);
+  thin_grads(s, st, 0, gcur, Q, s->s_in);
   return hipGetLastError();
 }
 

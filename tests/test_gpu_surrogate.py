@@ -234,6 +234,62 @@ def test_gradients_match_oracle(ctx, depth):
         assert eW <= 1e-4 and eb <= 1e-4, (l, eW, eb)
 
 
+def float64_gradients(q, t, ps):
+    """Loss and gradients of the network in 64-bit torch, [nz][ny][nx] grids."""
+    leaves = [(torch.tensor(W, device="cuda").requires_grad_(),
+               torch.tensor(b, device="cuda").requires_grad_()) for W, b in ps]
+    x, nz = q.double()[..., None], q.shape[0]
+    for l, (W, b) in enumerate(leaves):
+        pad = torch.nn.functional.pad(x, (0, 0, 0, 0, 0, 0, 1, 1))
+        y = b
+        for o in range(27):
+            dz, dy, dx = o // 9 - 1, o // 3 % 3 - 1, o % 3 - 1
+            s = torch.roll(pad[1 + dz:1 + dz + nz], (-dy, -dx), (1, 2))
+            y = y + s @ W.reshape(W.shape[0], W.shape[1], 27)[:, :, o].T
+        x = torch.relu(y) if l + 1 < len(ps) else y
+    loss = (x[..., 0] - t.double()).square().mean()
+    g = torch.autograd.grad(loss, [v for pair in leaves for v in pair])
+    return float(loss.detach()), [(g[2 * l].cpu().numpy(), g[2 * l + 1].cpu().numpy())
+                         for l in range(len(ps))]
+
+
+@pytest.mark.parametrize("grid,depth", [((32, 16, 4), 3), ((35, 18, 5), 3), ((256, 250, 9), 3),
+                                        ((256, 250, 9), 2)])
+def test_gradients_over_many_tiles(grid, depth):
+    """Whole tiles, ragged ones, and 2 304 tiles, of which a workgroup
+    of the weight-gradient kernels takes several. Every channel's bias exceeds
+    what its inputs can add up to, with alternating sign, so both sides take
+    the same ReLU decisions, and inputs and targets have one sign, so no sum
+    over the points cancels: a partial sum in 32 bits of at most 16 points in
+    each of 9 tiles, or 8 x 36 of the middle layer, is off by less than
+    300 * 2^-24 = 2e-5 of it."""
+    c = B.Context.from_problem(film(grid), device=0)
+    try:
+        c.surrogate_init(depth, seed=3)
+        rng = np.random.default_rng(23)
+        ps, hmax = random_params(rng, depth, bias_sd=0.0), 1.0
+        for l in range(depth - 1):
+            W = ps[l][0]
+            reach = hmax * np.abs(W).sum(axis=(1, 2, 3, 4))
+            b = np.where(np.arange(C) % 2 == 0, 1.1, -1.1) * reach
+            b = b.astype(np.float32).astype(np.float64)
+            ps[l], hmax = (W, b), (b + reach).max()
+        c.surrogate_set_params(flat(ps), scales=(1.0, 1.0))
+        shape = c._grid_shape()
+        assert shape == grid[::-1]
+        q = torch.tensor(rng.uniform(0.5, 1.0, shape).astype(np.float32), device="cuda")
+        t = torch.zeros_like(q)
+        print(f"[gpu surrogate] gradients grid {shape}, depth {depth}", flush=True)
+        loss, g = c.surrogate_loss_grad(q, t)
+        loss64, g64 = float64_gradients(q, t, ps)
+        assert abs(loss - loss64) <= 1e-5 * loss64
+        for (gW, gb), (kW, kb) in zip(g64, unflat(g.astype(np.float64), depth)):
+            assert np.abs(kW - gW).max() <= 1e-4 * np.abs(gW).max()
+            assert np.abs(kb - gb).max() <= 1e-4 * np.abs(gb).max()
+    finally:
+        c.close()
+
+
 def test_textures(ctx):
     n = ctx.n
     m = torch.empty((n, 3), dtype=torch.float64, device="cuda")
