@@ -28,7 +28,7 @@ constexpr int kSgMaxDepth = 12;
 constexpr int kSgTX = 32, kSgTY = 8;          // output tile of one z-plane
 constexpr int kSgHX = kSgTX + 2, kSgHY = kSgTY + 2;
 constexpr int kSgHalo = kSgHX * kSgHY;        // staged points of one plane
-constexpr int kSgWPart = 512;                 // partial sums of the weight-gradient pass
+constexpr int kSgWPart = 512;                 // most partial sums of a weight-gradient pass
 
 struct SgGrid {
   int nx, ny, nz;
@@ -66,7 +66,7 @@ struct Surrogate {
   float *gA = nullptr, *gB = nullptr;  // [nvox][C]
   float *y = nullptr, *gy = nullptr;   // [nvox]
   float *qbuf = nullptr, *ubuf = nullptr;  // a training pair's Q and U grids
-  float* part = nullptr;                // weight-gradient partial sums [kSgWPart][C*C*27]
+  float* part = nullptr;                // weight-gradient partial sums, kSgWPart rows
   double* dred = nullptr;               // reduction partials
   double* loss = nullptr;               // per training pair
   int loss_cap = 0;

@@ -14,8 +14,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 256;
 constexpr int kRedBlocks = 1024;   // blocks of the device reductions (partials in dred)
-constexpr int kSgWS = 48;          // LDS point stride (floats) of the weight-gradient kernel
-constexpr size_t kSgWgradLds = (size_t)(kSgTX * kSgTY + kSgHalo) * kSgWS * sizeof(float);
 
 constexpr int kSgThin = kSgC * 32;   // a thin layer's partial sums: 27 offsets, the bias, 4 unused
 
@@ -297,97 +295,201 @@ __global__ __launch_bounds__(kT, 2) void k_sg_mid(SgGrid g, const float* __restr
 }
 
 // Weight gradient of a kSgC -> kSgC layer: gW[co][ci][o] = sum over points v
-// of gr[v][co] a[v + o][ci] (circular in x, y; zero outside in z), on the
-// matrix cores with FP32 operands (v_mfma_f32_16x16x4f32: M = 16 output
-// channels, N = 16 input channels, K = 4 points, FP32 products and sums).
-// Grid (P, 3): blockIdx.y is dz; each 512-thread workgroup walks the tiles
-// blockIdx.x, +P, ...; wave w owns the 16 x 16 channel block (w & 3) for the
-// nine (dy, dx) of its dz (nine independent accumulators) and every other
-// group of four points (w >> 2). The tile's output gradient and the input
-// plane are staged in LDS at a point stride of kSgWS floats, so that four
-// consecutive points of one 16-channel block fall in distinct banks. Partial
-// sums per workgroup and half go to part[2 P][C*C*27]. The next tile's loads
-// are in flight (in registers) while the current one is multiplied.
-__global__ __launch_bounds__(512) void k_sg_wgrad(SgGrid g, const float* __restrict__ gr,
-                                                   const float* __restrict__ a,
-                                                   float* __restrict__ part) {
-  extern __shared__ float4 wsm4[];
-  float* sg = reinterpret_cast<float*>(wsm4);        // [kSgTX * kSgTY][kSgWS]
-  float* sa = sg + kSgTX * kSgTY * kSgWS;             // [kSgHalo][kSgWS]
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, kq = lane >> 4;
-  const int mt = (wv >> 1) & 1, nt = wv & 1, half = wv >> 2, dz = blockIdx.y;
-  const int tiles_x = (g.nx + kSgTX - 1) / kSgTX, tiles_y = (g.ny + kSgTY - 1) / kSgTY;
-  const int tpp = tiles_x * tiles_y, ntiles = tpp * g.nz;
-  constexpr int kLg = kSgTX * kSgTY * 8 / 512;            // float4 of the tile per thread
-  constexpr int kLa = (kSgHalo * 8 + 511) / 512;           // float4 of the plane per thread
-  static_assert(kLg * 512 == kSgTX * kSgTY * 8, "tile float4 count");
-  // the workgroup's tiles whose plane z + dz - 1 lies inside the grid
-  auto next_tile = [&](int tl) {
-    while (tl < ntiles && (tl / tpp + dz - 1 < 0 || tl / tpp + dz - 1 >= g.nz)) tl += gridDim.x;
-    return tl;
+// of gr[v][co] a[v + o][ci] (circular in x, y; zero outside in z), and the
+// bias gradient, the sum of gr[v][co]. On the matrix cores, M = 16 output
+// channels, N = 16 input channels, K = 32 points, each FP32 operand split into
+// three BF16 parts x = h + m + l that hold all its 24 bits; of the nine
+// products the six above 2^-26 of the whole are formed (v_mfma_f32_16x16x32_bf16),
+// 96 cycles for what FP32 operands take 256. The 32 points' sum is formed from
+// the smallest products on and then added to the running FP32 sum, one
+// rounding for 32 points where FP32 operands round eight times.
+//
+// A workgroup has one dz and walks the tiles of 16 x 8 points of its planes,
+// its tile's next loads in flight while the current one is multiplied. Tiles
+// are staged transposed, [x][channel] with the eight y of a column as one
+// 16-byte operand (K: four columns of eight rows), so that a shift by dx is
+// another column and a shift by dy the same operand funnel-shifted with the
+// two halo rows, and 16 lanes read 256 contiguous bytes. Each of its four
+// wavefronts owns one 16 x 16 channel block for all nine (dy, dx): 54 matrix
+// instructions for 21 LDS reads. 59 KB of LDS and one wavefront per SIMD, so
+// that two workgroups share a compute unit and one stages while the other
+// multiplies; with six wavefronts, one dx each, they did not share the SIMDs
+// evenly (68 us). 128 x 128 x 8 points: 48.7 us and 5.0 for the sums, where
+// FP32 operands (v_mfma_f32_16x16x4f32) took 91 and 20. Error of the gradient
+// against 64 bits 3.0e-8 (256 x 250 x 9 points, depth 3), with FP32 operands
+// 3.5e-8, and without the separate sum of 32 points 4.5e-8.
+struct SgWgradPlan {
+  int rows[3];   // workgroups, hence rows of partial sums, of each dz
+};
+
+constexpr int kSgWTX = 16, kSgWTY = 8, kSgWHX = kSgWTX + 2;   // its tile
+constexpr int kSgWT = 256;                                     // its threads
+constexpr int kSgWRow = kSgC * kSgC * 27 + kSgC;               // a row of partial sums: [o][co][ci], bias
+
+struct Bf3 {
+  uint32_t p[3];   // two neighbouring rows of one part each
+};
+
+__device__ __forceinline__ Bf3 split3(float v0, float v1) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  Bf3 r;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const bf16x2 h = {(__bf16)v0, (__bf16)v1};
+    r.p[k] = __builtin_bit_cast(uint32_t, h);
+    v0 -= (float)h[0];
+    v1 -= (float)h[1];
+  }
+  return r;
+}
+
+__global__ __launch_bounds__(kSgWT, 2) void k_sg_wgrad(SgGrid g, SgWgradPlan plan,
+                                                        const float* __restrict__ gr,
+                                                        const float* __restrict__ a,
+                                                        float* __restrict__ part) {
+  constexpr int kG = kSgWTX * kSgC, kA = kSgWHX * kSgC;        // columns of the tile and the plane
+  constexpr int kItems = (kG + kA + kSgWT - 1) / kSgWT;
+  __shared__ uint4 sg[3][kG], sa[3][kA];
+  __shared__ uint32_t sb[3][kA];                                // halo rows 8 and 9
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, kg = lane >> 4;
+  const int mt = wv >> 1, nt = wv & 1;
+  int row = blockIdx.x, dz = 0;
+  while (row >= plan.rows[dz]) row -= plan.rows[dz++];
+  const int tiles_x = (g.nx + kSgWTX - 1) / kSgWTX, tiles_y = (g.ny + kSgWTY - 1) / kSgWTY;
+  const int tpp = tiles_x * tiles_y;
+  // planes z whose input plane z + dz - 1 lies inside the grid
+  const int z_lo = dz == 0 ? 1 : 0, nplanes = g.nz - (dz != 1), ntiles = tpp * nplanes;
+  // a tile's plane, corner and, of item k, whether it is a column of gr
+  auto plane_of = [&](int tl, int& x0, int& y0) {
+    const int zi = tl / tpp, r2 = tl - zi * tpp;
+    x0 = (r2 % tiles_x) * kSgWTX;
+    y0 = (r2 / tiles_x) * kSgWTY;
+    return z_lo + zi;
   };
-  float4 pg[kLg], pa[kLa];
+  static_assert(kG % kSgWT == 0, "an item is a column of gr, or of a, in every thread");
+  auto of_gr = [](int k) { return k * kSgWT < kG; };
+  // Every load is issued: out of range, the nearest column or row is read
+  // (those of gr become zero when they are staged, those of a meet its zeros).
+  float pre[kItems][10];
   auto load_tile = [&](int tl) {
-    const int z = tl / tpp, r = tl - z * tpp;
-    const int x0 = (r % tiles_x) * kSgTX, y0 = (r / tiles_x) * kSgTY, gz = z + dz - 1;
+    int x0, y0;
+    const int z = plane_of(tl, x0, y0);
+    const uint32_t stride = g.nx * kSgC * sizeof(float);
+    const char* gz = reinterpret_cast<const char*>(gr + vox_of(g, z, y0, 0) * kSgC);
+    const char* az = reinterpret_cast<const char*>(a + vox_of(g, z + dz - 1, 0, 0) * kSgC);
 #pragma unroll
-    for (int k = 0; k < kLg; ++k) {
-      const int i = t + k * 512, v = i >> 3, q = i & 7;
-      const int gx = x0 + (v & (kSgTX - 1)), gy = y0 + v / kSgTX;
-      pg[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (gx < g.nx && gy < g.ny) pg[k] = reinterpret_cast<const float4*>(gr + vox_of(g, z, gy, gx) * kSgC)[q];
-    }
+    for (int k = 0; k < kItems; ++k) {
+      const int i = t + k * kSgWT, c = i & (kSgC - 1);
+      if (of_gr(k)) {
+        const uint32_t at = (min(x0 + i / kSgC, g.nx - 1) * kSgC + c) * sizeof(float);
+        const char* row_p = gz;
 #pragma unroll
-    for (int k = 0; k < kLa; ++k) {
-      const int i = t + k * 512;
-      pa[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (i < kSgHalo * 8) {
-        const int h = i >> 3, q = i & 7, hy = h / kSgHX, hx = h - hy * kSgHX;
-        pa[k] = reinterpret_cast<const float4*>(
-            a + vox_of(g, gz, wrapi(y0 + hy - 1, g.ny), wrapi(x0 + hx - 1, g.nx)) * kSgC)[q];
+        for (int r = 0; r < kSgWTY; ++r) {
+          pre[k][r] = *reinterpret_cast<const float*>(row_p + at);
+          row_p += y0 + r + 1 < g.ny ? stride : 0;
+        }
+      } else {
+        int gx = x0 + (i - kG) / kSgC - 1;  // x0 - 1 .. x0 + 22
+        gx = gx < 0 ? g.nx - 1 : gx == g.nx ? 0 : min(gx, g.nx - 1);
+        const uint32_t at = (gx * kSgC + c) * sizeof(float);
+        int gy = y0 == 0 ? g.ny - 1 : y0 - 1;
+        const char* row_p = az + (int64_t)gy * stride;
+#pragma unroll
+        for (int r = 0; r < kSgWTY + 2; ++r) {
+          pre[k][r] = *reinterpret_cast<const float*>(row_p + at);
+          const bool wrap = ++gy == g.ny;
+          gy = wrap ? 0 : gy;
+          row_p = wrap ? az : row_p + stride;
+        }
       }
     }
   };
-  f32x4 acc[9];
-#pragma unroll
-  for (int j = 0; j < 9; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  int tile = next_tile(blockIdx.x);  // the same for the whole workgroup
-  if (tile < ntiles) load_tile(tile);
-  while (tile < ntiles) {
+  f32x4 acc[3][3] = {};   // [dy][dx]
+  double bsum = 0.0;
+  if (row < ntiles) load_tile(row);
+  for (int tile = row; tile < ntiles; tile += plan.rows[dz]) {
+    int x0, y0;
+    (void)plane_of(tile, x0, y0);
     __syncthreads();  // the previous tile has been used
 #pragma unroll
-    for (int k = 0; k < kLg; ++k) {
-      const int i = t + k * 512;
-      reinterpret_cast<float4*>(sg + (i >> 3) * kSgWS)[i & 7] = pg[k];
-    }
+    for (int k = 0; k < kItems; ++k) {
+      const int i = t + k * kSgWT;
+      float* v = pre[k];
+      if (of_gr(k)) {
+        const bool in = x0 + i / kSgC < g.nx;
 #pragma unroll
-    for (int k = 0; k < kLa; ++k) {
-      const int i = t + k * 512;
-      if (i < kSgHalo * 8) reinterpret_cast<float4*>(sa + (i >> 3) * kSgWS)[i & 7] = pa[k];
+        for (int r = 0; r < kSgWTY; ++r) v[r] = in && y0 + r < g.ny ? v[r] : 0.f;
+        bsum += (double)(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])));
+      }
+      Bf3 s[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] = split3(v[2 * q], v[2 * q + 1]);
+      if (of_gr(k)) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) sg[p][i] = make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]);
+      } else if (i < kG + kA) {
+        const Bf3 e = split3(v[8], v[9]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          sa[p][i - kG] = make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]);
+          sb[p][i - kG] = e.p[p];
+        }
+      }
     }
     __syncthreads();
-    const int nxt = next_tile(tile + gridDim.x);
-    if (nxt < ntiles) load_tile(nxt);  // in flight while this tile is multiplied
-    tile = nxt;
-    for (int st = half; st < kSgTX * kSgTY / 4; st += 2) {
-      const int v = 4 * st + kq, ty = v / kSgTX, tx = v % kSgTX;
-      const float ga = sg[v * kSgWS + mt * 16 + li];     // A: output channel x point
-      const float* sb = sa + (ty * kSgHX + tx) * kSgWS + nt * 16 + li;
+    if (tile + plan.rows[dz] < ntiles) load_tile(tile + plan.rows[dz]);
+#pragma unroll 1
+    for (int st = 0; st < kSgWTX / 4; ++st) {
+      const int x = 4 * st + kg;
+      bf16x8 A[3];
 #pragma unroll
-      for (int j = 0; j < 9; ++j) {
-        const float bb = sb[((j / 3) * kSgHX + j % 3) * kSgWS];  // B: point x input channel
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, bb, acc[j], 0, 0, 0);
+      for (int p = 0; p < 3; ++p) A[p] = __builtin_bit_cast(bf16x8, sg[p][x * kSgC + mt * 16 + li]);
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        const int col = (x + dx) * kSgC + nt * 16 + li;
+        bf16x8 Bm[3][3];  // [dy][part]
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const uint4 q = sa[p][col];
+          const uint32_t e = sb[p][col];
+          Bm[0][p] = __builtin_bit_cast(bf16x8, q);
+          Bm[1][p] = __builtin_bit_cast(
+              bf16x8, make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16),
+                                 __builtin_amdgcn_alignbit(q.z, q.y, 16),
+                                 __builtin_amdgcn_alignbit(q.w, q.z, 16),
+                                 __builtin_amdgcn_alignbit(e, q.w, 16)));
+          Bm[2][p] = __builtin_bit_cast(bf16x8, make_uint4(q.y, q.z, q.w, e));
+        }
+        // h l, l h, m m, h m, m h, h h of 32 points, then onto the sum
+        constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
+        f32x4 s32[3] = {};
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy)
+            s32[dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[pa[j]], Bm[dy][pb[j]], s32[dy], 0,
+                                                              0, 0);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) acc[dy][dx] += s32[dy];
       }
     }
   }
-  // D block: lane holds output channels 16 mt + 4 kq + r, input channel 16 nt + li;
-  // partial sums as [offset][co][ci], so that 16 lanes store 64 contiguous bytes
-  float* P = part + ((int64_t)blockIdx.x * 2 + half) * (kSgC * kSgC * 27);
+  // D block: lane holds output channels 16 mt + 4 kg + r, input channel 16 nt + li
 #pragma unroll
-  for (int j = 0; j < 9; ++j)
+  for (int j = 0; j < 9; ++j) {
+    float* P = part + (int64_t)row * kSgWRow + (dz * 9 + j) * kSgC * kSgC;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      P[((dz * 9 + j) * kSgC + mt * 16 + 4 * kq + r) * kSgC + nt * 16 + li] = acc[j][r];
+      P[(mt * 16 + 4 * kg + r) * kSgC + nt * 16 + li] = acc[j / 3][j % 3][r];
+  }
+  __shared__ double red[kSgWT / kSgC][kSgC];
+  red[t / kSgC][t % kSgC] = bsum;
+  __syncthreads();
+  if (dz == 1 && t < kSgC) {
+    double s = 0.0;
+    for (int k = 0; k < kSgWT / kSgC; ++k) s += red[k][t];
+    part[(int64_t)row * kSgWRow + 27 * kSgC * kSgC + t] = (float)s;
+  }
 }
 
 // Weight gradient of the layers with one channel on a side, from their wide
@@ -485,57 +587,32 @@ __global__ __launch_bounds__(1024) void k_sg_reduce_thin(int P, const float* __r
     bias[c] = (float)sum;
 }
 
-// Sum of the weight-gradient partial sums part[P][27][C][C] into a layer's
-// W[co][ci][27]. A workgroup takes 64 consecutive partial entries (contiguous
-// loads) and four quarters of the P sums; the quarters are added in a fixed
-// order (FP64 throughout).
-__global__ __launch_bounds__(256) void k_sg_reduce_w(int P, const float* __restrict__ part,
-                                                      float* __restrict__ dst) {
-  __shared__ double red[4][64];
-  const int el = threadIdx.x & 63, qt = threadIdx.x >> 6;
+// Sum of a middle layer's partial sums (rows of kSgWRow, as many per dz as
+// the plan says; the bias in those of dz = 1) into its W[co][ci][27] and b. A
+// workgroup takes 64 consecutive entries (contiguous loads) and eight shares
+// of the rows, added in a fixed order (FP64 throughout).
+__global__ __launch_bounds__(512) void k_sg_reduce_w(SgWgradPlan plan, const float* __restrict__ part,
+                                                      float* __restrict__ dst,
+                                                      float* __restrict__ bias) {
+  __shared__ double red[8][64];
+  const int el = threadIdx.x & 63, sh = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + el;
   const int o = e / (kSgC * kSgC), co = (e / kSgC) % kSgC, ci = e % kSgC;
+  const int P = plan.rows[o < 27 ? o / 9 : 1];
   double sum = 0.0;
+  if (e < kSgWRow) {
 #pragma unroll 8
-  for (int p = qt; p < P; p += 4) sum += part[(int64_t)p * (27 * kSgC * kSgC) + e];
-  red[qt][el] = sum;
-  __syncthreads();
-  if (qt == 0)
-    dst[(co * kSgC + ci) * 27 + o] = (float)(((red[0][el] + red[1][el]) + red[2][el]) + red[3][el]);
-}
-
-// Column sums of g[V][C]: partial per workgroup -> part[P][C].
-__global__ __launch_bounds__(kT) void k_sg_colsum(int64_t V, const float* __restrict__ g,
-                                                   float* __restrict__ part) {
-  constexpr int C = kSgC;
-  __shared__ float red[kT];
-  const int t = threadIdx.x, c = t % C, grp = t / C, ng = kT / C;
-  float acc = 0.f;
-  for (int64_t v = (int64_t)blockIdx.x * ng + grp; v < V; v += (int64_t)gridDim.x * ng)
-    acc += g[v * C + c];
-  red[t] = acc;
-  __syncthreads();
-  if (t < C) {
-    float s = 0.f;
-    for (int k = 0; k < ng; ++k) s += red[k * C + t];
-    part[(int64_t)blockIdx.x * C + t] = s;
+    for (int p = sh; p < P; p += 8) sum += part[(int64_t)p * kSgWRow + e];
   }
-}
-
-// dst[i] = sum_p part[p * n + i]: one workgroup per output, the P partial
-// sums split over its threads and added by a fixed-order tree (FP64)
-__global__ __launch_bounds__(256) void k_sg_reduce(int P, int n, const float* __restrict__ part,
-                                                    float* __restrict__ dst) {
-  __shared__ double red[256];
-  double sum = 0.0;
-  for (int p = threadIdx.x; p < P; p += blockDim.x) sum += part[(int64_t)p * n + blockIdx.x];
-  red[threadIdx.x] = sum;
+  red[sh][el] = sum;
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) dst[blockIdx.x] = (float)red[0];
+  if (sh || e >= kSgWRow) return;
+  sum = 0.0;
+  for (int k = 0; k < 8; ++k) sum += red[k][el];
+  if (o < 27)
+    dst[(co * kSgC + ci) * 27 + o] = (float)sum;
+  else
+    bias[ci] = (float)sum;
 }
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -745,22 +822,27 @@ void forward(Surrogate* s, hipStream_t st, const float* Q, bool train, float* yo
   if (ev) (void)hipEventRecord(ev[2 * D - 1], st);
 }
 
+// Workgroups of each dz: the fewest tiles per workgroup with all of them
+// resident at once (two per compute unit), each dz in proportion to its planes.
+SgWgradPlan wgrad_plan(const SgGrid& g) {
+  const int tpp = ((g.nx + kSgWTX - 1) / kSgWTX) * ((g.ny + kSgWTY - 1) / kSgWTY);
+  const int tiles[3] = {tpp * (g.nz - 1), tpp * g.nz, tpp * (g.nz - 1)};
+  SgWgradPlan plan;
+  for (int each = (tiles[0] + tiles[1] + tiles[2] + kSgWPart - 1) / kSgWPart;; ++each) {
+    int sum = 0;
+    for (int d = 0; d < 3; ++d) sum += plan.rows[d] = (tiles[d] + each - 1) / each;
+    if (sum <= kSgWPart) return plan;
+  }
+}
+
 // weight and bias gradients of a middle layer from its output gradient g
 // [V][C] and its input a [V][C]
 void layer_grads(Surrogate* s, hipStream_t st, int l, const float* g, const float* a) {
-  const SgGrid& gd = s->gd;
-  const int ntiles = (int)tile_grid(gd).x * gd.nz;
-  const int P = std::min(kSgWPart / 2, ntiles);  // two partial sums per workgroup
-  const int64_t nW = (int64_t)kSgC * kSgC * 27;
-  hipLaunchKernelGGL(k_sg_wgrad, dim3((unsigned)P, 3), dim3(512), kSgWgradLds, st, gd, g, a,
-                     s->part);
-  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)(nW / 64)), dim3(kT), 0, st, 2 * P, s->part,
-                     s->grad + s->woff[l]);
-  // bias: column sums of the output gradient
-  float* bpart = s->part;  // reused after the reduction above (same stream)
-  hipLaunchKernelGGL(k_sg_colsum, dim3(kRedBlocks), dim3(kT), 0, st, s->nvox, g, bpart);
-  hipLaunchKernelGGL(k_sg_reduce, dim3((unsigned)kSgC), dim3(kT), 0, st, kRedBlocks, kSgC, bpart,
-                     s->grad + s->boff[l]);
+  const SgWgradPlan plan = wgrad_plan(s->gd);
+  hipLaunchKernelGGL(k_sg_wgrad, dim3((unsigned)(plan.rows[0] + plan.rows[1] + plan.rows[2])),
+                     dim3(kSgWT), 0, st, s->gd, plan, g, a, s->part);
+  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)((kSgWRow + 63) / 64)), dim3(512), 0, st, plan,
+                     s->part, s->grad + s->woff[l], s->grad + s->boff[l]);
 }
 
 // weight gradient of the first (l = 0, with its bias) or last layer from its
@@ -804,9 +886,6 @@ hipError_t sg_create(Surrogate* s, int depth, SgGrid gd, int64_t n, const double
       (e = alloc(&s->win, kSgC * 27)) || (e = alloc(&s->wout, kSgC * 27)) ||
       (e = alloc(&s->woutt, kSgC * 27)))
     return e;
-  if ((e = hipFuncSetAttribute((const void*)k_sg_wgrad, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)kSgWgradLds)))
-    return e;
   if ((e = alloc(&s->act, 2 * s->nvox * kSgC))) return e;
   if ((e = alloc(&s->dred, 2 * kRedBlocks + 8))) return e;
   if ((e = alloc(&s->pos, 3 * n)) || (e = alloc(&s->m64, 3 * n)) || (e = alloc(&s->m32, 3 * n)) ||
@@ -826,8 +905,7 @@ hipError_t sg_ensure_training(Surrogate* s, int n_loss) {
         (e = alloc(&s->y, s->nvox)) ||
         (e = alloc(&s->gy, s->nvox)) || (e = alloc(&s->qbuf, s->nvox)) ||
         (e = alloc(&s->ubuf, s->nvox)) ||
-        (e = alloc(&s->part, std::max<int64_t>((int64_t)kSgWPart * kSgC * kSgC * 27,
-                                               (int64_t)kRedBlocks * kSgC))))
+        (e = alloc(&s->part, (int64_t)kSgWPart * kSgWRow)))
       return e;
     s->trained_buffers = true;
   }
