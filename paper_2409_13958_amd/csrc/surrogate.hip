@@ -164,24 +164,80 @@ __global__ __launch_bounds__(kT) void k_sg_out(SgGrid g, const float* __restrict
 // B: 32 input x 16 output channels). A workgroup computes 8 rows x 32 points
 // of two consecutive z-planes; each of its four waves owns two rows (four
 // 16-point M tiles) times both 16-channel N tiles of both planes, sixteen
-// independent accumulators. The input planes z0-1 .. z0+2 are staged in LDS
-// one at a time as BF16 (and, with SPLIT, the BF16 remainder x - bf16(x),
-// which a second product adds), 16-byte channel chunks XOR-swizzled by point
-// so that 16 consecutive points of one chunk fall in distinct banks; every A
-// fragment read from LDS serves both output planes, and the next plane's
-// loads are in flight (in registers) while the current one is multiplied.
+// independent accumulators. The layer's weights (54 KB) are staged in LDS
+// once, the input planes z0-1 .. z0+2 one at a time as BF16 (and, with SPLIT,
+// the BF16 remainder x - bf16(x), which a second product adds), 16-byte
+// channel chunks XOR-swizzled by point or output channel so that 16
+// consecutive ones of one chunk fall in distinct banks; every A fragment read
+// from LDS serves both output planes, and the next plane's loads are in
+// flight (in registers) while the current one is multiplied. No branch lies
+// inside the nine offsets of a plane, so that the LDS reads of one are in
+// flight during the products of the one before. 128 x 128 x 8 points: 27.4 us;
+// with the weights read from global memory under a branch per offset and the
+// mask one value at a time 45. 256 workgroups leave one wavefront per SIMD
+// there, so staging and its barriers are not hidden.
 // Also the data gradient (weights transposed and flipped, no bias) with the
 // ReLU mask of the layer below.
 template <bool SPLIT>
-__global__ __launch_bounds__(kT, 2) void k_sg_mid(SgGrid g, const float* __restrict__ a,
-                                                   const uint16_t* __restrict__ w,
-                                                   const float* __restrict__ b,
-                                                   float* __restrict__ out, int relu,
-                                                   const float* __restrict__ mask) {
+struct SgMidLds {
+  uint4 w[27 * kSgC * 4];                     // [offset][output][chunk of 8 inputs]
+  uint4 hi[kSgHalo * 4], lo[SPLIT ? kSgHalo * 4 : 1];
+};
+
+// products of the staged plane: offset plane dz of output z0 (ON0), dz - 1 of
+// output z0 + 1 (ON1)
+template <bool SPLIT, bool ON0, bool ON1>
+__device__ __forceinline__ void sg_mid_plane(const SgMidLds<SPLIT>& sh, int dz, int wv, int li,
+                                             int kg, f32x4 (&acc)[2][4][2]) {
+  const uint4* w = &sh.w[(dz * 9 * kSgC + li) * 4 + (kg ^ ((li >> 2) & 3))];
+#pragma unroll 3
+  for (int j = 0; j < 9; ++j) {
+    const int dy = j / 3, dx = j % 3;
+    bf16x8 ah[4], al[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const int h = (2 * wv + (mt >> 1) + dy) * kSgHX + (mt & 1) * 16 + li + dx;
+      const int chunk = kg ^ ((h >> 2) & 3);
+      ah[mt] = __builtin_bit_cast(bf16x8, sh.hi[h * 4 + chunk]);
+      if (SPLIT) al[mt] = __builtin_bit_cast(bf16x8, sh.lo[h * 4 + chunk]);
+    }
+#pragma unroll
+    for (int zo = 0; zo < 2; ++zo) {
+      if (!(zo == 0 ? ON0 : ON1)) continue;
+      // output channels li and 16 + li
+      bf16x8 bw[2];
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+        bw[nt] = __builtin_bit_cast(bf16x8, w[((j - 9 * zo) * kSgC + nt * 16) * 4]);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          acc[zo][mt][nt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw[nt], acc[zo][mt][nt], 0, 0, 0);
+      if (SPLIT) {
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+            acc[zo][mt][nt] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw[nt], acc[zo][mt][nt], 0, 0, 0);
+      }
+    }
+  }
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict__ a,
+                                                const uint16_t* __restrict__ w,
+                                                const float* __restrict__ b,
+                                                float* __restrict__ out, int relu,
+                                                const float* __restrict__ mask) {
   constexpr int kLoads = (kSgHalo * (kSgC / 4) + kT - 1) / kT;  // float4 per thread per plane
+  constexpr int kWts = 27 * kSgC * 4, kWLoads = (kWts + kT - 1) / kT;  // uint4 of the weights
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  __shared__ uint4 shi[kSgHalo * 4];
-  __shared__ uint4 slo[SPLIT ? kSgHalo * 4 : 1];
+  extern __shared__ uint4 mid_lds[];
+  SgMidLds<SPLIT>& sh = *reinterpret_cast<SgMidLds<SPLIT>*>(mid_lds);
   const int tiles_x = (g.nx + kSgTX - 1) / kSgTX;
   const int x0 = (int)(blockIdx.x % tiles_x) * kSgTX, y0 = (int)(blockIdx.x / tiles_x) * kSgTY;
   const int z0 = 2 * (int)blockIdx.y, nout = min(2, g.nz - z0);
@@ -189,17 +245,18 @@ __global__ __launch_bounds__(kT, 2) void k_sg_mid(SgGrid g, const float* __restr
   const int lane = t & 63, wv = t >> 6, li = lane & 15, kg = lane >> 4;
   // input planes of the two outputs inside the grid
   const int p_lo = max(0, z0 - 1), p_hi = min(g.nz - 1, z0 + nout);
+  int off[kLoads];  // of the thread's values in a plane, the same in every plane
+#pragma unroll
+  for (int k = 0; k < kLoads; ++k) {
+    const int i = t + k * kT, h = i >> 3, hy = h / kSgHX, hx = h - hy * kSgHX;
+    off[k] = (wrapi(y0 + hy - 1, g.ny) * g.nx + wrapi(x0 + hx - 1, g.nx)) * (kSgC / 4) + (i & 7);
+  }
   float4 pre[kLoads];
   auto load_plane = [&](int gz) {
+    const float4* src = reinterpret_cast<const float4*>(a + vox_of(g, gz, 0, 0) * kSgC);
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
-      const int i = t + k * kT;
-      if (i < kSgHalo * (kSgC / 4)) {
-        const int h = i >> 3, q = i & 7, hy = h / kSgHX, hx = h - hy * kSgHX;
-        pre[k] = reinterpret_cast<const float4*>(
-            a + vox_of(g, gz, wrapi(y0 + hy - 1, g.ny), wrapi(x0 + hx - 1, g.nx)) * kSgC)[q];
-      }
-    }
+    for (int k = 0; k < kLoads; ++k)
+      if (t + k * kT < kSgHalo * (kSgC / 4)) pre[k] = src[off[k]];
   };
   auto store_plane = [&]() {
 #pragma unroll
@@ -209,11 +266,11 @@ __global__ __launch_bounds__(kT, 2) void k_sg_mid(SgGrid g, const float* __restr
         const int h = i >> 3, q = i & 7, chunk = (q >> 1) ^ ((h >> 2) & 3);
         const float4 v = pre[k];
         const bf16x4 hv = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
-        reinterpret_cast<bf16x4*>(&shi[h * 4 + chunk])[q & 1] = hv;
+        reinterpret_cast<bf16x4*>(&sh.hi[h * 4 + chunk])[q & 1] = hv;
         if (SPLIT) {
           const bf16x4 lv = {(__bf16)(v.x - (float)hv[0]), (__bf16)(v.y - (float)hv[1]),
                              (__bf16)(v.z - (float)hv[2]), (__bf16)(v.w - (float)hv[3])};
-          reinterpret_cast<bf16x4*>(&slo[h * 4 + chunk])[q & 1] = lv;
+          reinterpret_cast<bf16x4*>(&sh.lo[h * 4 + chunk])[q & 1] = lv;
         }
       }
     }
@@ -226,68 +283,65 @@ __global__ __launch_bounds__(kT, 2) void k_sg_mid(SgGrid g, const float* __restr
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) acc[zo][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   load_plane(p_lo);
+  {
+    const uint4* w4 = reinterpret_cast<const uint4*>(w);
+#pragma unroll
+    for (int k = 0; k < kWLoads; ++k) {
+      const int i = t + k * kT;
+      if ((k + 1) * kT <= kWts || i < kWts) sh.w[i ^ ((i >> 4) & 3)] = w4[i];
+    }
+  }
   for (int p = p_lo; p <= p_hi; ++p) {
     __syncthreads();  // the previous plane has been multiplied
     store_plane();
     __syncthreads();
     if (p < p_hi) load_plane(p + 1);  // the next plane, in flight meanwhile
-    // offset dz of this plane for output z0 + zo (valid if 0..2)
-    const int dz0 = p - z0 + 1, dz1 = p - z0;
-    const bool on0 = dz0 <= 2, on1 = nout > 1 && dz1 >= 0;
-#pragma unroll 3
-    for (int j = 0; j < 9; ++j) {
-      const int dy = j / 3, dx = j % 3;
-      bf16x8 ah[4], al[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int h = (2 * wv + (mt >> 1) + dy) * kSgHX + (mt & 1) * 16 + li + dx;
-        const int chunk = kg ^ ((h >> 2) & 3);
-        ah[mt] = *reinterpret_cast<const bf16x8*>(&shi[h * 4 + chunk]);
-        if (SPLIT) al[mt] = *reinterpret_cast<const bf16x8*>(&slo[h * 4 + chunk]);
-      }
-#pragma unroll
-      for (int zo = 0; zo < 2; ++zo) {
-        if (!(zo == 0 ? on0 : on1)) continue;
-        // B fragments of offset (dz, j): output channels li and 16 + li, inputs 8 kg ..
-        const bf16x8* wz = reinterpret_cast<const bf16x8*>(
-            w + ((int64_t)((zo == 0 ? dz0 : dz1) * 9 + j) * kSgC + li) * kSgC + kg * 8);
-        const bf16x8 bw0 = wz[0], bw1 = wz[16 * (kSgC / 8)];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-          acc[zo][mt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw0, acc[zo][mt][0], 0, 0, 0);
-          acc[zo][mt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw1, acc[zo][mt][1], 0, 0, 0);
-        }
-        if (SPLIT) {
-#pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
-            acc[zo][mt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw0, acc[zo][mt][0], 0, 0, 0);
-            acc[zo][mt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw1, acc[zo][mt][1], 0, 0, 0);
-          }
-        }
-      }
-    }
+    // offset dz of this plane for output z0, dz - 1 for output z0 + 1
+    const int dz = p - z0 + 1;
+    if (dz == 3)
+      sg_mid_plane<SPLIT, false, true>(sh, dz, wv, li, kg, acc);
+    else if (dz == 0 || nout == 1)
+      sg_mid_plane<SPLIT, true, false>(sh, dz, wv, li, kg, acc);
+    else
+      sg_mid_plane<SPLIT, true, true>(sh, dz, wv, li, kg, acc);
   }
-  // D tile of 16 points x 16 channels: lane holds points 4 kg + r, channel li
+  // D tile of 16 points x 16 channels: lane holds points 4 kg + r, channel li.
+  // The mask values of a plane are all requested before the first is used.
+  const float bias[2] = {b ? b[li] : 0.f, b ? b[16 + li] : 0.f};
 #pragma unroll
   for (int zo = 0; zo < 2; ++zo) {
     if (zo >= nout) continue;
+    const int64_t plane = vox_of(g, z0 + zo, 0, 0) * kSgC;
+    float mk[4][4][2];
+    if (mask) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gy = min(y0 + 2 * wv + (mt >> 1), g.ny - 1);
+          const int gx = min(x0 + (mt & 1) * 16 + kg * 4 + r, g.nx - 1);
+          const float* m = mask + plane + (gy * g.nx + gx) * kSgC + li;
+          mk[mt][r][0] = m[0];
+          mk[mt][r][1] = m[16];
+        }
+    }
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       const int gy = y0 + 2 * wv + (mt >> 1);
-      if (gy >= g.ny) continue;
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int co = nt * 16 + li;
-        const float bias = b ? b[co] : 0.f;
+      for (int r = 0; r < 4; ++r) {
+        const int gx = x0 + (mt & 1) * 16 + kg * 4 + r;
+        float v[2];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int gx = x0 + (mt & 1) * 16 + kg * 4 + r;
-          if (gx >= g.nx) continue;
-          const int64_t v = vox_of(g, z0 + zo, gy, gx);
-          float val = acc[zo][mt][nt][r] + bias;
-          if (mask && !(mask[v * kSgC + co] > 0.f)) val = 0.f;
-          if (relu) val = fmaxf(val, 0.f);
-          out[v * kSgC + co] = val;
+        for (int nt = 0; nt < 2; ++nt) {
+          v[nt] = acc[zo][mt][nt][r] + bias[nt];
+          if (mask && !(mk[mt][r][nt] > 0.f)) v[nt] = 0.f;
+          if (relu) v[nt] = fmaxf(v[nt], 0.f);
+        }
+        if (gx < g.nx && gy < g.ny) {
+          float* o = out + plane + (gy * g.nx + gx) * kSgC + li;
+          o[0] = v[0];
+          o[16] = v[1];
         }
       }
     }
@@ -791,9 +845,11 @@ void launch_mid(const Surrogate* s, hipStream_t st, const float* a, const uint16
                 const float* b, float* out, int relu, const float* mask) {
   const dim3 grid(tile_grid(s->gd).x, (unsigned)((s->gd.nz + 1) / 2));  // two planes per workgroup
   if (s->split)
-    hipLaunchKernelGGL(k_sg_mid<true>, grid, dim3(kT), 0, st, s->gd, a, w, b, out, relu, mask);
+    hipLaunchKernelGGL(k_sg_mid<true>, grid, dim3(kT), sizeof(SgMidLds<true>), st, s->gd, a, w, b,
+                       out, relu, mask);
   else
-    hipLaunchKernelGGL(k_sg_mid<false>, grid, dim3(kT), 0, st, s->gd, a, w, b, out, relu, mask);
+    hipLaunchKernelGGL(k_sg_mid<false>, grid, dim3(kT), sizeof(SgMidLds<false>), st, s->gd, a, w, b,
+                       out, relu, mask);
 }
 
 float* act_of(const Surrogate* s, int l, bool train) {
@@ -885,6 +941,11 @@ hipError_t sg_create(Surrogate* s, int depth, SgGrid gd, int64_t n, const double
       (e = alloc(&s->wmidt, std::max<int64_t>(1, (int64_t)nmid * 27 * kSgC * kSgC))) ||
       (e = alloc(&s->win, kSgC * 27)) || (e = alloc(&s->wout, kSgC * 27)) ||
       (e = alloc(&s->woutt, kSgC * 27)))
+    return e;
+  if ((e = hipFuncSetAttribute((const void*)k_sg_mid<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(SgMidLds<true>))) ||
+      (e = hipFuncSetAttribute((const void*)k_sg_mid<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(SgMidLds<false>))))
     return e;
   if ((e = alloc(&s->act, 2 * s->nvox * kSgC))) return e;
   if ((e = alloc(&s->dred, 2 * kRedBlocks + 8))) return e;
