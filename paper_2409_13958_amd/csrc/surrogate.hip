@@ -45,7 +45,12 @@ __device__ __forceinline__ int64_t vox_of(const SgGrid& g, int z, int y, int x) 
 // First-layer form (one input channel -> kSgC outputs), FP32 FMA. Also the
 // data gradient of the last layer (weights flipped). Tile: 8 rows of 32
 // points of one z-plane per 256-thread workgroup; the 3 input planes of the
-// tile with a one-point halo staged in LDS.
+// tile with a one-point halo staged in LDS. A thread forms 4 channels of 8
+// consecutive points, so that the ten values of a row serve 24 products each
+// of their channels and eight lanes store (and read the mask of) 128
+// contiguous bytes; with a thread for all channels of one point the 16-byte
+// stores, 128 bytes apart, and 216 weight reads bound it. 128 x 128 x 8 points:
+// 11.1 us, before 18.8; weights through the scalar cache 19.6.
 __global__ __launch_bounds__(kT) void k_sg_in(SgGrid g, const float* __restrict__ x, float xs,
                                                const float* __restrict__ w,
                                                const float* __restrict__ b,
@@ -56,6 +61,15 @@ __global__ __launch_bounds__(kT) void k_sg_in(SgGrid g, const float* __restrict_
   const int tiles_x = (g.nx + kSgTX - 1) / kSgTX;
   const int x0 = (int)(blockIdx.x % tiles_x) * kSgTX, y0 = (int)(blockIdx.x / tiles_x) * kSgTY;
   const int z = blockIdx.y, t = threadIdx.x;
+  const int q = t & 7, ty = t >> 5, tx = ((t >> 3) & 3) * 8;  // channels 4 q .., points tx .. tx + 7
+  const int gy = y0 + ty;
+  const int64_t v0 = vox_of(g, z, min(gy, g.ny - 1), 0);
+  float4 mk[8];
+  if (mask) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      mk[i] = reinterpret_cast<const float4*>(mask + (v0 + min(x0 + tx + i, g.nx - 1)) * kSgC)[q];
+  }
   for (int i = t; i < kSgC * 27; i += kT) sw[(i % 27) * kSgC + i / 27] = w[i];  // [o][co]
   for (int i = t; i < 3 * kSgHalo; i += kT) {
     const int pl = i / kSgHalo, h = i - pl * kSgHalo;
@@ -66,39 +80,36 @@ __global__ __launch_bounds__(kT) void k_sg_in(SgGrid g, const float* __restrict_
     sx[i] = v;
   }
   __syncthreads();
-  const int ty = t / kSgTX, tx = t % kSgTX;
-  float acc[kSgC];
+  const float4 b4 = b ? reinterpret_cast<const float4*>(b)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 acc[8];
 #pragma unroll
-  for (int co = 0; co < kSgC; ++co) acc[co] = b ? b[co] : 0.f;
-  for (int dz = 0; dz < 3; ++dz)
-    for (int dy = 0; dy < 3; ++dy)
+  for (int i = 0; i < 8; ++i) acc[i] = b4;
+#pragma unroll 3
+  for (int k = 0; k < 9; ++k) {  // dz, dy
+    const float* s = &sx[(k / 3) * kSgHalo + (ty + k % 3) * kSgHX + tx];
+    float v[10];
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const float v = sx[dz * kSgHalo + (ty + dy) * kSgHX + tx + dx];
-        const float4* w4 = reinterpret_cast<const float4*>(&sw[(dz * 9 + dy * 3 + dx) * kSgC]);
+    for (int i = 0; i < 10; ++i) v[i] = s[i];
 #pragma unroll
-        for (int q = 0; q < kSgC / 4; ++q) {
-          const float4 ww = w4[q];
-          acc[4 * q] = fmaf(ww.x, v, acc[4 * q]);
-          acc[4 * q + 1] = fmaf(ww.y, v, acc[4 * q + 1]);
-          acc[4 * q + 2] = fmaf(ww.z, v, acc[4 * q + 2]);
-          acc[4 * q + 3] = fmaf(ww.w, v, acc[4 * q + 3]);
-        }
+    for (int dx = 0; dx < 3; ++dx) {
+      const float4 ww = reinterpret_cast<const float4*>(&sw[(k * 3 + dx) * kSgC])[q];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i].x = fmaf(ww.x, v[i + dx], acc[i].x);
+        acc[i].y = fmaf(ww.y, v[i + dx], acc[i].y);
+        acc[i].z = fmaf(ww.z, v[i + dx], acc[i].z);
+        acc[i].w = fmaf(ww.w, v[i + dx], acc[i].w);
       }
-  const int gx = x0 + tx, gy = y0 + ty;
-  if (gx >= g.nx || gy >= g.ny) return;
-  const int64_t v = vox_of(g, z, gy, gx);
-  float4* o4 = reinterpret_cast<float4*>(out + v * kSgC);
-  const float4* m4 = mask ? reinterpret_cast<const float4*>(mask + v * kSgC) : nullptr;
+    }
+  }
 #pragma unroll
-  for (int q = 0; q < kSgC / 4; ++q) {
-    float4 r = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-    if (m4) {
-      const float4 mk = m4[q];
-      r.x = mk.x > 0.f ? r.x : 0.f;
-      r.y = mk.y > 0.f ? r.y : 0.f;
-      r.z = mk.z > 0.f ? r.z : 0.f;
-      r.w = mk.w > 0.f ? r.w : 0.f;
+  for (int i = 0; i < 8; ++i) {
+    float4 r = acc[i];
+    if (mask) {
+      r.x = mk[i].x > 0.f ? r.x : 0.f;
+      r.y = mk[i].y > 0.f ? r.y : 0.f;
+      r.z = mk[i].z > 0.f ? r.z : 0.f;
+      r.w = mk[i].w > 0.f ? r.w : 0.f;
     }
     if (relu) {
       r.x = fmaxf(r.x, 0.f);
@@ -106,56 +117,75 @@ __global__ __launch_bounds__(kT) void k_sg_in(SgGrid g, const float* __restrict_
       r.z = fmaxf(r.z, 0.f);
       r.w = fmaxf(r.w, 0.f);
     }
-    o4[q] = r;
+    const int gx = x0 + tx + i;
+    if (gx < g.nx && gy < g.ny) reinterpret_cast<float4*>(out + (v0 + gx) * kSgC)[q] = r;
   }
 }
 
 // Last-layer form (kSgC inputs -> one output), FP32 FMA: y = (conv + b) ys.
-// The input planes are staged one at a time with a padded point stride (36
-// floats: 16-byte aligned, and 16 consecutive points of a 16-byte read fall
-// in distinct banks); weights as [offset][channel], both read as float4.
+// A thread sums 4 channels of 8 consecutive points over the 27 offsets, then
+// eight lanes add their channels; the ten float4 of a row, eight lanes 128
+// contiguous bytes, serve 24 products each of their channels. Each is read
+// from the cache where it lies (by up to nine threads of a workgroup): staged
+// in LDS with a thread per point, its 216 reads per thread bound the kernel.
+// 128 x 128 x 8 points: 12.0 us, before 19.6.
 __global__ __launch_bounds__(kT) void k_sg_out(SgGrid g, const float* __restrict__ a,
                                                 const float* __restrict__ w,
                                                 const float* __restrict__ b, float ys,
                                                 float* __restrict__ y) {
-  constexpr int S = kSgC + 4;
-  __shared__ __align__(16) float sa[kSgHalo * S];
   __shared__ __align__(16) float sw[kSgC * 27];
   const int tiles_x = (g.nx + kSgTX - 1) / kSgTX;
   const int x0 = (int)(blockIdx.x % tiles_x) * kSgTX, y0 = (int)(blockIdx.x / tiles_x) * kSgTY;
   const int z = blockIdx.y, t = threadIdx.x;
-  const int ty = t / kSgTX, tx = t % kSgTX;
+  const int q = t & 7, ty = t >> 5, tx = ((t >> 3) & 3) * 8;
   for (int i = t; i < kSgC * 27; i += kT) sw[(i % 27) * kSgC + i / 27] = w[i];  // [o][ci]
-  float acc = 0.f;
-  for (int dz = 0; dz < 3; ++dz) {
-    const int gz = z + dz - 1;
-    if (gz < 0 || gz >= g.nz) continue;  // the same for the whole workgroup
-    __syncthreads();
-    for (int i = t; i < kSgHalo * (kSgC / 4); i += kT) {
-      const int h = i / (kSgC / 4), q = i % (kSgC / 4);
-      const int hy = h / kSgHX, hx = h - hy * kSgHX;
-      const float4 v = reinterpret_cast<const float4*>(
-          a + vox_of(g, gz, wrapi(y0 + hy - 1, g.ny), wrapi(x0 + hx - 1, g.nx)) * kSgC)[q];
-      reinterpret_cast<float4*>(&sa[h * S])[q] = v;
-    }
-    __syncthreads();
-    for (int dy = 0; dy < 3; ++dy)
-      for (int dx = 0; dx < 3; ++dx) {
-        const float4* s4 = reinterpret_cast<const float4*>(&sa[((ty + dy) * kSgHX + tx + dx) * S]);
-        const float4* w4 = reinterpret_cast<const float4*>(&sw[(dz * 9 + dy * 3 + dx) * kSgC]);
+  const int gy = y0 + ty;
+  int cx[10];  // the columns x0 + tx - 1 .. x0 + tx + 8, as float4 of a row
 #pragma unroll
-        for (int q = 0; q < kSgC / 4; ++q) {
-          const float4 av = s4[q], ww = w4[q];
-          acc = fmaf(ww.x, av.x, acc);
-          acc = fmaf(ww.y, av.y, acc);
-          acc = fmaf(ww.z, av.z, acc);
-          acc = fmaf(ww.w, av.w, acc);
-        }
-      }
+  for (int i = 0; i < 10; ++i) {
+    const int gx = x0 + tx + i - 1;
+    cx[i] = (gx < 0 ? g.nx - 1 : gx == g.nx ? 0 : min(gx, g.nx - 1)) * (kSgC / 4) + q;
   }
-  const int gx = x0 + tx, gy = y0 + ty;
-  if (gx >= g.nx || gy >= g.ny) return;
-  y[vox_of(g, z, gy, gx)] = (acc + b[0]) * ys;
+  __syncthreads();
+  float acc[8] = {};
+#pragma unroll 3
+  for (int k = 0; k < 9; ++k) {
+    const int gz = z + k / 3 - 1;
+    if (gz < 0 || gz >= g.nz) continue;  // the same for the whole workgroup
+    int yy = gy + k % 3 - 1;             // rows past the grid's end are not stored
+    yy = yy < 0 ? g.ny - 1 : yy == g.ny ? 0 : min(yy, g.ny - 1);
+    const float4* row = reinterpret_cast<const float4*>(a + vox_of(g, gz, yy, 0) * kSgC);
+    float4 v[10];
+#pragma unroll
+    for (int i = 0; i < 10; ++i) v[i] = row[cx[i]];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+      const float4 ww = reinterpret_cast<const float4*>(&sw[(k * 3 + dx) * kSgC])[q];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i] = fmaf(ww.x, v[i + dx].x, acc[i]);
+        acc[i] = fmaf(ww.y, v[i + dx].y, acc[i]);
+        acc[i] = fmaf(ww.z, v[i + dx].z, acc[i]);
+        acc[i] = fmaf(ww.w, v[i + dx].w, acc[i]);
+      }
+    }
+  }
+  // lane q ends with point tx + q: halves are exchanged three times
+  float s4[4], s2[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float keep = q & 4 ? acc[4 + i] : acc[i], send = q & 4 ? acc[i] : acc[4 + i];
+    s4[i] = keep + __shfl_xor(send, 4);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float keep = q & 2 ? s4[2 + i] : s4[i], send = q & 2 ? s4[i] : s4[2 + i];
+    s2[i] = keep + __shfl_xor(send, 2);
+  }
+  const float keep = q & 1 ? s2[1] : s2[0], send = q & 1 ? s2[0] : s2[1];
+  const float sum = keep + __shfl_xor(send, 1);
+  const int gx = x0 + tx + q;
+  if (gx < g.nx && gy < g.ny) y[vox_of(g, z, gy, gx)] = (sum + b[0]) * ys;
 }
 
 // Middle layer (kSgC -> kSgC) on the matrix cores, as an implicit GEMM: M =
