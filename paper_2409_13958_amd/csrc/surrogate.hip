@@ -388,26 +388,26 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
 // the smallest products on and then added to the running FP32 sum, one
 // rounding for 32 points where FP32 operands round eight times.
 //
-// A workgroup has one dz and walks the tiles of 16 x 8 points of its planes,
-// its tile's next loads in flight while the current one is multiplied. Tiles
-// are staged transposed, [x][channel] with the eight y of a column as one
-// 16-byte operand (K: four columns of eight rows), so that a shift by dx is
-// another column and a shift by dy the same operand funnel-shifted with the
-// two halo rows, and 16 lanes read 256 contiguous bytes. Each of its four
-// wavefronts owns one 16 x 16 channel block for all nine (dy, dx): 54 matrix
-// instructions for 21 LDS reads. 59 KB of LDS and one wavefront per SIMD, so
-// that two workgroups share a compute unit and one stages while the other
-// multiplies; with six wavefronts, one dx each, they did not share the SIMDs
-// evenly (68 us). 128 x 128 x 8 points: 48.7 us and 5.0 for the sums, where
-// FP32 operands (v_mfma_f32_16x16x4f32) took 91 and 20. Error of the gradient
-// against 64 bits 3.0e-8 (256 x 250 x 9 points, depth 3), with FP32 operands
-// 3.5e-8, and without the separate sum of 32 points 4.5e-8.
-struct SgWgradPlan {
-  int rows[3];   // workgroups, hence rows of partial sums, of each dz
-};
-
+// A workgroup walks tiles of 16 x 8 points up the planes of a column, a share
+// of the (tile, plane) steps in order, so that each input plane is staged once
+// for its three dz, in a ring of three; the next planes' loads are in flight
+// while the current ones are multiplied. Tiles are staged transposed,
+// [x][channel] with the eight y of a column as one 16-byte operand (K: four
+// columns of eight rows), so that a shift by dx is another column and a shift
+// by dy the same operand funnel-shifted with the two halo rows, and 16 lanes
+// read 256 contiguous bytes. Each of its twelve wavefronts owns one dz and one
+// 16 x 16 channel block for all nine (dy, dx): 54 matrix instructions for 21
+// LDS reads. 128 KB of LDS, one workgroup of three wavefronts per SIMD on a
+// compute unit.
+// 128 x 128 x 8 points: 44.2 us, and 5.5 for the sums; a workgroup per dz, two
+// on a compute unit, each staging its planes for itself, took 48.5; FP32
+// operands (v_mfma_f32_16x16x4f32) 91 and 20. Without five of the six products
+// it takes 24: the rest is the operands' shifts, staging and barriers. Error of
+// the gradient against 64 bits 2.8e-8 (256 x 250 x 9 points, depth 3), with
+// FP32 operands 3.5e-8, and with one running sum for all products 4.5e-8.
 constexpr int kSgWTX = 16, kSgWTY = 8, kSgWHX = kSgWTX + 2;   // its tile
-constexpr int kSgWT = 256;                                     // its threads
+constexpr int kSgWT = 768;                                     // its threads
+constexpr int kSgWBlocks = 256;                                // most workgroups, one per compute unit
 constexpr int kSgWRow = kSgC * kSgC * 27 + kSgC;               // a row of partial sums: [o][co][ci], bias
 
 struct Bf3 {
@@ -427,152 +427,183 @@ __device__ __forceinline__ Bf3 split3(float v0, float v1) {
   return r;
 }
 
-__global__ __launch_bounds__(kSgWT, 2) void k_sg_wgrad(SgGrid g, SgWgradPlan plan,
+struct SgWgradLds {
+  static constexpr int kG = kSgWTX * kSgC, kA = kSgWHX * kSgC;  // columns of the tile and its plane
+  uint4 g[3][kG];           // [part]
+  uint4 a[3][3][kA];        // [plane mod 3][part] rows 0 .. 7
+  uint32_t e[3][3][kA];     // halo rows 8 and 9
+};
+
+__global__ __launch_bounds__(kSgWT, 3) void k_sg_wgrad(SgGrid g, int each,
                                                         const float* __restrict__ gr,
                                                         const float* __restrict__ a,
                                                         float* __restrict__ part) {
-  constexpr int kG = kSgWTX * kSgC, kA = kSgWHX * kSgC;        // columns of the tile and the plane
-  constexpr int kItems = (kG + kA + kSgWT - 1) / kSgWT;
-  __shared__ uint4 sg[3][kG], sa[3][kA];
-  __shared__ uint32_t sb[3][kA];                                // halo rows 8 and 9
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, kg = lane >> 4;
-  const int mt = wv >> 1, nt = wv & 1;
-  int row = blockIdx.x, dz = 0;
-  while (row >= plan.rows[dz]) row -= plan.rows[dz++];
+  constexpr int kG = SgWgradLds::kG, kA = SgWgradLds::kA;
+  static_assert(kG % 64 == 0 && kG < kSgWT && kG + kA <= 2 * kSgWT, "two items of a thread");
+  extern __shared__ uint4 wgrad_lds[];
+  SgWgradLds& sh = *reinterpret_cast<SgWgradLds*>(wgrad_lds);
+  const int t = threadIdx.x, lane = t & 63, li = lane & 15, kg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int dz = wv >> 2, mt = (wv >> 1) & 1, nt = wv & 1;
   const int tiles_x = (g.nx + kSgWTX - 1) / kSgWTX, tiles_y = (g.ny + kSgWTY - 1) / kSgWTY;
-  const int tpp = tiles_x * tiles_y;
-  // planes z whose input plane z + dz - 1 lies inside the grid
-  const int z_lo = dz == 0 ? 1 : 0, nplanes = g.nz - (dz != 1), ntiles = tpp * nplanes;
-  // a tile's plane, corner and, of item k, whether it is a column of gr
-  auto plane_of = [&](int tl, int& x0, int& y0) {
-    const int zi = tl / tpp, r2 = tl - zi * tpp;
-    x0 = (r2 % tiles_x) * kSgWTX;
-    y0 = (r2 / tiles_x) * kSgWTY;
-    return z_lo + zi;
+  const int steps = tiles_x * tiles_y * g.nz;
+  const int first = blockIdx.x * each, last = min(first + each, steps);
+  // A stage brings input plane z + 1 + lead; with lead 0 also the tile of plane
+  // z, which is then multiplied. A column's first step is led by the planes
+  // below it that lie inside the grid.
+  struct Stage {
+    int step, x0, y0, z, lead;
   };
-  static_assert(kG % kSgWT == 0, "an item is a column of gr, or of a, in every thread");
-  auto of_gr = [](int k) { return k * kSgWT < kG; };
-  // Every load is issued: out of range, the nearest column or row is read
-  // (those of gr become zero when they are staged, those of a meet its zeros).
-  float pre[kItems][10];
-  auto load_tile = [&](int tl) {
-    int x0, y0;
-    const int z = plane_of(tl, x0, y0);
+  auto column = [&](int step) {
+    const int tl = step / g.nz, z = step - tl * g.nz;
+    return Stage{step, (tl % tiles_x) * kSgWTX, (tl / tiles_x) * kSgWTY, z, z == 0 ? -1 : -2};
+  };
+  auto next = [&](Stage s) {
+    if (s.lead < 0) {
+      ++s.lead;
+      return s;
+    }
+    if (s.z + 1 == g.nz) return column(s.step + 1);
+    ++s.step;
+    ++s.z;
+    return s;
+  };
+  // Item 0 of the first kG threads is a column of the tile, the others'
+  // and item 1 a column of the plane. Every load lies inside its array: out
+  // of range, the nearest column or row is read (those of gr become zero when
+  // they are staged, those of a meet its zeros).
+  float pre[2][kSgWTY + 2];
+  auto of_gr = [&](int k) { return k == 0 && wv < kG / 64; };
+  auto load = [&](const Stage& s) {
     const uint32_t stride = g.nx * kSgC * sizeof(float);
-    const char* gz = reinterpret_cast<const char*>(gr + vox_of(g, z, y0, 0) * kSgC);
-    const char* az = reinterpret_cast<const char*>(a + vox_of(g, z + dz - 1, 0, 0) * kSgC);
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
+    for (int k = 0; k < 2; ++k) {
       const int i = t + k * kSgWT, c = i & (kSgC - 1);
       if (of_gr(k)) {
-        const uint32_t at = (min(x0 + i / kSgC, g.nx - 1) * kSgC + c) * sizeof(float);
-        const char* row_p = gz;
+        if (s.lead < 0) continue;
+        const char* row = reinterpret_cast<const char*>(gr + vox_of(g, s.z, s.y0, 0) * kSgC);
+        const uint32_t at = (min(s.x0 + i / kSgC, g.nx - 1) * kSgC + c) * sizeof(float);
 #pragma unroll
         for (int r = 0; r < kSgWTY; ++r) {
-          pre[k][r] = *reinterpret_cast<const float*>(row_p + at);
-          row_p += y0 + r + 1 < g.ny ? stride : 0;
+          pre[k][r] = *reinterpret_cast<const float*>(row + at);
+          row += s.y0 + r + 1 < g.ny ? stride : 0;
         }
-      } else {
-        int gx = x0 + (i - kG) / kSgC - 1;  // x0 - 1 .. x0 + 22
+      } else if (s.z + 1 + s.lead < g.nz && i < kG + kA) {
+        int gx = s.x0 + (i - kG) / kSgC - 1;  // x0 - 1 .. x0 + 16
         gx = gx < 0 ? g.nx - 1 : gx == g.nx ? 0 : min(gx, g.nx - 1);
         const uint32_t at = (gx * kSgC + c) * sizeof(float);
-        int gy = y0 == 0 ? g.ny - 1 : y0 - 1;
-        const char* row_p = az + (int64_t)gy * stride;
+        const char* plane = reinterpret_cast<const char*>(a + vox_of(g, s.z + 1 + s.lead, 0, 0) * kSgC);
+        int gy = s.y0 == 0 ? g.ny - 1 : s.y0 - 1;
+        const char* row = plane + (int64_t)gy * stride;
 #pragma unroll
         for (int r = 0; r < kSgWTY + 2; ++r) {
-          pre[k][r] = *reinterpret_cast<const float*>(row_p + at);
+          pre[k][r] = *reinterpret_cast<const float*>(row + at);
           const bool wrap = ++gy == g.ny;
           gy = wrap ? 0 : gy;
-          row_p = wrap ? az : row_p + stride;
+          row = wrap ? plane : row + stride;
+        }
+      }
+    }
+  };
+  double bsum = 0.0;
+  auto store = [&](const Stage& s) {
+    const int slot = (s.z + 1 + s.lead) % 3;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = t + k * kSgWT;
+      float* v = pre[k];
+      if (of_gr(k)) {
+        if (s.lead < 0) continue;
+        const bool in = s.x0 + i / kSgC < g.nx;
+#pragma unroll
+        for (int r = 0; r < kSgWTY; ++r) v[r] = in && s.y0 + r < g.ny ? v[r] : 0.f;
+        bsum += (double)(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])));
+        Bf3 p4[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p4[q] = split3(v[2 * q], v[2 * q + 1]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          sh.g[p][i] = make_uint4(p4[0].p[p], p4[1].p[p], p4[2].p[p], p4[3].p[p]);
+      } else if (s.z + 1 + s.lead < g.nz && i < kG + kA) {
+        Bf3 p5[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) p5[q] = split3(v[2 * q], v[2 * q + 1]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          sh.a[slot][p][i - kG] = make_uint4(p5[0].p[p], p5[1].p[p], p5[2].p[p], p5[3].p[p]);
+          sh.e[slot][p][i - kG] = p5[4].p[p];
         }
       }
     }
   };
   f32x4 acc[3][3] = {};   // [dy][dx]
-  double bsum = 0.0;
-  if (row < ntiles) load_tile(row);
-  for (int tile = row; tile < ntiles; tile += plan.rows[dz]) {
-    int x0, y0;
-    (void)plane_of(tile, x0, y0);
-    __syncthreads();  // the previous tile has been used
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const int i = t + k * kSgWT;
-      float* v = pre[k];
-      if (of_gr(k)) {
-        const bool in = x0 + i / kSgC < g.nx;
-#pragma unroll
-        for (int r = 0; r < kSgWTY; ++r) v[r] = in && y0 + r < g.ny ? v[r] : 0.f;
-        bsum += (double)(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])));
-      }
-      Bf3 s[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s[q] = split3(v[2 * q], v[2 * q + 1]);
-      if (of_gr(k)) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) sg[p][i] = make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]);
-      } else if (i < kG + kA) {
-        const Bf3 e = split3(v[8], v[9]);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          sa[p][i - kG] = make_uint4(s[0].p[p], s[1].p[p], s[2].p[p], s[3].p[p]);
-          sb[p][i - kG] = e.p[p];
-        }
-      }
-    }
-    __syncthreads();
-    if (tile + plan.rows[dz] < ntiles) load_tile(tile + plan.rows[dz]);
+  if (first < last) {
+    Stage s = column(first);
+    load(s);
+    while (s.step < last) {
+      __syncthreads();  // the previous stage has been multiplied
+      store(s);
+      __syncthreads();
+      const Stage n = next(s);
+      if (n.step < last) load(n);
+      const int pz = s.z + dz - 1;  // this wavefront's input plane
+      const bool mult = s.lead == 0 && pz >= 0 && pz < g.nz;
+      const int slot = (pz + 3) % 3;
+      s = n;
+      if (!mult) continue;  // the barriers are met by every wavefront
 #pragma unroll 1
-    for (int st = 0; st < kSgWTX / 4; ++st) {
-      const int x = 4 * st + kg;
-      bf16x8 A[3];
+      for (int st = 0; st < kSgWTX / 4; ++st) {
+        const int x = 4 * st + kg;
+        bf16x8 A[3];
 #pragma unroll
-      for (int p = 0; p < 3; ++p) A[p] = __builtin_bit_cast(bf16x8, sg[p][x * kSgC + mt * 16 + li]);
+        for (int p = 0; p < 3; ++p)
+          A[p] = __builtin_bit_cast(bf16x8, sh.g[p][x * kSgC + mt * 16 + li]);
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const int col = (x + dx) * kSgC + nt * 16 + li;
-        bf16x8 Bm[3][3];  // [dy][part]
+        for (int dx = 0; dx < 3; ++dx) {
+          const int col = (x + dx) * kSgC + nt * 16 + li;
+          bf16x8 Bm[3][3];  // [dy][part]
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          const uint4 q = sa[p][col];
-          const uint32_t e = sb[p][col];
-          Bm[0][p] = __builtin_bit_cast(bf16x8, q);
-          Bm[1][p] = __builtin_bit_cast(
-              bf16x8, make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16),
-                                 __builtin_amdgcn_alignbit(q.z, q.y, 16),
-                                 __builtin_amdgcn_alignbit(q.w, q.z, 16),
-                                 __builtin_amdgcn_alignbit(e, q.w, 16)));
-          Bm[2][p] = __builtin_bit_cast(bf16x8, make_uint4(q.y, q.z, q.w, e));
+          for (int p = 0; p < 3; ++p) {
+            const uint4 q = sh.a[slot][p][col];
+            const uint32_t e = sh.e[slot][p][col];
+            Bm[0][p] = __builtin_bit_cast(bf16x8, q);
+            Bm[1][p] = __builtin_bit_cast(
+                bf16x8, make_uint4(__builtin_amdgcn_alignbit(q.y, q.x, 16),
+                                   __builtin_amdgcn_alignbit(q.z, q.y, 16),
+                                   __builtin_amdgcn_alignbit(q.w, q.z, 16),
+                                   __builtin_amdgcn_alignbit(e, q.w, 16)));
+            Bm[2][p] = __builtin_bit_cast(bf16x8, make_uint4(q.y, q.z, q.w, e));
+          }
+          // h l, l h, m m, h m, m h, h h of 32 points, then onto the sum
+          constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
+          f32x4 s32[3] = {};
+#pragma unroll
+          for (int j = 0; j < 6; ++j)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+              s32[dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[pa[j]], Bm[dy][pb[j]], s32[dy],
+                                                                0, 0, 0);
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy) acc[dy][dx] += s32[dy];
         }
-        // h l, l h, m m, h m, m h, h h of 32 points, then onto the sum
-        constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
-        f32x4 s32[3] = {};
-#pragma unroll
-        for (int j = 0; j < 6; ++j)
-#pragma unroll
-          for (int dy = 0; dy < 3; ++dy)
-            s32[dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[pa[j]], Bm[dy][pb[j]], s32[dy], 0,
-                                                              0, 0);
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) acc[dy][dx] += s32[dy];
       }
     }
   }
   // D block: lane holds output channels 16 mt + 4 kg + r, input channel 16 nt + li
+  float* P = part + (int64_t)blockIdx.x * kSgWRow;
 #pragma unroll
-  for (int j = 0; j < 9; ++j) {
-    float* P = part + (int64_t)row * kSgWRow + (dz * 9 + j) * kSgC * kSgC;
+  for (int j = 0; j < 9; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      P[(mt * 16 + 4 * kg + r) * kSgC + nt * 16 + li] = acc[j / 3][j % 3][r];
-  }
-  __shared__ double red[kSgWT / kSgC][kSgC];
-  red[t / kSgC][t % kSgC] = bsum;
+      P[((dz * 9 + j) * kSgC + mt * 16 + 4 * kg + r) * kSgC + nt * 16 + li] = acc[j / 3][j % 3][r];
+  double* red = reinterpret_cast<double*>(wgrad_lds);
   __syncthreads();
-  if (dz == 1 && t < kSgC) {
+  if (t < kG) red[t] = bsum;
+  __syncthreads();
+  if (t < kSgC) {
     double s = 0.0;
-    for (int k = 0; k < kSgWT / kSgC; ++k) s += red[k][t];
-    part[(int64_t)row * kSgWRow + 27 * kSgC * kSgC + t] = (float)s;
+    for (int k = 0; k < kG / kSgC; ++k) s += red[k * kSgC + t];
+    P[27 * kSgC * kSgC + t] = (float)s;
   }
 }
 
@@ -671,18 +702,16 @@ __global__ __launch_bounds__(1024) void k_sg_reduce_thin(int P, const float* __r
     bias[c] = (float)sum;
 }
 
-// Sum of a middle layer's partial sums (rows of kSgWRow, as many per dz as
-// the plan says; the bias in those of dz = 1) into its W[co][ci][27] and b. A
-// workgroup takes 64 consecutive entries (contiguous loads) and eight shares
+// Sum of a middle layer's partial sums part[P][kSgWRow] into its W[co][ci][27]
+// and b. A workgroup takes 64 consecutive entries (contiguous loads) and eight shares
 // of the rows, added in a fixed order (FP64 throughout).
-__global__ __launch_bounds__(512) void k_sg_reduce_w(SgWgradPlan plan, const float* __restrict__ part,
+__global__ __launch_bounds__(512) void k_sg_reduce_w(int P, const float* __restrict__ part,
                                                       float* __restrict__ dst,
                                                       float* __restrict__ bias) {
   __shared__ double red[8][64];
   const int el = threadIdx.x & 63, sh = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + el;
   const int o = e / (kSgC * kSgC), co = (e / kSgC) % kSgC, ci = e % kSgC;
-  const int P = plan.rows[o < 27 ? o / 9 : 1];
   double sum = 0.0;
   if (e < kSgWRow) {
 #pragma unroll 8
@@ -908,26 +937,15 @@ void forward(Surrogate* s, hipStream_t st, const float* Q, bool train, float* yo
   if (ev) (void)hipEventRecord(ev[2 * D - 1], st);
 }
 
-// Workgroups of each dz: the fewest tiles per workgroup with all of them
-// resident at once (two per compute unit), each dz in proportion to its planes.
-SgWgradPlan wgrad_plan(const SgGrid& g) {
-  const int tpp = ((g.nx + kSgWTX - 1) / kSgWTX) * ((g.ny + kSgWTY - 1) / kSgWTY);
-  const int tiles[3] = {tpp * (g.nz - 1), tpp * g.nz, tpp * (g.nz - 1)};
-  SgWgradPlan plan;
-  for (int each = (tiles[0] + tiles[1] + tiles[2] + kSgWPart - 1) / kSgWPart;; ++each) {
-    int sum = 0;
-    for (int d = 0; d < 3; ++d) sum += plan.rows[d] = (tiles[d] + each - 1) / each;
-    if (sum <= kSgWPart) return plan;
-  }
-}
-
 // weight and bias gradients of a middle layer from its output gradient g
 // [V][C] and its input a [V][C]
 void layer_grads(Surrogate* s, hipStream_t st, int l, const float* g, const float* a) {
-  const SgWgradPlan plan = wgrad_plan(s->gd);
-  hipLaunchKernelGGL(k_sg_wgrad, dim3((unsigned)(plan.rows[0] + plan.rows[1] + plan.rows[2])),
-                     dim3(kSgWT), 0, st, s->gd, plan, g, a, s->part);
-  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)((kSgWRow + 63) / 64)), dim3(512), 0, st, plan,
+  const SgGrid& gd = s->gd;
+  const int steps = ((gd.nx + kSgWTX - 1) / kSgWTX) * ((gd.ny + kSgWTY - 1) / kSgWTY) * gd.nz;
+  const int each = (steps + kSgWBlocks - 1) / kSgWBlocks, P = (steps + each - 1) / each;
+  hipLaunchKernelGGL(k_sg_wgrad, dim3((unsigned)P), dim3(kSgWT), sizeof(SgWgradLds), st, gd, each, g,
+                     a, s->part);
+  hipLaunchKernelGGL(k_sg_reduce_w, dim3((unsigned)((kSgWRow + 63) / 64)), dim3(512), 0, st, P,
                      s->part, s->grad + s->woff[l], s->grad + s->boff[l]);
 }
 
@@ -974,6 +992,8 @@ hipError_t sg_create(Surrogate* s, int depth, SgGrid gd, int64_t n, const double
     return e;
   if ((e = hipFuncSetAttribute((const void*)k_sg_mid<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)sizeof(SgMidLds<true>))) ||
+      (e = hipFuncSetAttribute((const void*)k_sg_wgrad, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(SgWgradLds))) ||
       (e = hipFuncSetAttribute((const void*)k_sg_mid<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)sizeof(SgMidLds<false>))))
     return e;
@@ -996,7 +1016,7 @@ hipError_t sg_ensure_training(Surrogate* s, int n_loss) {
         (e = alloc(&s->y, s->nvox)) ||
         (e = alloc(&s->gy, s->nvox)) || (e = alloc(&s->qbuf, s->nvox)) ||
         (e = alloc(&s->ubuf, s->nvox)) ||
-        (e = alloc(&s->part, (int64_t)kSgWPart * kSgWRow)))
+        (e = alloc(&s->part, std::max<int64_t>((int64_t)kSgWBlocks * kSgWRow, (int64_t)kSgWPart * kSgThin))))
       return e;
     s->trained_buffers = true;
   }
