@@ -13,6 +13,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 256;
+constexpr int kSgMT = 512;         // threads of a middle layer's workgroup
 constexpr int kRedBlocks = 1024;   // blocks of the device reductions (partials in dred)
 
 constexpr int kSgThin = kSgC * 32;   // a thin layer's partial sums: 27 offsets, the bias, 4 unused
@@ -32,9 +33,11 @@ inline uint16_t bf16_bits_host(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// v in [-1, n] on a circular axis of n points; a tile's points past n, which
+// nothing reads or meets only zeros, take the last one's. A remainder here took
+// 40 instructions per staged value.
 __device__ __forceinline__ int wrapi(int v, int n) {
-  v %= n;
-  return v < 0 ? v + n : v;
+  return v < 0 ? n - 1 : v == n ? 0 : min(v, n - 1);
 }
 
 __device__ __forceinline__ int64_t vox_of(const SgGrid& g, int z, int y, int x) {
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(kT) void k_sg_out(SgGrid g, const float* __restrict
 #pragma unroll
   for (int i = 0; i < 10; ++i) {
     const int gx = x0 + tx + i - 1;
-    cx[i] = (gx < 0 ? g.nx - 1 : gx == g.nx ? 0 : min(gx, g.nx - 1)) * (kSgC / 4) + q;
+    cx[i] = wrapi(gx, g.nx) * (kSgC / 4) + q;
   }
   __syncthreads();
   float acc[8] = {};
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(kT) void k_sg_out(SgGrid g, const float* __restrict
     const int gz = z + k / 3 - 1;
     if (gz < 0 || gz >= g.nz) continue;  // the same for the whole workgroup
     int yy = gy + k % 3 - 1;             // rows past the grid's end are not stored
-    yy = yy < 0 ? g.ny - 1 : yy == g.ny ? 0 : min(yy, g.ny - 1);
+    yy = wrapi(yy, g.ny);
     const float4* row = reinterpret_cast<const float4*>(a + vox_of(g, gz, yy, 0) * kSgC);
     float4 v[10];
 #pragma unroll
@@ -192,79 +195,91 @@ __global__ __launch_bounds__(kT) void k_sg_out(SgGrid g, const float* __restrict
 // grid points, N = output channels, K = 27 offsets x kSgC input channels,
 // with v_mfma_f32_16x16x32_bf16 (A: 16 points x 32 channels of one offset;
 // B: 32 input x 16 output channels). A workgroup computes 8 rows x 32 points
-// of two consecutive z-planes; each of its four waves owns two rows (four
-// 16-point M tiles) times both 16-channel N tiles of both planes, sixteen
+// of two consecutive z-planes; each of its eight waves owns two rows (four
+// 16-point M tiles) times one 16-channel N tile of both planes, eight
 // independent accumulators. The layer's weights (54 KB) are staged in LDS
 // once, the input planes z0-1 .. z0+2 one at a time as BF16 (and, with SPLIT,
-// the BF16 remainder x - bf16(x), which a second product adds), 16-byte
-// channel chunks XOR-swizzled by point or output channel so that 16
-// consecutive ones of one chunk fall in distinct banks; every A fragment read
-// from LDS serves both output planes, and the next plane's loads are in
-// flight (in registers) while the current one is multiplied. No branch lies
-// inside the nine offsets of a plane, so that the LDS reads of one are in
-// flight during the products of the one before. 128 x 128 x 8 points: 27.4 us;
-// with the weights read from global memory under a branch per offset and the
-// mask one value at a time 45. 256 workgroups leave one wavefront per SIMD
-// there, so staging and its barriers are not hidden.
+// the BF16 remainder x - bf16(x), which a second product adds); every A
+// fragment read from LDS serves both output planes, and the next plane's loads
+// are in flight (in registers) while the current one is multiplied. The nine
+// offsets of a plane are straight-line code, each one's LDS reads issued before
+// the products of the one before. A 16-byte read of a wavefront takes four
+// turns, the first of lanes 0-3, 12-15 and 20-27: the chunk of a point is
+// XORed with twice bit 2 of its column, which leaves every turn without a bank
+// conflict (with bits 2 and 3: 1.3 M conflict cycles of 3.1 M, now none), and
+// as it does not depend on the row, all reads of a plane lie at fixed distances
+// from three addresses.
+// 128 x 128 x 8 points: 23.3 us; with four waves of both N tiles and addresses
+// formed for every read 27.4; with the weights read from global memory under a
+// branch per offset and the mask one value at a time 45. 256 workgroups leave
+// two wavefronts per SIMD there, so staging and its barriers are only partly
+// hidden: the matrix cores are busy for 5.8 us of it.
 // Also the data gradient (weights transposed and flipped, no bias) with the
 // ReLU mask of the layer below.
+constexpr int kSgMP = kSgHX + 2;   // staged row: a multiple of four points
+constexpr int kSgMPlane = kSgHY * kSgMP * 4;
+// chunk swizzle of the point of column h, or of output channel h
+__device__ __forceinline__ int swz(int h) { return (h >> 1) & 2; }
+
 template <bool SPLIT>
 struct SgMidLds {
   uint4 w[27 * kSgC * 4];                     // [offset][output][chunk of 8 inputs]
-  uint4 hi[kSgHalo * 4], lo[SPLIT ? kSgHalo * 4 : 1];
+  uint4 hi[kSgMPlane], lo[SPLIT ? kSgMPlane : 1];
 };
 
 // products of the staged plane: offset plane dz of output z0 (ON0), dz - 1 of
 // output z0 + 1 (ON1)
 template <bool SPLIT, bool ON0, bool ON1>
 __device__ __forceinline__ void sg_mid_plane(const SgMidLds<SPLIT>& sh, int dz, int wv, int li,
-                                             int kg, f32x4 (&acc)[2][4][2]) {
-  const uint4* w = &sh.w[(dz * 9 * kSgC + li) * 4 + (kg ^ ((li >> 2) & 3))];
-#pragma unroll 3
-  for (int j = 0; j < 9; ++j) {
-    const int dy = j / 3, dx = j % 3;
-    bf16x8 ah[4], al[4];
+                                             int kg, int nt, f32x4 (&acc)[2][4]) {
+  const uint4* w = &sh.w[(dz * 9 * kSgC + nt * 16 + li) * 4 + (kg ^ swz(li))];
+  struct Frags {
+    bf16x8 ah[4], al[4], bw[2];  // points' high parts and remainders, weights [zo]
+  };
+  int at[3];  // of the wavefront's first row at dx; the other rows and columns lie at fixed distances
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx) at[dx] = (2 * wv * kSgMP + li + dx) * 4 + (kg ^ swz(li + dx));
+  auto load = [&](int j, Frags& f) {
+#pragma unroll
+    for (int zo = 0; zo < 2; ++zo)
+      if (zo == 0 ? ON0 : ON1) f.bw[zo] = __builtin_bit_cast(bf16x8, w[(j - 9 * zo) * kSgC * 4]);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
-      const int h = (2 * wv + (mt >> 1) + dy) * kSgHX + (mt & 1) * 16 + li + dx;
-      const int chunk = kg ^ ((h >> 2) & 3);
-      ah[mt] = __builtin_bit_cast(bf16x8, sh.hi[h * 4 + chunk]);
-      if (SPLIT) al[mt] = __builtin_bit_cast(bf16x8, sh.lo[h * 4 + chunk]);
+      const int h = at[j % 3] + (((mt >> 1) + j / 3) * kSgMP + (mt & 1) * 16) * 4;
+      f.ah[mt] = __builtin_bit_cast(bf16x8, sh.hi[h]);
+      if (SPLIT) f.al[mt] = __builtin_bit_cast(bf16x8, sh.lo[h]);
     }
+  };
+  auto multiply = [&](const Frags& f) {
 #pragma unroll
     for (int zo = 0; zo < 2; ++zo) {
       if (!(zo == 0 ? ON0 : ON1)) continue;
-      // output channels li and 16 + li
-      bf16x8 bw[2];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        bw[nt] = __builtin_bit_cast(bf16x8, w[((j - 9 * zo) * kSgC + nt * 16) * 4]);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-          acc[zo][mt][nt] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bw[nt], acc[zo][mt][nt], 0, 0, 0);
-      if (SPLIT) {
+      for (int part = 0; part < (SPLIT ? 2 : 1); ++part)
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
-            acc[zo][mt][nt] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bw[nt], acc[zo][mt][nt], 0, 0, 0);
-      }
+          acc[zo][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part ? f.al[mt] : f.ah[mt],
+                                                                f.bw[zo], acc[zo][mt], 0, 0, 0);
     }
+  };
+  Frags f[2];
+  load(0, f[0]);
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    if (j < 8) load(j + 1, f[(j + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f[j & 1]);
   }
 }
 
 template <bool SPLIT>
-__global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict__ a,
+__global__ __launch_bounds__(kSgMT) void k_sg_mid(SgGrid g, const float* __restrict__ a,
                                                 const uint16_t* __restrict__ w,
                                                 const float* __restrict__ b,
                                                 float* __restrict__ out, int relu,
                                                 const float* __restrict__ mask) {
-  constexpr int kLoads = (kSgHalo * (kSgC / 4) + kT - 1) / kT;  // float4 per thread per plane
-  constexpr int kWts = 27 * kSgC * 4, kWLoads = (kWts + kT - 1) / kT;  // uint4 of the weights
+  constexpr int kLoads = (kSgHalo * (kSgC / 4) + kSgMT - 1) / kSgMT;  // float4 per thread per plane
+  constexpr int kWts = 27 * kSgC * 4, kWLoads = (kWts + kSgMT - 1) / kSgMT;  // uint4 of the weights
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   extern __shared__ uint4 mid_lds[];
   SgMidLds<SPLIT>& sh = *reinterpret_cast<SgMidLds<SPLIT>*>(mid_lds);
@@ -272,13 +287,13 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
   const int x0 = (int)(blockIdx.x % tiles_x) * kSgTX, y0 = (int)(blockIdx.x / tiles_x) * kSgTY;
   const int z0 = 2 * (int)blockIdx.y, nout = min(2, g.nz - z0);
   const int t = threadIdx.x;
-  const int lane = t & 63, wv = t >> 6, li = lane & 15, kg = lane >> 4;
+  const int lane = t & 63, wv = (t >> 6) & 3, nt = t >> 8, li = lane & 15, kg = lane >> 4;
   // input planes of the two outputs inside the grid
   const int p_lo = max(0, z0 - 1), p_hi = min(g.nz - 1, z0 + nout);
   int off[kLoads];  // of the thread's values in a plane, the same in every plane
 #pragma unroll
   for (int k = 0; k < kLoads; ++k) {
-    const int i = t + k * kT, h = i >> 3, hy = h / kSgHX, hx = h - hy * kSgHX;
+    const int i = t + k * kSgMT, h = i >> 3, hy = h / kSgHX, hx = h - hy * kSgHX;
     off[k] = (wrapi(y0 + hy - 1, g.ny) * g.nx + wrapi(x0 + hx - 1, g.nx)) * (kSgC / 4) + (i & 7);
   }
   float4 pre[kLoads];
@@ -286,39 +301,38 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
     const float4* src = reinterpret_cast<const float4*>(a + vox_of(g, gz, 0, 0) * kSgC);
 #pragma unroll
     for (int k = 0; k < kLoads; ++k)
-      if (t + k * kT < kSgHalo * (kSgC / 4)) pre[k] = src[off[k]];
+      if (t + k * kSgMT < kSgHalo * (kSgC / 4)) pre[k] = src[off[k]];
   };
   auto store_plane = [&]() {
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
-      const int i = t + k * kT;
+      const int i = t + k * kSgMT;
       if (i < kSgHalo * (kSgC / 4)) {
-        const int h = i >> 3, q = i & 7, chunk = (q >> 1) ^ ((h >> 2) & 3);
+        const int p = i >> 3, q = i & 7, hy = p / kSgHX, hx = p - hy * kSgHX;
+        const int at = (hy * kSgMP + hx) * 4 + ((q >> 1) ^ swz(hx));
         const float4 v = pre[k];
         const bf16x4 hv = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
-        reinterpret_cast<bf16x4*>(&sh.hi[h * 4 + chunk])[q & 1] = hv;
+        reinterpret_cast<bf16x4*>(&sh.hi[at])[q & 1] = hv;
         if (SPLIT) {
           const bf16x4 lv = {(__bf16)(v.x - (float)hv[0]), (__bf16)(v.y - (float)hv[1]),
                              (__bf16)(v.z - (float)hv[2]), (__bf16)(v.w - (float)hv[3])};
-          reinterpret_cast<bf16x4*>(&sh.lo[h * 4 + chunk])[q & 1] = lv;
+          reinterpret_cast<bf16x4*>(&sh.lo[at])[q & 1] = lv;
         }
       }
     }
   };
-  f32x4 acc[2][4][2];
+  f32x4 acc[2][4];
 #pragma unroll
   for (int zo = 0; zo < 2; ++zo)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) acc[zo][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < 4; ++mt) acc[zo][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
   load_plane(p_lo);
   {
     const uint4* w4 = reinterpret_cast<const uint4*>(w);
 #pragma unroll
     for (int k = 0; k < kWLoads; ++k) {
-      const int i = t + k * kT;
-      if ((k + 1) * kT <= kWts || i < kWts) sh.w[i ^ ((i >> 4) & 3)] = w4[i];
+      const int i = t + k * kSgMT;
+      if ((k + 1) * kSgMT <= kWts || i < kWts) sh.w[i ^ swz(i >> 2)] = w4[i];
     }
   }
   for (int p = p_lo; p <= p_hi; ++p) {
@@ -329,20 +343,21 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
     // offset dz of this plane for output z0, dz - 1 for output z0 + 1
     const int dz = p - z0 + 1;
     if (dz == 3)
-      sg_mid_plane<SPLIT, false, true>(sh, dz, wv, li, kg, acc);
+      sg_mid_plane<SPLIT, false, true>(sh, dz, wv, li, kg, nt, acc);
     else if (dz == 0 || nout == 1)
-      sg_mid_plane<SPLIT, true, false>(sh, dz, wv, li, kg, acc);
+      sg_mid_plane<SPLIT, true, false>(sh, dz, wv, li, kg, nt, acc);
     else
-      sg_mid_plane<SPLIT, true, true>(sh, dz, wv, li, kg, acc);
+      sg_mid_plane<SPLIT, true, true>(sh, dz, wv, li, kg, nt, acc);
   }
   // D tile of 16 points x 16 channels: lane holds points 4 kg + r, channel li.
   // The mask values of a plane are all requested before the first is used.
-  const float bias[2] = {b ? b[li] : 0.f, b ? b[16 + li] : 0.f};
+  const int co = nt * 16 + li;
+  const float bias = b ? b[co] : 0.f;
 #pragma unroll
   for (int zo = 0; zo < 2; ++zo) {
     if (zo >= nout) continue;
     const int64_t plane = vox_of(g, z0 + zo, 0, 0) * kSgC;
-    float mk[4][4][2];
+    float mk[4][4];
     if (mask) {
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
@@ -350,9 +365,7 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
         for (int r = 0; r < 4; ++r) {
           const int gy = min(y0 + 2 * wv + (mt >> 1), g.ny - 1);
           const int gx = min(x0 + (mt & 1) * 16 + kg * 4 + r, g.nx - 1);
-          const float* m = mask + plane + (gy * g.nx + gx) * kSgC + li;
-          mk[mt][r][0] = m[0];
-          mk[mt][r][1] = m[16];
+          mk[mt][r] = mask[plane + (gy * g.nx + gx) * kSgC + co];
         }
     }
 #pragma unroll
@@ -361,18 +374,10 @@ __global__ __launch_bounds__(kT) void k_sg_mid(SgGrid g, const float* __restrict
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int gx = x0 + (mt & 1) * 16 + kg * 4 + r;
-        float v[2];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          v[nt] = acc[zo][mt][nt][r] + bias[nt];
-          if (mask && !(mk[mt][r][nt] > 0.f)) v[nt] = 0.f;
-          if (relu) v[nt] = fmaxf(v[nt], 0.f);
-        }
-        if (gx < g.nx && gy < g.ny) {
-          float* o = out + plane + (gy * g.nx + gx) * kSgC + li;
-          o[0] = v[0];
-          o[16] = v[1];
-        }
+        float v = acc[zo][mt][r] + bias;
+        if (mask && !(mk[mt][r] > 0.f)) v = 0.f;
+        if (relu) v = fmaxf(v, 0.f);
+        if (gx < g.nx && gy < g.ny) out[plane + (gy * g.nx + gx) * kSgC + co] = v;
       }
     }
   }
@@ -490,7 +495,7 @@ __global__ __launch_bounds__(kSgWT, 3) void k_sg_wgrad(SgGrid g, int each,
         }
       } else if (s.z + 1 + s.lead < g.nz && i < kG + kA) {
         int gx = s.x0 + (i - kG) / kSgC - 1;  // x0 - 1 .. x0 + 16
-        gx = gx < 0 ? g.nx - 1 : gx == g.nx ? 0 : min(gx, g.nx - 1);
+        gx = wrapi(gx, g.nx);
         const uint32_t at = (gx * kSgC + c) * sizeof(float);
         const char* plane = reinterpret_cast<const char*>(a + vox_of(g, s.z + 1 + s.lead, 0, 0) * kSgC);
         int gy = s.y0 == 0 ? g.ny - 1 : s.y0 - 1;
@@ -904,10 +909,10 @@ void launch_mid(const Surrogate* s, hipStream_t st, const float* a, const uint16
                 const float* b, float* out, int relu, const float* mask) {
   const dim3 grid(tile_grid(s->gd).x, (unsigned)((s->gd.nz + 1) / 2));  // two planes per workgroup
   if (s->split)
-    hipLaunchKernelGGL(k_sg_mid<true>, grid, dim3(kT), sizeof(SgMidLds<true>), st, s->gd, a, w, b,
+    hipLaunchKernelGGL(k_sg_mid<true>, grid, dim3(kSgMT), sizeof(SgMidLds<true>), st, s->gd, a, w, b,
                        out, relu, mask);
   else
-    hipLaunchKernelGGL(k_sg_mid<false>, grid, dim3(kT), sizeof(SgMidLds<false>), st, s->gd, a, w, b,
+    hipLaunchKernelGGL(k_sg_mid<false>, grid, dim3(kSgMT), sizeof(SgMidLds<false>), st, s->gd, a, w, b,
                        out, relu, mask);
 }
 
