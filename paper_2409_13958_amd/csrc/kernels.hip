@@ -1080,7 +1080,7 @@ __global__ void k_rk_stage(int64_t n, const double* __restrict__ m, float* __res
   if (i < 3 * n) m32[i] = (float)m[i];
 }
 
-// k_rk_rhs of stage k and k_rk_stage of the next one: the slope at mst goes into
+// The slope of stage k and the vector of the next one: the slope at mst goes into
 // acc, and m + c k into the next stage's mst (in place of this one's) and m32.
 // One launch instead of two, and the slope itself goes to no array of its own:
 // with small cells a step is bound by its launches.
