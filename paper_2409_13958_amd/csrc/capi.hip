@@ -1371,7 +1371,7 @@ constexpr int kGsParts = 512;
 constexpr int kHostH = 64, kHostH2 = 128, kHostCoef = 192;
 static_assert(kMaxKrylov + 2 <= kHostH && kMaxKrylov + 1 <= kGsMaxVectors, "Krylov sizes");
 
-int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
+int implicit_alloc(pmfem_ctx* c, int kdim, bool adaptive) {
   pmfem_dev* d = c->dev;
   pmfem_dev::Implicit& W = d->imp;
   const int64_t n = d->n, n3 = 3 * n;
@@ -1405,6 +1405,23 @@ int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
   }
   W.kdim = kdim;
   return PMFEM_OK;
+}
+
+// Workspace for kdim Krylov vectors. Where an allocation or copy is refused,
+// what the call took is given back and the workspace is as it was before, so
+// that no later call runs on a part of one.
+int implicit_setup(pmfem_ctx* c, int kdim, bool adaptive) {
+  pmfem_dev* d = c->dev;
+  const pmfem_dev::Implicit before = d->imp;
+  const size_t held = d->allocs.size();
+  const int rc = implicit_alloc(c, kdim, adaptive);
+  if (rc) {
+    for (size_t k = held; k < d->allocs.size(); ++k) (void)hipFree(d->allocs[k]);
+    d->allocs.resize(held);
+    if (d->imp.host != before.host) (void)hipHostFree(d->imp.host);
+    d->imp = before;
+  }
+  return rc;
 }
 
 // out[j] = V_j . w for j < nv (V with leading dimension ldv); synchronises

@@ -1,0 +1,91 @@
+"""Host code that allocates, sizes and launches, on the CPU: the library runs
+in a child process on a stand-in for the HIP runtime (host_runtime.cpp), which
+records the launches and can refuse one chosen call."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+stub.stub_over.restype = ctypes.c_char_p
+stub.stub_launches.restype = stub.stub_seen.restype = ctypes.c_int64
+import numpy as np
+from paper_2409_13958_amd import binding as B, meshgen as mg
+
+def context(prob, **kw):
+    return B.Context.from_problem(prob, device=0, stream=1, **kw)
+
+def film(nx, ny, nz=1, grid=(16, 16, 4), periodic=0b011):
+    return mg.kuhn_box((nx, ny, nz), 1e-9, periodic=periodic, jitter=0.1, grid=grid)
+
+def seen(watch):
+    buf = np.zeros(4096, np.uint64)
+    return buf[:stub.stub_seen(watch, buf.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(4096))]
+
+def ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+def heff(ctx):
+    m, h = np.zeros((ctx.n, 3), np.float32), np.zeros((ctx.n, 3), np.float32)
+    return ctx.lib.pmfem_heff(ctx.h, ptr(m), ptr(h), 3, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("runtime") / "host_runtime.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC",
+                    os.path.join(HERE, "host_runtime.cpp"), "-o", str(lib)], check=True)
+    return str(lib)
+
+
+def child(runtime, code, *args):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + code, runtime, *map(str, args)],
+                       cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+# the refused call: every allocation and copy of the workspace in turn
+@pytest.mark.parametrize("scheme", ["midpoint", "adaptive"])
+@pytest.mark.parametrize("call, nth", [("hipHostGetDevicePointer", 1), ("hipHostMalloc", 1),
+                                       ("hipMemcpy", 1)]
+                         + [("hipMalloc", k) for k in range(1, 16)])
+def test_implicit_workspace_after_a_refused_call(runtime, scheme, call, nth):
+    """A step whose workspace could not be set up reports it, and the next one
+    sets up what is missing: no kernel is launched with a null buffer."""
+    child(runtime, """
+scheme, call, nth = sys.argv[2:]
+ctx = context(film(4, 4))
+m = np.zeros((ctx.n, 3)); m[:, 2] = 1.0
+
+def step(kdim):
+    if scheme == "midpoint":
+        return ctx.lib.pmfem_llg_implicit(ctx.h, ptr(m), 1e-15, 0.5, 1, 3, None, 1e-8, kdim, None)
+    dt = np.array([1e-15])
+    return ctx.lib.pmfem_llg_implicit_adaptive(ctx.h, ptr(m), 2e-15, ptr(dt), 0.5, 3, None, 1e-6,
+                                               1e-8, kdim, 0, None, None, 0)
+watches = [(k, a, stub.stub_watch(k.encode(), a)) for k, a in (
+    ("k_mid_point", 1), ("k_mid_point", 2), ("k_mid_point", 4), ("k_mid_point", 5),
+    ("k_mid_residual", 1), ("k_mid_residual", 2), ("k_mid_residual", 3), ("k_mid_residual", 4),
+    ("k_mid_residual", 5), ("k_mid_residual", 10), ("k_mid_residual", 11), ("k_mid_residual", 12),
+    ("k_gs_next", 1), ("k_gs_next", 2), ("k_gs_next", 3), ("k_gs_next", 6), ("k_gs_next", 7),
+    ("k_gs_next", 8), ("k_gs_next", 9), ("k_lincomb", 7))]
+for kdim in (4, 8):               # a first workspace, then a larger one
+    stub.stub_fail(call.encode(), ctypes.c_int64(int(nth)))
+    rc = step(kdim)
+    refused = stub.stub_failed()
+    stub.stub_fail(b"", ctypes.c_int64(0))
+    assert rc != 0 if refused else rc == 0
+    assert step(4) == 0
+    assert step(kdim) == 0
+for k, a, w in watches:
+    assert len(seen(w)) > 0 or (k, scheme) == ("k_lincomb", "midpoint")
+    assert (seen(w) != 0).all(), (k, a)
+""", scheme, call, nth)
