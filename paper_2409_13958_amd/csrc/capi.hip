@@ -589,7 +589,9 @@ bool plan_scatter_with(const HostOps& o, ScPlan& pl, std::vector<int2>& list,
   lstart[nt] = (int32_t)list.size();
   if ((int64_t)pl.fsize * (o.p <= 3 ? 4 : 1) * 4 > kScLdsBudget) return false;
   // the footprint copies, one per wavefront, at padded strides; fewer of them
-  // where a tile is large
+  // where a tile is large. Over all extents a grid may have one copy takes 32 KB
+  // at most (p = 5, 75 points along each axis), so that with the kernel's
+  // weights a launch stays within the 64 KB that need no function attribute.
   pl.sy = pl.fd[0];
   while (pl.sy % 8 != 4) ++pl.sy;
   pl.sz = pl.sy * pl.fd[1];
@@ -598,7 +600,7 @@ bool plan_scatter_with(const HostOps& o, ScPlan& pl, std::vector<int2>& list,
   pl.nw = kScWaves;
   while (pl.nw > 1 && pl.lsize * 4 * pl.nw > kScLdsBudget - kScWeights) pl.nw /= 2;
   pl.lds_bytes = pl.lsize * 4 * pl.nw;
-  return (int64_t)list.size() == o.n_unk;
+  return (int64_t)list.size() == o.n_unk && pl.lds_bytes <= kScLdsBudget - kScWeights;
 }
 
 // The scatter plan: the preferred tile sizes, else tiles dividing the
@@ -753,23 +755,6 @@ bool plan_interp(const HostOps& o, int max_xs, double want, IcPlan& pl) {
   return most > 0;
 }
 
-// The scatter kernel of order p (cells: its multi-cell form), allowed `lds`
-// bytes of dynamic LDS where that and its weights exceed the default 64 KB.
-bool scatter_lds(int p, bool cells, int lds) {
-  if (lds + kScWeights <= 65536) return true;
-  const void* f = nullptr;
-  switch (p) {
-    case 1: f = cells ? (const void*)k_anterp_scatter_cells<1> : (const void*)k_anterp_scatter<1>; break;
-    case 2: f = cells ? (const void*)k_anterp_scatter_cells<2> : (const void*)k_anterp_scatter<2>; break;
-    case 3: f = cells ? (const void*)k_anterp_scatter_cells<3> : (const void*)k_anterp_scatter<3>; break;
-    case 4: f = cells ? (const void*)k_anterp_scatter_cells<4> : (const void*)k_anterp_scatter<4>; break;
-    default: f = cells ? (const void*)k_anterp_scatter_cells<5> : (const void*)k_anterp_scatter<5>; break;
-  }
-  const bool ok = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
-  (void)hipGetLastError();
-  return ok;
-}
-
 int upload_all(pmfem_ctx* c) {
   HostOps& o = c->ops;
   pmfem_dev* d = c->dev;
@@ -854,8 +839,7 @@ int upload_all(pmfem_ctx* c) {
     std::vector<int2> list;
     std::vector<int32_t> lstart;
     std::vector<int2> tab[3];
-    d->sc_ok = plan_scatter(o, d->sp, list, lstart, tab) &&
-               scatter_lds(o.p, false, d->sp.lds_bytes);
+    d->sc_ok = plan_scatter(o, d->sp, list, lstart, tab);
     if (d->sc_ok) {
       // launch order: the tiles that hold nodes, the fullest first (in
       // sixteenths of the fullest, grid order within one)
@@ -2169,8 +2153,6 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
       (rc = batch_launch_table(b, nzm, b->zm)) || (rc = batch_launch_table(b, nic, b->ic)) ||
       (rc = batch_launch_table(b, nxl, b->xl)) || (rc = batch_launch_table(b, nyl, b->yl)))
     return rc;
-  if (!scatter_lds(b->p, true, (int)b->lds_sc))
-    return batch_err(b, PMFEM_EINVAL, "scatter tiles of the batch do not fit in LDS");
   if (b->fxy.lds > 65536) {
     int max_lds = 0;
     (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, b->device);

@@ -28,7 +28,7 @@ constexpr int kFail = 2;                // hipErrorOutOfMemory
 std::mutex mu;
 std::map<const void*, std::string> names;
 std::map<const void*, size_t> limit;
-std::map<std::string, int64_t> launches;
+std::map<std::string, int64_t> launches, attributes;
 std::vector<Watch> watches;
 std::string over;      // kernels launched over their limit
 std::string fail_call;
@@ -47,6 +47,13 @@ int get(void** p, size_t n, const char* what) {
   if (const int e = call(what)) return e;
   *p = std::calloc(n ? n : 1, 1);
   return *p ? 0 : kFail;
+}
+
+int64_t count(const std::map<std::string, int64_t>& m, const char* kernel) {
+  int64_t n = 0;
+  for (const auto& l : m)
+    if (l.first.find(kernel) != std::string::npos) n += l.second;
+  return n;
 }
 
 }  // namespace
@@ -69,12 +76,8 @@ int64_t stub_seen(int w, uint64_t* out, int64_t cap) {
   for (size_t i = 0; i < s.size() && (int64_t)i < cap; ++i) out[i] = s[i];
   return (int64_t)s.size();
 }
-int64_t stub_launches(const char* kernel) {
-  int64_t n = 0;
-  for (const auto& l : launches)
-    if (l.first.find(kernel) != std::string::npos) n += l.second;
-  return n;
-}
+int64_t stub_launches(const char* kernel) { return count(launches, kernel); }
+int64_t stub_attributes(const char* kernel) { return count(attributes, kernel); }
 
 // -- the runtime -----------------------------------------------------------
 void** __hipRegisterFatBinary(const void*) {
@@ -118,6 +121,7 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t ld
   return 0;
 }
 int hipFuncSetAttribute(const void* f, int, int value) {
+  ++attributes[names[f]];
   limit[f] = (size_t)value;
   return 0;
 }

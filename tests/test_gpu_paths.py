@@ -204,3 +204,24 @@ def test_implicit_step_solves_its_equation(nx, ny, grid, terms, dt):
     g = x - m + dt * 4e-7 * np.pi * 1.76086e11 / (1 + alpha ** 2) * c
     # Newton stops at tol; the FP64 roundings of this formula are 1e-14 of it
     assert float(g.pow(2).mean().sqrt()) <= tol * (1 + 1e-3)
+
+
+@pytest.mark.parametrize("grid, nw", [((75, 75, 50), 2), ((75, 75, 75), 1)])
+def test_scatter_of_the_largest_footprints(grid, nw):
+    """Tiles of 15 boxes at p = 5, whose footprint leaves LDS for two copies
+    or for one, against the gather by tiles."""
+    prob = mg.kuhn_box((6, 7, 6), 1e-9, periodic=0b111, jitter=0.1, grid=grid)
+    ctx = B.Context.from_problem(prob, device=0, order_p=5, near_boxes=1)
+    fd = ctx.export("sc_plan")[6:9]
+    padded = 4 * fd[2] * ((fd[0] * fd[1] - 16 + 31) // 32 * 32 + 16)
+    assert fd[0] % 8 == 4 and min(4, 1 << int(np.log2((65536 - 12288) // padded))) == nw
+    _, _, nou, _ = ctx.query()
+    m = torch.tensor(prob.m[nou], dtype=torch.float32, device="cuda")
+    h = []
+    for v in (3, 1):
+        ctx.set_variant("anterp", v)
+        h.append(torch.empty_like(m))
+        ctx.heff(m, h[-1], terms=B.TERM_MS)
+    torch.cuda.synchronize()
+    # as in the test of every order above
+    assert float((h[0] - h[1]).norm() / h[1].norm()) < 1e-5

@@ -14,7 +14,8 @@ PRELUDE = """
 import ctypes, sys
 stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 stub.stub_over.restype = ctypes.c_char_p
-stub.stub_launches.restype = stub.stub_seen.restype = ctypes.c_int64
+for f in (stub.stub_launches, stub.stub_attributes, stub.stub_seen):
+    f.restype = ctypes.c_int64
 import numpy as np
 from paper_2409_13958_amd import binding as B, meshgen as mg
 
@@ -89,3 +90,24 @@ for k, a, w in watches:
     assert len(seen(w)) > 0 or (k, scheme) == ("k_lincomb", "midpoint")
     assert (seen(w) != 0).all(), (k, a)
 """, scheme, call, nth)
+
+
+@pytest.mark.parametrize("p, rb, grid", [
+    (1, 0, (5, 7, 5)), (2, 1, (10, 10, 49)), (3, 2, (50, 50, 81)), (4, 1, (18, 18, 16)),
+    (5, 1, (14, 14, 14)), (5, 1, (75, 75, 75)), (5, 1, (125, 125, 20)),
+])
+def test_scatter_tiles_launch_without_an_attribute(runtime, p, rb, grid):
+    """The largest footprints of every order, one context's and a batch's, fit
+    in the LDS that a launch may have without a function attribute (an
+    attribute belongs to the function: one context would set another's)."""
+    child(runtime, """
+p, rb, *grid = map(int, sys.argv[2:])
+ctx = context(film(5, 5, 5, tuple(grid), 0b111), order_p=p, near_boxes=rb)
+assert heff(ctx) == 0
+b = B.Batch([ctx], stream=1)
+m, h = np.zeros((ctx.n, 3), np.float32), np.zeros((ctx.n, 3), np.float32)
+assert b.lib.pmfem_batch_heff(b.h, ptr(m), ptr(h), 3) == 0
+assert stub.stub_launches(b"k_anterp_scatter") == 2
+assert stub.stub_over() == b"", stub.stub_over()
+assert stub.stub_attributes(b"k_anterp_scatter") == 0
+""", p, rb, *grid)
