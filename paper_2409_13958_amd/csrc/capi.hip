@@ -55,6 +55,7 @@ struct pmfem_dev {
   AntPlan ap{};            // line form of anterpolation
   int32_t *ant_list = nullptr, *ant_lstart = nullptr, *ant_col = nullptr;  // its node lists
   bool ant_ok = false, ic_ok = false, fft_ok = false;  // the plans fit
+  bool fft_pick = false;      // the plane transforms are the automatic choice
   bool ant_line = false;   // false: the tile form k_anterp
   int ant_threads = 0;
   ScPlan sp{};              // scatter form of anterpolation
@@ -316,7 +317,7 @@ int select_variants(pmfem_ctx* c) {
   d->ant_scatter = va == 0 ? d->sc_ok : va == 3;
   d->ant_line = !d->ant_scatter && (va == 0 ? d->ant_ok : va == 2);
   d->ic_seg = vi == 0 ? d->ic_ok : vi == 2;
-  d->fft_plane = vf == 0 ? d->fft_ok : vf == 2;
+  d->fft_plane = vf == 0 ? d->fft_pick : vf == 2;
   const char* names_split[12] = {"k_charges", "k_anterp",    "k_r2c_x", "k_fft_y_fwd",
                                  "k_fft_z_mul", "k_fft_y_inv", "k_c2r_x", "k_interp",
                                  "k_gsum",    "k_zcorr",     "k_exch",  "-"};
@@ -802,11 +803,19 @@ int upload_all(pmfem_ctx* c) {
     int max_lds = 0;
     (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
     FftPlane& f = d->fp;
-    f.ldx = fft_stride(Mx);
-    f.ldy = fft_stride(My);
-    f.cap = std::max(pairs * f.ldx, Hx * f.ldy);
-    d->fxy.lds = (size_t)(Mx + My + 2 * f.cap) * sizeof(float2);
-    d->fft_ok = d->fxy.lds <= (size_t)max_lds;
+    auto strides = [&](int ldx, int ldy) {
+      f.ldx = ldx;
+      f.ldy = ldy;
+      f.cap = std::max(pairs * f.ldx, Hx * f.ldy);
+      d->fxy.lds = (size_t)(Mx + My + 2 * f.cap) * sizeof(float2);
+      return d->fxy.lds <= (size_t)max_lds;
+    };
+    // at strides without padding, where only those fit, on request alone: the
+    // bank conflicts cost more than the passes saved (48 x 400 x 4 points 52 us
+    // against 27 one axis at a time, 125 x 160 x 4 50 against 24, 490 x 40 x 8 32
+    // against 26)
+    d->fft_pick = strides(fft_stride(Mx), fft_stride(My));
+    d->fft_ok = d->fft_pick || strides(Mx, My);
     f.nsplit = fft_split(o.N[2]);
     d->fxy.T = fft_threads(std::max(pairs * Mx, Hx * My), 1024);
     if (d->fft_ok && d->fxy.lds > 65536) {
@@ -816,6 +825,7 @@ int upload_all(pmfem_ctx* c) {
                   hipFuncSetAttribute((const void*)k_fft_yx_inv,
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
                                       max_lds) == hipSuccess;
+      d->fft_pick = d->fft_pick && d->fft_ok;
       (void)hipGetLastError();
     }
     d->fx = fft_launch((int64_t)pairs * o.N[2], Mx, 1, 16);
@@ -2046,7 +2056,7 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     const GridParams& g = b->cells[c]->dev->g;
     const int Hx = g.M[0] / 2 + 1;
     zlines += (int64_t)g.M[1] * Hx;
-    if (b->cells[c]->dev->fft_ok) {
+    if (b->cells[c]->dev->fft_pick) {
       planes += g.N[2];
     } else {
       xlines += (int64_t)((g.N[1] + 1) / 2) * g.N[2];
@@ -2131,7 +2141,7 @@ int batch_setup(pmfem_batch* b, int32_t spmv_lanes) {
     // FFT: whole z-planes in LDS where they fit, else one axis per pass
     t.fp = d->fp;
     t.bx = t.by = 1;
-    if (d->fft_ok) {
+    if (d->fft_pick) {
       t.fp.nsplit = fft_split(planes);
       nxy[c] = (int64_t)g.N[2] * t.fp.nsplit;
       widest(b->fxy, d->fxy);

@@ -225,3 +225,30 @@ def test_scatter_of_the_largest_footprints(grid, nw):
     torch.cuda.synchronize()
     # as in the test of every order above
     assert float((h[0] - h[1]).norm() / h[1].norm()) < 1e-5
+
+
+def convolution_error(ctx, seed):
+    """Relative L2 error of the grid convolution against numpy in 64 bits, and
+    the bound: about log2(M) roundings of 2^-24 per axis and direction, at most
+    doubled."""
+    info = ctx.export("grid_info")
+    N, M = info[:3].astype(int), info[3:6].astype(int)
+    q = np.random.default_rng(seed).standard_normal(N[::-1]).astype(np.float32)
+    u = torch.empty(tuple(N[::-1]), dtype=torch.float32, device="cuda")
+    ctx.grid_convolve(torch.tensor(q, device="cuda"), u)
+    khat = ctx.export("khat").reshape(M[2], M[1], M[0] // 2 + 1).astype(np.float64)
+    s = tuple(M[::-1])
+    ref = np.fft.irfftn(np.fft.rfftn(q.astype(np.float64), s=s, axes=(0, 1, 2)) * khat, s=s,
+                        axes=(0, 1, 2))[:N[2], :N[1], :N[0]] * np.prod(M)
+    err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
+    return err, 2 * 2 * np.log2(np.prod(M)) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("grid", [(48, 400, 4), (60, 324, 5), (125, 160, 4), (392, 50, 4),
+                                  (400, 49, 4), (490, 40, 4)])
+def test_planes_that_fit_in_lds_only_at_unpadded_strides(grid):
+    ctx = B.Context.from_problem(mg.kuhn_box((4, 4, 2), 1e-9, periodic=0b011, grid=grid,
+                                             m=[0.0, 0.0, 1.0]), device=0)
+    ctx.set_variant("fft", 2)
+    err, bound = convolution_error(ctx, grid[0])
+    assert err < bound

@@ -111,3 +111,31 @@ assert stub.stub_launches(b"k_anterp_scatter") == 2
 assert stub.stub_over() == b"", stub.stub_over()
 assert stub.stub_attributes(b"k_anterp_scatter") == 0
 """, p, rb, *grid)
+
+
+def test_plane_transforms_of_every_extent_that_fits(runtime):
+    """The plane form of the transforms can be asked for wherever the twiddle
+    tables and two buffers of a plane's row pairs or columns fit in LDS, and
+    nowhere else; it is the automatic choice, alone and in a batch, where they
+    also fit at padded strides."""
+    child(runtime, """
+edge = [(48, 400), (49, 400), (60, 324), (125, 160), (392, 50), (400, 49), (486, 40), (490, 40)]
+for nx, ny in edge + [(16, 16), (128, 128), (140, 140), (144, 140), (490, 42), (512, 512)]:
+    ctx = context(film(4, 4, 2, (nx, ny, 4)))
+    Hx, pairs = nx // 2 + 1, (ny + 1) // 2
+    fits = 8 * (nx + ny + 2 * max(pairs * nx, Hx * ny)) <= 160 * 1024
+    assert (ctx.lib.pmfem_set_variant(ctx.h, b"fft", 2) == 0) == fits, (nx, ny)
+    assert fits or (nx, ny) not in edge
+    planes = lambda: stub.stub_launches(b"k_fft_xy_fwd")
+    before = planes()
+    assert heff(ctx) == 0
+    assert planes() - before == int(fits)
+    ctx.lib.pmfem_set_variant(ctx.h, b"fft", 0)
+    b = B.Batch([ctx], stream=1)
+    before = planes()
+    assert heff(ctx) == 0
+    m = np.zeros((ctx.n, 3), np.float32)
+    assert b.lib.pmfem_batch_heff(b.h, ptr(m), ptr(m.copy()), 3) == 0
+    assert planes() - before == 2 * int(fits and (nx, ny) not in edge)
+    assert stub.stub_over() == b"", stub.stub_over()
+""")
