@@ -5,6 +5,8 @@
 #include <atomic>
 #include <cstdint>
 #include <cstdlib>
+#include <exception>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -103,7 +105,9 @@ inline unsigned host_threads() {
   return hw > 64 ? 64 : hw;
 }
 
-// Dynamic parallel loop over [0, n) in chunks of `grain`.
+// Dynamic parallel loop over [0, n) in chunks of `grain`. What f throws ends the
+// loop and is thrown again here once every thread has ended; threads that
+// cannot be started leave their share to the others.
 template <class F>
 void parallel_for(int64_t n, F&& f, int64_t grain = 256) {
   if (n <= 0) return;
@@ -113,18 +117,30 @@ void parallel_for(int64_t n, F&& f, int64_t grain = 256) {
     return;
   }
   std::atomic<int64_t> next(0);
+  std::mutex mu;
+  std::exception_ptr thrown;
   auto work = [&]() {
-    for (;;) {
-      int64_t s = next.fetch_add(grain);
-      if (s >= n) break;
-      int64_t e = s + grain < n ? s + grain : n;
-      for (int64_t i = s; i < e; ++i) f(i);
+    try {
+      for (;;) {
+        int64_t s = next.fetch_add(grain);
+        if (s >= n) break;
+        int64_t e = s + grain < n ? s + grain : n;
+        for (int64_t i = s; i < e; ++i) f(i);
+      }
+    } catch (...) {
+      next = n;
+      std::lock_guard<std::mutex> lock(mu);
+      if (!thrown) thrown = std::current_exception();
     }
   };
   std::vector<std::thread> th;
-  for (unsigned t = 1; t < nt; ++t) th.emplace_back(work);
+  try {
+    for (unsigned t = 1; t < nt; ++t) th.emplace_back(work);
+  } catch (...) {
+  }
   work();
   for (auto& t : th) t.join();
+  if (thrown) std::rethrow_exception(thrown);
 }
 
 }  // namespace pmfem

@@ -139,3 +139,36 @@ for nx, ny in edge + [(16, 16), (128, 128), (140, 140), (144, 140), (490, 42), (
     assert planes() - before == 2 * int(fits and (nx, ny) not in edge)
     assert stub.stub_over() == b"", stub.stub_over()
 """)
+
+
+def test_an_exception_in_a_parallel_loop_reaches_its_caller(tmp_path):
+    """The set-up's loops run on threads that allocate: what one of them throws
+    is thrown to the loop's caller (which reports it as a status), once all
+    threads have ended, and does not end the process."""
+    src = tmp_path / "loop.cpp"
+    src.write_text("""
+#include "internal.h"
+#include <cstdio>
+#include <new>
+int main() {
+  for (int64_t bad : {0, 1, 777, 4095}) {
+    std::atomic<int> in(0);
+    bool caught = false;
+    try {
+      pmfem::parallel_for(4096, [&](int64_t i) {
+        ++in;
+        if (i == bad) { --in; throw std::bad_alloc(); }
+        --in;
+      }, 1);
+    } catch (const std::bad_alloc&) { caught = true; }
+    if (!caught || in != 0) return 1;
+  }
+  std::atomic<int64_t> sum(0);
+  pmfem::parallel_for(1001, [&](int64_t i) { sum += i; }, 7);
+  return sum == 1001 * 500 ? 0 : 2;
+}
+""")
+    exe = tmp_path / "loop"
+    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{ROOT}/paper_2409_13958_amd/csrc",
+                    f"-I{ROOT}/include", str(src), "-o", str(exe), "-lpthread"], check=True)
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
