@@ -1252,13 +1252,15 @@ int run_heff(pmfem_ctx* c, const float* m, float* h, uint32_t terms, const doubl
     }
     const size_t gbytes = (size_t)g.N[0] * g.N[1] * g.N[2] * sizeof(float);
     if (d->tap_q) (void)hipMemcpyAsync(d->tap_q, d->grid, gbytes, hipMemcpyDeviceToDevice, s);
+    hipError_t net_err = hipSuccess;
     if (d->net_on) {
-      (void)sg_apply(d->net, s, d->grid, d->grid);
+      net_err = sg_apply(d->net, s, d->grid, d->grid);
     } else {
       convolve(d, s, d->grid, d->grid, d->spec, d->g.gmode, mark);
     }
     if (d->tap_u) (void)hipMemcpyAsync(d->tap_u, d->grid, gbytes, hipMemcpyDeviceToDevice, s);
     if (overlap) (void)hipStreamWaitEvent(s, d->join, 0);
+    if (net_err != hipSuccess) return hip_err(c, net_err, "surrogate launch");
     mark(7, 0);
     {
       const IcPlan& pl = d->ic_seg ? d->icp : d->icp_small;

@@ -26,13 +26,6 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
 }
 __device__ __forceinline__ float bf16_float(uint32_t h) { return __uint_as_float(h << 16); }
 
-inline uint16_t bf16_bits_host(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 // v in [-1, n] on a circular axis of n points; a tile's points past n, which
 // nothing reads or meets only zeros, take the last one's. A remainder here took
 // 40 instructions per staged value.
@@ -902,6 +895,7 @@ dim3 tile_grid(const SgGrid& g) {
 
 template <class T>
 hipError_t alloc(T** p, int64_t count) {
+  *p = nullptr;
   return hipMalloc((void**)p, (size_t)count * sizeof(T));
 }
 
@@ -1021,8 +1015,17 @@ hipError_t sg_ensure_training(Surrogate* s, int n_loss) {
         (e = alloc(&s->y, s->nvox)) ||
         (e = alloc(&s->gy, s->nvox)) || (e = alloc(&s->qbuf, s->nvox)) ||
         (e = alloc(&s->ubuf, s->nvox)) ||
-        (e = alloc(&s->part, std::max<int64_t>((int64_t)kSgWBlocks * kSgWRow, (int64_t)kSgWPart * kSgThin))))
+        (e = alloc(&s->part, std::max<int64_t>((int64_t)kSgWBlocks * kSgWRow, (int64_t)kSgWPart * kSgThin)))) {
+      // back to the buffers of inference (none held: sg_apply refuses)
+      float** bufs[] = {&s->act, &s->gA, &s->gB, &s->y, &s->gy, &s->qbuf, &s->ubuf, &s->part};
+      for (float** b : bufs) {
+        (void)hipFree(*b);
+        *b = nullptr;
+      }
+      (void)alloc(&s->act, 2 * s->nvox * kSgC);
+      (void)hipGetLastError();
       return e;
+    }
     s->trained_buffers = true;
   }
   if (n_loss > s->loss_cap) {
@@ -1093,11 +1096,13 @@ hipError_t sg_get_params(const Surrogate* s, float* host, hipStream_t st) {
 }
 
 hipError_t sg_apply(Surrogate* s, hipStream_t st, const float* Q, float* U) {
+  if (!s->act) return hipErrorOutOfMemory;
   forward(s, st, Q, s->trained_buffers, U, s->s_out);
   return hipGetLastError();
 }
 
 hipError_t sg_profile(Surrogate* s, hipStream_t st, const float* Q, float* U, int reps, double* ms) {
+  if (!s->act) return hipErrorOutOfMemory;
   const int D = s->depth;
   std::vector<hipEvent_t> ev(2 * D, nullptr);
   hipError_t e = hipSuccess;

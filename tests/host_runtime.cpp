@@ -32,14 +32,17 @@ std::map<std::string, int64_t> launches, attributes;
 std::vector<Watch> watches;
 std::string over;      // kernels launched over their limit
 std::string fail_call;
-int64_t fail_in = 0;   // calls of fail_call until the one that fails (0: none)
+int64_t fail_in = 0;     // calls of fail_call until the first that fails (0: none)
+int64_t fail_more = 0;   // and how many fail from then on
 Dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
 void* cfg_stream;
 
 int call(const char* what) {
   std::lock_guard<std::mutex> lock(mu);
-  return fail_in > 0 && fail_call == what && --fail_in == 0 ? kFail : 0;
+  if (fail_call != what || fail_more == 0 || (fail_in > 0 && --fail_in > 0)) return 0;
+  --fail_more;
+  return kFail;
 }
 
 int get(void** p, size_t n, const char* what) {
@@ -61,10 +64,12 @@ int64_t count(const std::map<std::string, int64_t>& m, const char* kernel) {
 extern "C" {
 
 // -- for the tests ---------------------------------------------------------
-void stub_fail(const char* what, int64_t nth) {
+void stub_fail_run(const char* what, int64_t nth, int64_t calls) {
   fail_call = what;
   fail_in = nth;
+  fail_more = calls;
 }
+void stub_fail(const char* what, int64_t nth) { stub_fail_run(what, nth, 1); }
 int stub_failed() { return fail_in == 0; }
 const char* stub_over() { return over.c_str(); }
 int stub_watch(const char* kernel, int arg) {

@@ -172,3 +172,36 @@ int main() {
     subprocess.run(["g++", "-O1", "-std=c++17", f"-I{ROOT}/paper_2409_13958_amd/csrc",
                     f"-I{ROOT}/include", str(src), "-o", str(exe), "-lpthread"], check=True)
     assert subprocess.run([str(exe)], timeout=60).returncode == 0
+
+
+@pytest.mark.parametrize("nth, more", [(k, 1) for k in range(1, 9)] + [(1, 2), (8, 2)])
+def test_surrogate_after_refused_training_buffers(runtime, nth, more):
+    """A gradient whose buffers are refused leaves the network usable for
+    inference and for a later gradient; where even the buffers of inference
+    are refused afterwards (more = 2), inference is refused too. No kernel is
+    launched with a null buffer."""
+    child(runtime, """
+nth, more = map(int, sys.argv[2:])
+ctx = context(film(4, 4))
+ctx.surrogate_init(depth=4)
+p, _ = ctx.surrogate_get_params()
+ctx.surrogate_set_params(p, scales=(1.0, 1.0))
+q = np.zeros(ctx._grid_shape(), np.float32); u = q.copy()
+watches = [(k, a, stub.stub_watch(k.encode(), a)) for k, a in (
+    ("k_sg_in", 1), ("k_sg_in", 5), ("k_sg_mid", 1), ("k_sg_mid", 4), ("k_sg_out", 1),
+    ("k_sg_out", 5), ("k_sg_loss", 4), ("k_sg_wgradE", 4))]
+apply = lambda: ctx.lib.pmfem_surrogate_apply(ctx.h, ptr(q), ptr(u))
+grad = lambda: ctx.lib.pmfem_surrogate_loss_grad(ctx.h, ptr(q), ptr(u), None, None, 0)
+profile = lambda: ctx.lib.pmfem_surrogate_profile(ctx.h, ptr(q), ptr(u), 1, ptr(np.zeros(12)))
+stub.stub_fail_run(b"hipMalloc", ctypes.c_int64(nth), ctypes.c_int64(more))
+assert grad() != 0
+stub.stub_fail(b"", ctypes.c_int64(0))
+# the second refused call is the one that would bring inference back
+assert (apply() == 0) == (more == 1)
+assert (profile() == 0) == (more == 1)
+ctx.surrogate_enable(True)
+assert (heff(ctx) == 0) == (more == 1)
+assert grad() == 0 and apply() == 0 and profile() == 0 and heff(ctx) == 0
+for k, a, w in watches:
+    assert len(seen(w)) > 0 and (seen(w) != 0).all(), (k, a)
+""", nth, more)
