@@ -1358,9 +1358,11 @@ int ready(pmfem_ctx* c) {
 
 constexpr int kMaxKrylov = 60;
 constexpr int kDotParts = 1024;
-// workgroups of the Gram-Schmidt kernels: each sums the shares of all, so more
-// than two per compute unit would read more shares than basis
-constexpr int kGsParts = 512;
+// most workgroups of the Gram-Schmidt kernels. Each sums the shares of all, but
+// the reads of the basis need them: at 1.03 M unknowns and ten vectors the
+// products take 38 us with 1024 and 48 with 512, the update 28 and 31, at 590 k
+// 20 and 24, 17 and 17; smaller cells have one per 256 unknowns
+constexpr int kGsParts = 1024;
 // the pinned host buffer: reductions at [0, 62), the Gram-Schmidt products of
 // the two passes at kHostH and kHostH2 (written by the kernels), coefficients
 // at kHostCoef
@@ -1502,7 +1504,7 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
                        alpha, theta, W.G, W.Minv, W.part);
     // the residual's norm and, for the case that it is not small enough yet,
     // V_0 = G / beta, preconditioned
-    hipLaunchKernelGGL(k_gs_next, dim3(std::min(b1, 2u * kGsParts)), dim3(256), 0, s, n,
+    hipLaunchKernelGGL(k_gs_next, dim3(P), dim3(256), 0, s, n,
                        (const double*)W.G, (const double*)W.Minv, (const double*)W.part, (int)P, 0,
                        W.V, W.z, W.z32, W.host_dev);
     hipError_t e = hipStreamSynchronize(s);
@@ -1543,7 +1545,7 @@ int newton_solve(pmfem_ctx* c, const double* r, const double* m, double theta, d
                          W.w, W.part);
       hipLaunchKernelGGL(k_gs_update, dim3(P), dim3(256), 0, s, n3, (const float*)W.V, n3, nv, 1,
                          W.w, W.part, W.host_dev + kHostH2);
-      hipLaunchKernelGGL(k_gs_next, dim3(std::min(b1, 2u * kGsParts)), dim3(256), 0, s, n,
+      hipLaunchKernelGGL(k_gs_next, dim3(P), dim3(256), 0, s, n,
                          (const double*)W.w, (const double*)W.Minv, (const double*)W.part, (int)P,
                          nv, W.V + (int64_t)nv * n3, W.z, W.z32, W.host_dev);
       ++*krylov_its;

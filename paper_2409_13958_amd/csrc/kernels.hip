@@ -1275,8 +1275,9 @@ __global__ void k_mid_normalize(int64_t n, double* __restrict__ x) {
 // nothing sums the workgroups' shares in a launch of its own - each workgroup
 // of the reader sums all of them, in the same order - and whether the second
 // pass of the Gram-Schmidt is needed is read on the device.
-// Film of 8 k nodes, two steps: 1405 us with a launch per operation, a
-// copy and a wait per pass, 1130 us so.
+// Film of 12 k unknowns, one step of 7 vectors: 1120 us with a launch per
+// operation, a copy and a wait per pass, 805 us so; 138 k unknowns and 25
+// vectors 5150 and 4570, 1.03 M and 26 vectors 21.4 and 19.6 ms.
 //
 // Rows of part (stride nparts), for nv basis vectors: [0, nv) V_j . w,
 // nv: |w|^2, nv + 1: |w|^2 after the first pass, nv + 2: after the second,
@@ -1290,13 +1291,22 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 }
 
 // out[r] = sum over b < nparts of part[r * nparts + b] for r < rows, by all 256
-// threads: 16 lanes a row
+// threads: 16 lanes a row, each with 16 loads in flight. With one load behind
+// the other's addition a kernel waited some 10 us for the shares of 512
+// workgroups: k_gs_update at 138 k nodes and 8 vectors took 17 us, now 8.
 __device__ __forceinline__ void sum_rows(const double* __restrict__ part, int nparts, int rows,
                                          double* out) {
   const int l = threadIdx.x & 15;
   for (int r = threadIdx.x >> 4; r < rows; r += 16) {
+    const double* p = part + (int64_t)r * nparts;
     double v = 0.0;
-    for (int b = l; b < nparts; b += 16) v += part[(int64_t)r * nparts + b];
+    for (int b = l; b < nparts; b += 16 * 16) {
+      double x[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) x[k] = b + 16 * k < nparts ? p[b + 16 * k] : 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v += x[k];
+    }
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
     if (l == 0) out[r] = v;

@@ -252,3 +252,13 @@ def test_planes_that_fit_in_lds_only_at_unpadded_strides(grid):
     ctx.set_variant("fft", 2)
     err, bound = convolution_error(ctx, grid[0])
     assert err < bound
+
+
+@pytest.mark.parametrize("nx, ny", [
+    (64, 65),      # 17 workgroups: a second share for one of the 16 lanes of a sum
+    (256, 257),    # 257: a second batch of loads
+    (516, 512),    # more nodes than 1024 workgroups take at once
+])
+def test_implicit_step_by_number_of_workgroups(nx, ny):
+    """The sums over the workgroups' shares, as in the test above."""
+    test_implicit_step_solves_its_equation(nx, ny, (128, 128, 4), 1, 1e-13)
