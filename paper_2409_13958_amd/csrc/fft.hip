@@ -6,9 +6,9 @@
 //
 // Any extent whose prime factors are 2, 3, 5 and 7. Every transform is a
 // Stockham autosort in LDS between two buffers, natural order in and out, of
-// as few passes as the radices 2 .. 10 allow (FftAxis). Pass with Ns = product of the radices done
-// so far and radix R: butterfly j of the n / R reads a_q = src[j + q n / R],
-// q < R, multiplies a_q by w^(q k), k = j mod Ns, w = exp(-2 pi i / (Ns R)),
+// as few passes as the radices 2 .. 10 allow (FftAxis). Pass with Ns = product
+// of the radices done so far and radix R: butterfly j of the n / R reads a_q =
+// src[j + q n / R], q < R, multiplies a_q by w^(q k), k = j mod Ns, w = exp(-2 pi i / (Ns R)),
 // forms the R-point DFT in registers and writes b_p to
 // dst[(j / Ns) Ns R + k + p Ns]. The inverse is the conjugate of the transform
 // of the conjugate, so the z pass holds one copy of the passes: on a small grid
@@ -21,12 +21,16 @@
 // and are bound by the latency of their LDS passes, so the passes are few, a
 // thread has one or two butterflies in each, and where a grid has few planes
 // several workgroups share one. Radices above 10 gain a pass at 128 and 256
-// points but leave too few threads (radix 16: 52 us at 128^3 against 45).
+// points but leave too few threads (radix 16: 52 us at 128^3 against 45 then).
+// A workgroup of a small grid spends a third of its time on its one round trip
+// to memory, so tables and lines are requested together (Tables).
+//
 // Radix 2 in place with stride-8 passes (16-way bank conflicts) and mixed
-// radices with integer divisions took, the three kernels together: 57 us at
-// 128^3 points, against 45 now; 42 x 40 x 30: 36 us against 20; 64^3: 22 against
-// 23, and 64 x 64 x 128 points, padded, 25 against 23; the planes of 16 films of 16^2 to 180^2 points in one batch: 93 against
-// 35.
+// radices with integer divisions took, us per convolution: 57 at 128^3 points,
+// against 43 now; 96^3 70 and 29; 64^3 20.2 and 19.3; 42 x 40 x 15 30 and 16;
+// 64 x 64 x 128, z alone periodic, 50 and 40; 256 x 256 x 4 57 and 27. Small
+// grids of powers of two are the exception: 32^3 14.3 and 15.6, 16^3 13.2 and
+// 13.7, 16 x 16 x 64 15.4 and 16.1.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -252,9 +256,26 @@ __device__ __forceinline__ void fft_lines(Lines& a, Lines& b, const FftAxis& f, 
   }
 }
 
-__device__ __forceinline__ void copy_table(float2* dst, const float2* __restrict__ src, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
-}
+// The twiddle tables at the start of LDS (a of na values, then b of nb): each
+// thread's first value is requested before the lines' loads and stored after
+// them, so that a workgroup waits for memory once. With the tables copied
+// first a convolution took 17.2 us instead of 15.6 at 32^3 points, 14.9 instead
+// of 13.7 at 16^3, 44.9 instead of 42.8 at 128^3.
+struct Tables {
+  const float2 *a, *b;
+  int na, n;
+  float2 first;
+  __device__ __forceinline__ Tables(const float2* __restrict__ a_, int na_,
+                                    const float2* __restrict__ b_, int nb_)
+      : a(a_), b(b_), na(na_), n(na_ + nb_), first(make_float2(0.f, 0.f)) {
+    if ((int)threadIdx.x < n) first = at(threadIdx.x);
+  }
+  __device__ __forceinline__ float2 at(int i) const { return i < na ? a[i] : b[i - na]; }
+  __device__ __forceinline__ void store(float2* sh) const {
+    if ((int)threadIdx.x < n) sh[threadIdx.x] = first;
+    for (int i = threadIdx.x + blockDim.x; i < n; i += blockDim.x) sh[i] = at(i);
+  }
+};
 
 // spectrum of row y (odd: y + 1 of the pair) at k from the complex line of
 // the pair: X_y = (Z[k] + conj Z[-k]) / 2, X_{y+1} = (Z[k] - conj Z[-k]) / (2i)
@@ -292,8 +313,7 @@ __device__ __forceinline__ void fft_xy_fwd_body(const GridParams& g, const float
   if (nk <= 0) return;  // the whole workgroup
   float2 *tx = sh, *ty = sh + Mx;
   Lines A = {ty + My, pl.ldx}, B = {ty + My + pl.cap, pl.ldx};
-  copy_table(tx, twx, Mx);
-  copy_table(ty, twy, My);
+  const Tables tw(twx, Mx, twy, My);
   const int64_t qz = (int64_t)z * Ny * Nx;
   const float iMx = recip(Mx);
   batched<4>(
@@ -311,6 +331,7 @@ __device__ __forceinline__ void fft_xy_fwd_body(const GridParams& g, const float
         const int l = fdiv(idx, Mx, iMx);
         A.at(l, idx - l * Mx) = v;
       });
+  tw.store(sh);
   const float ipr = recip(pairs);
   // the x lines, then (from their buffer into the other one) the columns
 #pragma unroll
@@ -362,8 +383,7 @@ __device__ __forceinline__ void fft_yx_inv_body(const GridParams& g,
   if (nl <= 0) return;  // the whole workgroup
   float2 *tx = sh, *ty = sh + Mx;
   Lines A = {ty + My, pl.ldy}, B = {ty + My + pl.cap, pl.ldy};
-  copy_table(tx, twx, Mx);
-  copy_table(ty, twy, My);
+  const Tables tw(twx, Mx, twy, My);
   const float2* Sz = spec + (int64_t)z * My * Hx;
   const float iHx = recip(Hx), inl = recip(nl);
   batched<8>(
@@ -372,6 +392,7 @@ __device__ __forceinline__ void fft_yx_inv_body(const GridParams& g,
         const int ky = fdiv(idx, Hx, iHx);
         A.at(idx - ky * Hx, ky) = conj(v);
       });
+  tw.store(sh);
 #pragma unroll
   for (int axis = 1; axis >= 0; --axis) {
     if (axis == 0) {
@@ -409,7 +430,7 @@ __device__ __forceinline__ void r2c_x_body(const GridParams& g, const float* __r
   extern __shared__ float2 sh[];
   const int Mx = g.M[0], Hx = Mx / 2 + 1, Nx = g.N[0], Ny = g.N[1], ld = fft_stride(Mx);
   Lines A = {sh + Mx, ld}, D = {sh + Mx + B * ld, ld};
-  copy_table(sh, twx, Mx);
+  const Tables tw(twx, Mx, nullptr, 0);
   const int pairs = (Ny + 1) / 2;
   const int l0 = blk * B, nl = min(pairs * g.N[2] - l0, B);
   const float iMx = recip(Mx), iHx = recip(Hx), ipr = recip(pairs);
@@ -429,6 +450,7 @@ __device__ __forceinline__ void r2c_x_body(const GridParams& g, const float* __r
         const int l = fdiv(idx, Mx, iMx);
         A.at(l, idx - l * Mx) = v;
       });
+  tw.store(sh);
   __syncthreads();
   fft_lines(A, D, g.fa[0], nl, sh);
   for (int idx = threadIdx.x; idx < nl * Hx; idx += blockDim.x) {
@@ -447,7 +469,7 @@ __device__ __forceinline__ void c2r_x_body(const GridParams& g, const float2* __
   extern __shared__ float2 sh[];
   const int Mx = g.M[0], Hx = Mx / 2 + 1, Nx = g.N[0], Ny = g.N[1], ld = fft_stride(Mx);
   Lines A = {sh + Mx, ld}, D = {sh + Mx + B * ld, ld};
-  copy_table(sh, twx, Mx);
+  const Tables tw(twx, Mx, nullptr, 0);
   const int pairs = (Ny + 1) / 2;
   const int l0 = blk * B, nl = min(pairs * g.N[2] - l0, B);
   const float iHx = recip(Hx), iNx = recip(Nx), ipr = recip(pairs);
@@ -460,6 +482,7 @@ __device__ __forceinline__ void c2r_x_body(const GridParams& g, const float2* __
     A.at(l, k) = pair_line(a, b, false);
     if (k > 0 && Mx - k >= Hx) A.at(l, Mx - k) = pair_line(a, b, true);
   }
+  tw.store(sh);
   __syncthreads();
   fft_lines(A, D, g.fa[0], nl, sh);
   for (int idx = threadIdx.x; idx < nl * Nx; idx += blockDim.x) {
@@ -480,7 +503,7 @@ __device__ __forceinline__ void fft_y_body(const GridParams& g, float2* __restri
   const int My = g.M[1], Hx = g.M[0] / 2 + 1, ld = fft_stride(My);
   const int n_in = inverse ? My : g.N[1], n_out = inverse ? g.N[1] : My;
   Lines A = {sh + My, ld}, D = {sh + My + B * ld, ld};
-  copy_table(sh, twy, My);
+  const Tables tw(twy, My, nullptr, 0);
   const int groups = (Hx + B - 1) / B, z = blk / groups;
   const int k0 = (blk - z * groups) * B, nb = min(Hx - k0, B);
   const float inb = recip(nb);
@@ -495,6 +518,7 @@ __device__ __forceinline__ void fft_y_body(const GridParams& g, float2* __restri
         const int y = fdiv(idx, nb, inb);
         A.at(idx - y * nb, y) = inverse ? conj(v) : v;
       });
+  tw.store(sh);
   __syncthreads();
   fft_lines(A, D, g.fa[1], nb, sh);
   for (int idx = threadIdx.x; idx < nb * n_out; idx += blockDim.x) {
@@ -514,7 +538,7 @@ __device__ __forceinline__ void fft_z_mul_body(const GridParams& g, float2* __re
   const int Mz = g.M[2], Hx = g.M[0] / 2 + 1, ld = fft_stride(Mz), Nz = g.N[2];
   const int64_t plane = (int64_t)g.M[1] * Hx, c0 = (int64_t)blk * B;
   Lines A = {sh + Mz, ld}, D = {sh + Mz + B * ld, ld};
-  copy_table(sh, twz, Mz);
+  const Tables tw(twz, Mz, nullptr, 0);
   const int nb = (int)((plane - c0) < B ? (plane - c0) : B);
   const float inb = recip(nb);
   // the first values of the spectrum of K, requested with the lines
@@ -536,6 +560,7 @@ __device__ __forceinline__ void fft_z_mul_body(const GridParams& g, float2* __re
         const int z = fdiv(idx, nb, inb);
         A.at(idx - z * nb, z) = v;
       });
+  tw.store(sh);
   // the product with K, conjugated for the inverse
   auto scale = [&](int idx, float k) {
     const int kz = fdiv(idx, nb, inb);
