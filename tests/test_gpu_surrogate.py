@@ -443,3 +443,77 @@ def test_surrogate_rejects_bad_use():
             wire.surrogate_init(3)               # not a film
     finally:
         wire.close()
+
+
+def bf16_parts(x):
+    """x as three BF16 parts that hold its 24 bits (x in [2^-100, 2^100])."""
+    out = []
+    for _ in range(3):
+        out.append(bf16_round(x))
+        x = (x - out[-1]).astype(np.float32)
+    assert not x.any()
+    return [p.astype(np.float64) for p in out]
+
+
+@pytest.mark.parametrize("grid", [(16, 16, 4), (32, 20, 5), (35, 18, 6), (48, 12, 4)])
+def test_middle_weight_gradient_of_one_product_keeps_fp32_accuracy(grid):
+    """Every entry a single product, so that no averaging over points hides
+    how it is formed: the first layer scales its input (its output is known bit
+    for bit), the last reads one point, and the target differs from the
+    network's own output at one point only. Points at the faces, the wrapped
+    edges and the tile edges of the grid.
+
+    The product's FP32 operands are split into three BF16 parts, of whose nine
+    products the three below 2^-26 of the whole are left out; adding the others
+    from the smallest on rounds the whole once (2^-24, or 2^-23 if the matrix
+    cores cut off) and parts of 2^-8 of it before: 2^-23 + 2^-25 at most."""
+    bound = 2.0 ** -23 + 2.0 ** -25
+    nx, ny, nz = grid
+    prob = mg.kuhn_box((8, 8, 2), 1e-9, periodic=0b011, jitter=0.1, grid=grid)
+    c = B.Context.from_problem(prob, device=0)
+    try:
+        c.surrogate_init(3, seed=1)
+        rng = np.random.default_rng(nx * ny)
+        shapes = [(C, 1, 3, 3, 3), (C, C, 3, 3, 3), (1, C, 3, 3, 3)]
+        W = [np.zeros(s, np.float32) for s in shapes]
+        b = [np.zeros(s[0], np.float32) for s in shapes]
+        W[0][:, 0, 1, 1, 1] = bf16_round(rng.uniform(1.0, 2.0, C))
+        W[1][:, :, 1, 1, 1] = bf16_round(rng.uniform(0.01, 0.02, (C, C)))   # positive outputs
+        W[2][0, :, 1, 1, 1] = bf16_round(rng.uniform(0.5, 1.0, C) * rng.choice([-1, 1], C))
+        c.surrogate_set_params(flat([(w, v) for w, v in zip(W, b)]), scales=(1.0, 1.0))
+        assert c._grid_shape() == (nz, ny, nx)
+        q = rng.uniform(0.5, 1.5, (nz, ny, nx)).astype(np.float32)
+        qd = torch.tensor(q, device="cuda")
+        y = torch.empty_like(qd)
+        c.surrogate_apply(qd, y)
+        a = W[0][:, 0, 1, 1, 1][:, None, None, None] * q            # one rounding, as in FP32
+        missed = 0.0
+        for z, yy, x in [(1, 5, 7), (0, 0, 0), (nz - 1, ny - 1, nx - 1), (nz - 1, 0, min(16, nx - 1)),
+                         (2, min(8, ny - 1), 15), (0, 7, nx - 1)]:
+            t = y.clone()
+            t[z, yy, x] -= float(rng.uniform(0.3, 0.7))
+            d = (y[z, yy, x] - t[z, yy, x]).cpu().numpy()           # FP32
+            gy = np.float32(np.float32(2.0) / np.float32(nx * ny * nz)) * d
+            gr = (W[2][0, :, 1, 1, 1] * gy).astype(np.float32)
+            print(f"[gpu surrogate] one product, grid {grid}, point {(x, yy, z)}", flush=True)
+            _, g = c.surrogate_loss_grad(qd, t)
+            gW, gb = unflat(g, 3)[1]
+            assert np.array_equal(gb.astype(np.float32), gr)
+            win = np.zeros((C, 3, 3, 3), np.float32)                # a at the point's neighbours
+            for dz in (-1, 0, 1):
+                if 0 <= z + dz < nz:
+                    for dy in (-1, 0, 1):
+                        for dx in (-1, 0, 1):
+                            win[:, dz + 1, dy + 1, dx + 1] = a[:, z + dz, (yy + dy) % ny,
+                                                               (x + dx) % nx]
+            exact = gr.astype(np.float64)[:, None, None, None, None] * win.astype(np.float64)
+            err = np.abs(gW.reshape(exact.shape) - exact)
+            assert (err <= bound * np.abs(exact)).all(), (err / np.maximum(np.abs(exact), 1e-300)).max()
+            # the bound tells a form of two parts apart
+            gh, gm, _ = bf16_parts(gr)
+            ah, am, _ = bf16_parts(win)
+            two = (gh + gm)[:, None, None, None, None] * (ah + am)
+            missed = max(missed, (np.abs(two - exact) / np.maximum(np.abs(exact), 1e-300)).max())
+        assert missed > 8 * bound
+    finally:
+        c.close()
