@@ -262,3 +262,16 @@ def test_planes_that_fit_in_lds_only_at_unpadded_strides(grid):
 def test_implicit_step_by_number_of_workgroups(nx, ny):
     """The sums over the workgroups' shares, as in the test above."""
     test_implicit_step_solves_its_equation(nx, ny, (128, 128, 4), 1, 1e-13)
+
+
+@pytest.mark.parametrize("periodic, grid", [(0b011, (375, 16, 4)), (0b011, (16, 375, 4)),
+                                            (0b111, (16, 14, 375))])
+@pytest.mark.parametrize("fft", [1, 2])
+def test_transforms_of_four_passes(periodic, grid, fft):
+    """375 = 3 * 5 * 5 * 5 is the one extent that takes four passes, the most
+    of any, along each axis in turn."""
+    ctx = B.Context.from_problem(mg.kuhn_box((4, 4, 4), 1e-9, periodic=periodic, grid=grid,
+                                             m=[0.0, 0.0, 1.0]), device=0)
+    ctx.set_variant("fft", fft)
+    err, bound = convolution_error(ctx, sum(grid))
+    assert err < bound
