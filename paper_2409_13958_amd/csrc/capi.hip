@@ -402,13 +402,11 @@ bool plan_anterp(const HostOps& o, const std::vector<int2>& bx, const std::vecto
   return false;
 }
 
-// Node lists of k_anterp_line for plan pl, in launch order: per workgroup the
-// nodes of its box columns (column-major, box row, node order), each entry
-// node | row << 26, the list start of every workgroup and the column starts
-// within it (stride sbx + 1).
 // Launch order of the interpolation tiles: those that hold observer rows, the
 // fullest first (in sixteenths of the fullest tile, grid order within one), so
-// that the launch ends with its short workgroups.
+// that the launch ends with its short workgroups. Neighbours share sources, so
+// this order costs L2 hits (the 1.03 M unknown composite reads 1016 MB instead
+// of 911) and still takes 181 us there instead of 212.
 std::vector<int32_t> interp_order(const HostOps& o, const IcPlan& pl) {
   const int nbx = o.nbox[0], nby = o.nbox[1], nbz = o.nbox[2];
   const int64_t nt = (int64_t)pl.nsx * nby * pl.nsz;
@@ -612,6 +610,10 @@ bool plan_scatter(const HostOps& o, ScPlan& pl, std::vector<int2>& list,
          plan_scatter_with(o, pl, list, lstart, tab, true);
 }
 
+// Node lists of k_anterp_line for plan pl, in launch order: per workgroup the
+// nodes of its box columns (column-major, box row, node order), each entry
+// node | row << 26, the list start of every workgroup and the column starts
+// within it (stride sbx + 1).
 bool build_anterp_lists(const HostOps& o, const std::vector<int2>& bx,
                         const std::vector<int2>& by, const std::vector<int2>& bz,
                         const AntPlan& pl, std::vector<int32_t>& list,

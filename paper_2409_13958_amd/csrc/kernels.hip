@@ -1317,9 +1317,7 @@ __device__ __forceinline__ void sum_rows(const double* __restrict__ part, int np
 // the first pass removed more than half of |w|^2: w has lost orthogonality
 __device__ __forceinline__ bool gs_again(double ww, double w2) { return w2 < 0.5 * ww; }
 
-// block b's share of V_j . w for j < nv (and |w|^2 for j = nv where norm), a
-// node's three components per thread; JVP: w = dG/dx z first, with Az = A z
-// from one FP32 field evaluation
+// w = dG/dx z of one node, with Az = A z from one FP32 field evaluation
 __device__ __forceinline__ void mid_jvp(const MidJvp& a, int64_t i, double* __restrict__ w) {
   const double bx = a.mb[3 * i], by = a.mb[3 * i + 1], bz = a.mb[3 * i + 2];
   const double hx = a.H[3 * i], hy = a.H[3 * i + 1], hz = a.H[3 * i + 2];
@@ -1337,6 +1335,8 @@ __device__ __forceinline__ void mid_jvp(const MidJvp& a, int64_t i, double* __re
   w[2] = zz + a.s * (t1z + t2z + a.alpha * (t3z + t4z + t5z));
 }
 
+// block b's share of V_j . w for j < nv, a node's three components per thread;
+// JVP: w = dG/dx z is formed first, and |w|^2 is one more row (j = nv)
 template <bool JVP>
 __device__ __forceinline__ void gs_dots_body(int64_t n, const MidJvp& a,
                                              const float* __restrict__ V, int64_t ldv, int nv,

@@ -66,7 +66,7 @@ struct Surrogate {
   float *gA = nullptr, *gB = nullptr;  // [nvox][C]
   float *y = nullptr, *gy = nullptr;   // [nvox]
   float *qbuf = nullptr, *ubuf = nullptr;  // a training pair's Q and U grids
-  float* part = nullptr;                // weight-gradient partial sums, kSgWPart rows
+  float* part = nullptr;                // weight-gradient partial sums (most workgroups of either kernel)
   double* dred = nullptr;               // reduction partials
   double* loss = nullptr;               // per training pair
   int loss_cap = 0;

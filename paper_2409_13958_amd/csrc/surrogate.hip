@@ -384,7 +384,10 @@ __global__ __launch_bounds__(kSgMT) void k_sg_mid(SgGrid g, const float* __restr
 // products the six above 2^-26 of the whole are formed (v_mfma_f32_16x16x32_bf16),
 // 96 cycles for what FP32 operands take 256. The 32 points' sum is formed from
 // the smallest products on and then added to the running FP32 sum, one
-// rounding for 32 points where FP32 operands round eight times.
+// rounding for 32 points where FP32 operands round eight times. The split holds
+// every bit of operands from about 2^-110 (below, the third part is a subnormal
+// BF16 number) to 3.39e38 (above, the first part rounds to infinity and leaves
+// a remainder that is not a number, as an infinite operand does).
 //
 // A workgroup walks tiles of 16 x 8 points up the planes of a column, a share
 // of the (tile, plane) steps in order, so that each input plane is staged once
