@@ -85,20 +85,26 @@ WORKLOADS = {
 }
 
 
-def measured_traffic(kernel, summary="composite_c3_hbm_traffic.json", source="kernels.hip"):
+# what an evaluation's kernels, their tiles and their launches are made from
+PATH_SOURCES = ("kernels.hip", "fft.hip", "device.h", "kernels.h", "capi.hip", "setup.cpp")
+SURROGATE_SOURCES = ("surrogate.hip", "surrogate.h")
+
+
+def measured_traffic(kernel, summary="composite_c3_hbm_traffic.json", source=PATH_SOURCES):
     """HBM bytes per launch of `kernel` from a committed counter summary, or
-    None when the kernel source has changed since the counters were taken."""
+    None when a source file that it depends on (one name or several) has
+    changed since the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", summary)
-    src = os.path.join(ROOT, "paper_2409_13958_amd", "csrc", source)
     try:
         with open(path) as f:
             rec = json.load(f)
-        with open(src, "rb") as f:
-            h = hashlib.sha256(f.read()).hexdigest()
+        for name in (source,) if isinstance(source, str) else source:
+            with open(os.path.join(ROOT, "paper_2409_13958_amd", "csrc", name), "rb") as f:
+                h = hashlib.sha256(f.read()).hexdigest()
+            if rec.get(name.replace(".", "_") + "_sha256") != h:
+                return None
     except OSError:
-        return None
-    if rec.get(source.replace(".", "_") + "_sha256") != h:
         return None
     for name, b in rec.get("bytes_per_launch", {}).items():
         if name.split("<")[0] == kernel:
@@ -569,7 +575,7 @@ def run_surrogate(args):
                      "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
                      "traffic": (None if args.sg_bf16 else measured_traffic(
-                         "k_sg_mid", "film_c5_surrogate_hbm_traffic.json", "surrogate.hip")),
+                         "k_sg_mid", "film_c5_surrogate_hbm_traffic.json", SURROGATE_SOURCES)),
                      "flop_per_launch": flop_mid,
                      "note": ("algorithmic FLOPs 2*27*32*32 per grid point; the FP32-accurate "
                               "form issues twice as many matrix-core products (BF16 high part "

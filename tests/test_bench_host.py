@@ -44,3 +44,27 @@ def test_traffic_is_dropped_once_the_source_changes(tmp_path, monkeypatch):
     assert bench.measured_traffic("k", "t.json", "k.hip") is None
     shutil.rmtree(csrc)
     assert bench.measured_traffic("k", "t.json", "k.hip") is None
+
+
+def test_traffic_depends_on_every_source_it_is_keyed_on(tmp_path, monkeypatch):
+    """The figures of the evaluation's kernels lapse with any file that the
+    kernels, their tiles or their launches are made from, those of the
+    surrogate with its header too; the committed ones name all of them."""
+    for summary, sources in (("composite_c3_hbm_traffic.json", bench.PATH_SOURCES),
+                             ("film_c5_surrogate_hbm_traffic.json", bench.SURROGATE_SOURCES)):
+        assert bench.measured_traffic({"c": "k_interp_tile", "f": "k_sg_mid"}[summary[0]], summary,
+                                      sources) > 0
+    shutil.copytree(os.path.join(ROOT, "profiles"), tmp_path / "profiles")
+    csrc = tmp_path / "paper_2409_13958_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    for name in bench.PATH_SOURCES:
+        shutil.copy(os.path.join(ROOT, "paper_2409_13958_amd", "csrc", name), csrc / name)
+    assert {"kernels.hip", "fft.hip", "device.h", "kernels.h", "capi.hip"} <= set(bench.PATH_SOURCES)
+    assert bench.measured_traffic("k_interp_tile") > 0
+    for name in bench.PATH_SOURCES:
+        kept = (csrc / name).read_bytes()
+        (csrc / name).write_bytes(kept + b"\n")
+        assert bench.measured_traffic("k_interp_tile") is None, name
+        (csrc / name).write_bytes(kept)
+    assert bench.measured_traffic("k_interp_tile") > 0
