@@ -2897,13 +2897,11 @@ int pmfem_batch_create(pmfem_batch** out, int32_t n_cells, pmfem_ctx* const* cel
   } catch (const std::bad_alloc&) {
     rc = PMFEM_ENOMEM;
   }
-  if (rc) {
-    // the caller gets the batch back to read the message, unless it could not be made
-    *out = b;
-    return rc;
-  }
+  // refused part-way: the caller gets the batch back to read the message, and
+  // without its table every other call refuses it
+  if (rc) b->tab = nullptr;
   *out = b;
-  return PMFEM_OK;
+  return rc;
 }
 
 int pmfem_batch_query(pmfem_batch* b, int64_t* n_unknowns, int64_t* cell_offsets,

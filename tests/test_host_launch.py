@@ -205,3 +205,38 @@ assert grad() == 0 and apply() == 0 and profile() == 0 and heff(ctx) == 0
 for k, a, w in watches:
     assert len(seen(w)) > 0 and (seen(w) != 0).all(), (k, a)
 """, nth, more)
+
+
+@pytest.mark.parametrize("call", ["hipMalloc", "hipMemcpy"])
+def test_a_batch_that_could_not_be_set_up_is_refused(runtime, call):
+    """Whichever allocation or copy of a batch's set-up is refused, its
+    evaluation and steps say so and launch nothing."""
+    child(runtime, """
+call = sys.argv[2]
+cells = [context(film(4, 4)), context(film(5, 4))]
+lib = cells[0].lib
+arr = (ctypes.c_void_p * 2)(*[c.h for c in cells])
+n = sum(c.n for c in cells)
+m, m64 = np.zeros((n, 3), np.float32), np.zeros((n, 3))
+nth = 0
+while True:
+    nth += 1
+    stub.stub_fail(call.encode(), ctypes.c_int64(nth))
+    b = ctypes.c_void_p()
+    rc = lib.pmfem_batch_create(ctypes.byref(b), 2, ctypes.cast(arr, ctypes.c_void_p),
+                                ctypes.c_void_p(1), 0)
+    refused = stub.stub_failed()
+    stub.stub_fail(b"", ctypes.c_int64(0))
+    if not refused:
+        assert rc == 0
+        break
+    assert rc != 0
+    before = stub.stub_launches(b"")
+    if b.value:
+        assert lib.pmfem_batch_heff(b, ptr(m), ptr(m.copy()), 3) == B.Status.ESTATE, nth
+        assert lib.pmfem_batch_llg_step(b, ptr(m64), 1e-15, 0.5, 1) == B.Status.ESTATE, nth
+        assert lib.pmfem_batch_llg_step_graph(b, ptr(m64), 1e-15, 0.5, 1) == B.Status.ESTATE, nth
+        lib.pmfem_batch_destroy(b)
+    assert stub.stub_launches(b"") == before
+assert nth > 20
+""", call)
