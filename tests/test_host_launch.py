@@ -238,5 +238,5 @@ while True:
         assert lib.pmfem_batch_llg_step_graph(b, ptr(m64), 1e-15, 0.5, 1) == B.Status.ESTATE, nth
         lib.pmfem_batch_destroy(b)
     assert stub.stub_launches(b"") == before
-assert nth > 20
+assert nth > 10     # calls of the set-up were refused
 """, call)
